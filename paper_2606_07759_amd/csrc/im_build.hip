@@ -61,7 +61,7 @@ struct PlanJob {
   const int32_t* valid;
   const uint8_t* pupil;
   int n_sub_x, n_sub_y, p, nv;
-  int PH, PW, n_planes, cap_floats;
+  int PH, PW, LPS, n_planes, cap_floats;
   int TX, TY, NSLOT, n_tiles_x;
   int n_tiles, BHmax;
   int H_in, W_in;             // IF grid, for the out-of-grid count (0: not counted)
@@ -77,7 +77,7 @@ struct PlanJob {
   int2* origin;
   int2* hrows;                // [nv] patch rows [x, y) holding a non-zero weight
   double* inv2nk;
-  float* weights;             // [plane][kk][x|y][PH*PW]
+  float* weights;             // [plane][kk][2*PH*PW], in lane order (plan_weight_entry)
   int* slot_kk;               // [tile][NSLOT]
   int4* tile_info;            // [tile] (y0, rows, packed floats, 0)
   int2* rows;                 // [tile][BHmax] (first column, packed offset)
@@ -307,7 +307,7 @@ __global__ __launch_bounds__(PLAN_SUBAPS_BLOCK) void plan_subaps_kernel(
 
 // Weight patch entry gid = (valid subaperture, patch entry): gathers, in a
 // fixed order, every haloed-window sample q whose bilinear cell has this entry
-// as a tap.  Weights layout: [plane][kk][component x|y][PH*PW].  A used entry
+// as a tap.  Weights layout: [plane][kk][2*PH*PW] in lane order.  A used entry
 // widens its subaperture's row range in s_lo/s_hi (index kk - kk0).
 // MULTI = false: the IM plane alone (J.n_planes == 1); the derivative maps and
 // their accumulators then take no registers.
@@ -430,6 +430,14 @@ __device__ __forceinline__ void plan_weight_entry(const PlanJob& J, int E, long 
       }
     }
   const double s = J.inv2nk[kk];
+  // where the stream kernel's lanes read it: lane q of a subaperture holds
+  // patch rows q + LPS i; its floats (component, i, column) are stored four at
+  // a time, the lanes side by side, so that one 16-byte load of a wave
+  // touches one line per subaperture (rows stored whole took one line per
+  // lane: 64 for a wave)
+  const int LPS = J.LPS, fe = (r / LPS) * J.PW + c, FX = (J.PH / LPS) * J.PW;
+  const int at_x = ((fe >> 2) * LPS + r % LPS) * 4 + (fe & 3);
+  const int at_y = (((fe + FX) >> 2) * LPS + r % LPS) * 4 + ((fe + FX) & 3);
   bool used = false;
 #pragma unroll
   for (int j = 0; j < NP; ++j)
@@ -442,8 +450,8 @@ __device__ __forceinline__ void plan_weight_entry(const PlanJob& J, int E, long 
   for (int j = 0; j < NP; ++j) {
     if (j >= n_planes) break;
     float* w = J.weights + ((size_t)j * J.nv + kk) * 2 * E;
-    w[e] = (float)(acc[j][0] * s);
-    w[E + e] = (float)(acc[j][1] * s);
+    w[at_x] = (float)(acc[j][0] * s);
+    w[at_y] = (float)(acc[j][1] * s);
   }
 }
 
@@ -794,12 +802,6 @@ constexpr int MAX_PLANES = 5;
 // Counter ints of a plan: 8 work-item counters per plane, then one XCD sync
 // counter per plane and XCD, each on its own 128-byte line.
 constexpr int COUNTER_INTS = 8 * MAX_PLANES + 8 * MAX_PLANES * 32;
-// The finish count of a single-pair stream launch follows them, on a line of
-// its own; a plan clears all PLAN_COUNTER_INTS, and every stream launch on the
-// plan leaves them zero when it ends.
-constexpr int FINISH_INT = COUNTER_INTS + 32;
-constexpr int PLAN_COUNTER_INTS = FINISH_INT + 32;
-
 // Patch size (columns, rows) a map needs for subapertures of p pixels: the
 // haloed subaperture spans (p+1) output pixels, which the map stretches by
 // the row sums of |A|; a bilinear tap adds one more column/row.
@@ -880,6 +882,32 @@ int tiles_for_variant(const synim_wfs& w, const synim_affine& A, const Variant& 
 
 int persistent_grid(StreamFn fn, int block);
 
+// Relative cost of streaming a geometry through tiles of `ns` slots of variant
+// v.  tile_cost: staged floats per slot (tiles_for_variant), waste: slots of
+// all tiles per grid subaperture.  The terms, each fitted to measured times of
+// every dynamic candidate on seven geometries (8x8 to 80x80 subapertures):
+//  * staged bytes weigh little (ELT build: 16x8 tiles 905 us, 8x8 tiles, with
+//    1.3 times the bytes, 960);
+//  * waves per SIMD that hold slots hide the LDS latency of the contraction
+//    (the same build: 4 waves 905 us, 3 waves 925, 2 waves 1100, 1 wave 1980);
+//  * several workgroups per CU keep one contracting while another waits at
+//    its barrier (one 1024-thread workgroup 990 us, two of 512 threads 905; on
+//    the clocked 12x12 patches, three of 256 threads 937, two of 512 965);
+//  * patches whose weights and read-ahead row do not fit the registers spill
+//    (12x12 at 4 waves per SIMD: MCAO batch 4.4 ms against 3.9 at 3 waves).
+// Ranking by staged bytes alone, with the one-chunk-per-XCD schedule preferred,
+// picked 1420 us for the ELT build, 337 us instead of 98 for 40x40 subapertures
+// of 6 px, and 586 us instead of 108 for 37x37 of 7 px.
+double stream_cost(const Variant& v, int ns, double tile_cost, double waste) {
+  const double waves = stream_waves_per_simd(v.BLOCK, v.NJ4, 4, v.NST);
+  const double w = waves * ns * v.LPS / v.BLOCK;   // waves per SIMD holding slots
+  const double wgs = waves * 256 / v.BLOCK;        // workgroups per CU
+  const int regs = 2 * v.RPL * v.PW + (v.PW >= 12 ? v.PW : 0) + v.RPL + v.NJ4 + 40;
+  return std::pow(waste, 0.25) * (1.0 + tile_cost / 250.0) *
+         (1.0 + 0.264 * std::pow(4.0 / w - 1.0, 1.3)) *
+         (wgs < 2 ? 1.1 : wgs < 3 ? 1.0 : 0.95) * (regs > 512 / waves ? 1.2 : 1.0);
+}
+
 // Every (variant, tile shape, schedule) that can run this geometry with the
 // smallest weight patch that fits, cheapest first by the cost model.  The
 // one-chunk-per-XCD schedule is offered for tile shapes with at most 5/4 as
@@ -903,6 +931,8 @@ int candidate_dims(const synim_wfs& w, const synim_affine& A, Dims* out, double*
     const int m = tiles_for_variant(w, A, v, tmp, tc, 64, pe);
     const int G = persistent_grid(v.im4, v.BLOCK);
     for (int k = 0; k < m; ++k) {
+      tc[k] = stream_cost(v, tmp[k].NSLOT, tc[k],
+                          (double)tmp[k].n_tiles * tmp[k].NSLOT / ((double)w.n_sub_x * w.n_sub_y));
       all.push_back({tc[k], tmp[k]});
       // empty tiles (outside the pupil) are skipped at once, so a few more
       // tiles than resident workgroups still start together
@@ -911,7 +941,7 @@ int candidate_dims(const synim_wfs& w, const synim_affine& A, Dims* out, double*
         // prologue free of block entries
         const int e_min = std::max(2, v.NST - 1);
         const int es[4] = {e_min, std::max(4, e_min), std::max(8, e_min), 0};
-        const double f[4] = {0.85, 0.86, 0.87, 0.9};
+        const double f[4] = {1.06, 1.07, 1.08, 1.1};
         for (int q = 0; q < 4; ++q) {
           if (q > 0 && q < 3 && es[q] == es[q - 1]) continue;
           Dims d = tmp[k];
@@ -1005,7 +1035,7 @@ WsLayout layout(const synim_wfs& w, const Dims& d, int planes, bool repair = fal
   };
   const size_t nv = (size_t)w.n_valid;
   L.status = take(16 * sizeof(int));
-  L.counters = take(PLAN_COUNTER_INTS * sizeof(int));   // work items, sync blocks, finish
+  L.counters = take(COUNTER_INTS * sizeof(int));   // work items, sync blocks
   L.scratch = take(64 * sizeof(float));
   L.origin = take(nv * sizeof(int2));
   L.hrows = take(nv * sizeof(int2));
@@ -1102,6 +1132,7 @@ PlanJob make_job(const synim_wfs& w, const MapD& m, const MapD* m_dev, const Map
   J.nv = w.n_valid;
   J.PH = d.PH;
   J.PW = d.PW;
+  J.LPS = d.var->LPS;
   J.n_planes = planes;
   J.cap_floats = d.var->cap_floats();
   J.TX = d.TX;
@@ -1177,8 +1208,8 @@ int enqueue_plans(const PlanJob& one, const PlanJob* jobs_dev, int n, int max_nv
     hipLaunchKernelGGL(zero_job_status_kernel, dim3((n + 255) / 256), dim3(256), 0, st, jobs_dev,
                        n);
   } else {
-    hipLaunchKernelGGL(zero_plan_kernel, dim3((PLAN_COUNTER_INTS + 255) / 256), dim3(256), 0,
-                       st, one.status, one.counters, PLAN_COUNTER_INTS);
+    hipLaunchKernelGGL(zero_plan_kernel, dim3((COUNTER_INTS + 255) / 256), dim3(256), 0,
+                       st, one.status, one.counters, COUNTER_INTS);
   }
   SYNIM_HIP_TRY(hipGetLastError());
   if (jobs_dev)
@@ -1219,28 +1250,44 @@ int persistent_grid(StreamFn fn, int block) {
   return grid;
 }
 
-// Chunk length: enough (chunk, tile) items per workgroup for dynamic balance,
-// chunks long enough to amortise each item's set-up, and no longer than
-// CHUNK_MAX actuators: neighbouring tiles of a chunk start together and
-// drift apart as they stream it, so short chunks keep their shared halo rows
-// in L2 (measured on the ELT workload: 32 beats 64 by 8%, and 16-48 are
-// within 3% of each other).
-// A batch deals super-chunks of many small per-pair tiles, whose items are
-// short already: there 64 measures best (MCAO workload: 14.1 ms against 14.7
-// at 32).
+// Longest chunk.  Neighbouring tiles of a chunk start together and drift apart
+// as they stream it, so short chunks keep their shared halo rows in L2
+// (measured on the ELT workload: 32 beats 64 by 8%, and 16-48 are within 3%
+// of each other).  A batch deals super-chunks of many small per-pair tiles;
+// there 64 measures best (MCAO workload: 14.1 ms against 14.7 at 32).
 constexpr int CHUNK_MAX = 32, CHUNK_MAX_BATCH = 64;
-int chunk_for(long act_tiles, int G, int cap = CHUNK_MAX) {
-  long chunk = (act_tiles + 4L * G - 1) / (4L * G);
-  return (int)std::max(1L, std::min((long)cap, chunk));
+
+// Chunk length of a batch whose group i streams n_act[i] actuators through
+// tiles[i] tiles: every workgroup gets the same number of items (one for a
+// batch whose share of a workgroup stays within CHUNK_MAX_BATCH actuators).
+// An item's set-up (row table, weight patches, pipeline fill) costs as much as
+// several actuators, so splitting finer for balance loses more than it gains
+// (20x20 subapertures, 373 actuators: 70 us at four items per workgroup, 42
+// at one).
+int batch_chunk(const std::vector<int>& n_act, const std::vector<int>& tiles, int G) {
+  long work = 0;
+  for (size_t i = 0; i < n_act.size(); ++i) work += (long)n_act[i] * tiles[i];
+  const long rounds = std::max(1L, (work + (long)G * CHUNK_MAX_BATCH - 1) / ((long)G * CHUNK_MAX_BATCH));
+  long chunk = std::max(1L, (work + G * rounds - 1) / (G * rounds));
+  // the last, shorter chunks of the groups count as items too
+  for (; chunk < 2 * CHUNK_MAX_BATCH; ++chunk) {
+    long items = 0;
+    for (size_t i = 0; i < n_act.size(); ++i)
+      items += (n_act[i] + chunk - 1) / chunk * (long)tiles[i];
+    if (items <= G * rounds) break;
+  }
+  return (int)std::min<long>(chunk, CHUNK_MAX_BATCH);
 }
 
-// Chunks of a single-pair launch: as chunk_for asks, rounded up to a multiple
-// of 8 so that every XCD queue holds the same number, the actuators split
-// evenly over them (lengths differ by at most one).
+// Chunks of a single-pair launch: as many as give every workgroup the same
+// number of items (one, for a stack that a workgroup's share of stays within
+// CHUNK_MAX actuators), a multiple of 8 so that every XCD queue holds the same,
+// the actuators split evenly over them (lengths differ by at most one).
 int chunks_for(int n_act, int n_tiles, int G) {
-  const long len = chunk_for((long)n_act * n_tiles, G);
-  long nc = (n_act + len - 1) / len;
-  nc = (nc + 7) / 8 * 8;
+  const long per_round = std::max(1, G / n_tiles);
+  const long rounds = (n_act + per_round * CHUNK_MAX - 1) / (per_round * CHUNK_MAX);
+  long nc = per_round * rounds;
+  if (nc > 8) nc = nc / 8 * 8;
   return (int)std::min<long>(nc, n_act);
 }
 
@@ -1281,11 +1328,22 @@ int launch_stream(const Plan& P, const float* ifs, int n_act, int H_in, int W_in
   const bool vec4 = (W_in % 4 == 0) && ((reinterpret_cast<uintptr_t>(ifs) & 15) == 0);
   if ((long)H_in * W_in * 4 > INT_MAX) return SYNIM_E_SHAPE;   // 32-bit DMA offsets
   StreamFn fn = pick_fn(v, vec4, grad != nullptr);
-  const int G = persistent_grid(fn, v.BLOCK);
+  int G = persistent_grid(fn, v.BLOCK);
   if (G < 0) return SYNIM_E_HIP;
   if (grad && G > GMAX_VJP) return SYNIM_E_SHAPE;
   StreamArgs g{};
-  const int n_chunks = d.sched == SCHED_XCD ? std::min(8, n_act) : chunks_for(n_act, d.n_tiles, G);
+  int n_chunks = std::min(8, n_act);
+  if (d.sched == SCHED_DYNAMIC) {
+    // the planes of a launch share the resident workgroups, and no workgroup
+    // is launched that could get no item (one without an item still takes
+    // its turn on the counters: the 8x8 gradient's four planes ran 2048
+    // workgroups for 616 items)
+    G = std::max(8, G / nplanes / 8 * 8);
+    n_chunks = chunks_for(n_act, d.n_tiles, G);
+    const long items = (long)n_chunks * d.n_tiles;
+    if (items <= G) g.one_round = n_chunks % 8 == 0 ? 1 : 2;
+    G = (int)std::min<long>(G, (items + 7) / 8 * 8);
+  }
   g.one = pair_desc(P, ifs, n_act, H_in, W_in, nv, out, 0, n_chunks);
   g.pairs = nullptr;
   g.counters = P.counters();
@@ -1297,10 +1355,7 @@ int launch_stream(const Plan& P, const float* ifs, int n_act, int H_in, int W_in
   g.sync_every = d.sched == SCHED_XCD ? d.sync_every : 0;
   g.sync_ctr = P.counters() + 8 * MAX_PLANES;
   g.n_active = P.status() + 1;
-  // the plan cleared the counters, and every launch on it clears them as it
-  // ends (its last workgroup)
-  g.finish = P.counters() + FINISH_INT;
-  g.n_counters = COUNTER_INTS;
+  // (the plan cleared the counters, and every launch on it leaves them zero)
   hipLaunchKernelGGL(fn, dim3((unsigned)G, 1, nplanes), dim3(v.BLOCK), 0, st, g);
   SYNIM_HIP_TRY(hipGetLastError());
   if (grid_out) *grid_out = G;
@@ -2115,7 +2170,7 @@ const Variant* batch_variant(const synim_batch* b, int rank) {
         ok = false;
         break;
       }
-      total += cost[0] * b->wfs[pr.wfs].n_valid;
+      total += stream_cost(v, v.BLOCK / v.LPS, cost[0], 1.0) * b->wfs[pr.wfs].n_valid;
     }
     if (ok) ranked.push_back({total, i});
   }
@@ -2139,19 +2194,14 @@ int batch_bind(synim_batch* b, const Variant& v, hipStream_t st) {
   StreamFn fn = pick_fn(v, b->vec4, false, true);
   b->G = persistent_grid(fn, v.BLOCK);
   if (b->G < 0) return SYNIM_E_HIP;
-  long act_tiles = 0;
-  if (b->shared) {
-    for (int gi = 0; gi < b->n_groups; ++gi)
-      for (int i = 0; i < np; ++i)
-        if (b->group[i] == gi) {
-          act_tiles += (long)b->dms[b->pairs[i].dm].n_act * b->jgroups_host[gi].y;
-          break;
-        }
-  } else {
-    for (int i = 0; i < np; ++i)
-      act_tiles += (long)b->dms[b->pairs[i].dm].n_act * b->plans[i].d.n_tiles;
+  b->G = std::max(8, b->G / b->planes / 8 * 8);   // the planes share the workgroups
+  std::vector<int> grp_act(b->n_groups, 0), grp_tiles(b->n_groups, 0);
+  for (int i = 0; i < np; ++i) {
+    const int gi = b->group[i];
+    grp_act[gi] = b->dms[b->pairs[i].dm].n_act;
+    grp_tiles[gi] = b->shared ? b->jgroups_host[gi].y : grp_tiles[gi] + b->plans[i].d.n_tiles;
   }
-  const int chunk = chunk_for(act_tiles, b->G, CHUNK_MAX_BATCH);
+  const int chunk = batch_chunk(grp_act, grp_tiles, b->G);
   // pair table in DM order, groups, super-chunk records
   std::vector<PairDesc> pd(np);
   std::vector<int2> groups(b->n_groups, make_int2(0, 0));
@@ -2195,6 +2245,10 @@ int batch_bind(synim_batch* b, const Variant& v, hipStream_t st) {
     }
     b->xcd_items[x] = acc;
   }
+  // no workgroup that could get no item
+  long items = 0;
+  for (int x = 0; x < 8; ++x) items += b->xcd_items[x];
+  b->G = (int)std::max(8L, std::min<long>(b->G, (items + 7) / 8 * 8));
   b->n_recs = (int)recs.size();
   b->recs_host = recs;
   std::vector<PlanJob> jobs(np);
@@ -2287,6 +2341,9 @@ int batch_enqueue(synim_batch* b, hipStream_t st, int n_groups = -1) {
     g.rec_cnt[x] = b->rec_cnt[x];
     g.xcd_items[x] = items[x];
   }
+  g.one_round = 1;
+  for (int x = 0; x < 8; ++x)
+    if (8 * b->xcd_items[x] > b->G) g.one_round = 0;
   g.counters = reinterpret_cast<int*>(b->ws + b->off_ctr);
   g.scratch = reinterpret_cast<float*>(b->ws + b->off_scratch);
   hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, g.counters, 8 * b->planes);

@@ -56,7 +56,9 @@ struct StreamArgs {
   const SuperChunk* recs;    // batched: per-XCD records, XCD x at recs[rec_off[x]..]
   const int2* groups;        // batched: per DM (first pair, number of pairs)
   int rec_off[8], rec_cnt[8], xcd_items[8];
-  int* counters;             // [gridDim.z][8] work counters, zero at the launch
+  // [gridDim.z][8] work counters, zero at the launch; a single-pair launch
+  // leaves them (and the sync counters) zero as it ends
+  int* counters;
   float* scratch;            // 64 floats that absorb the stores of idle lanes
   int plane0;                // first weight plane handled (blockIdx.z adds to it)
   int out_plane0;            // weight plane that lands in out[0]
@@ -79,12 +81,14 @@ struct StreamArgs {
   const int2* jrows;         // [tile][jBHmax] (first column, packed offset)
   const int2* jgroups;       // per DM group: (first shared tile, count)
   int jNS, jBHmax;
-  // Single-pair launches: the last workgroup to finish sets the n_counters
-  // ints from `counters` (work and sync counters) and *finish back to zero,
-  // so the next launch on the same plan needs no clearing launch before it.
-  // nullptr: the caller clears the counters (batched launches).
-  int* finish;
-  int n_counters;
+  // 1: no queue holds more items than workgroups, so each workgroup's first
+  // item is its only one and the counters stay untouched; 2: so, and the
+  // chunks are no multiple of 8: workgroup b takes tile b mod n_tiles of chunk
+  // b / n_tiles.  Atomics of many workgroups on one address are served one
+  // after another: with a first claim, a last, failing claim and a finish
+  // count per workgroup, 504 one-item workgroups (20x20 subapertures, 373
+  // actuators) took 41 us, without them 21.
+  int one_round;
 };
 
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -258,6 +262,7 @@ im_stream_kernel(StreamArgs g) {
   constexpr int E = PH * PW;
   constexpr int STAGE_F4 = NJ * BLOCK * VW / 4;   // float4 per stage buffer
   constexpr int KPMAX = stage_pack(NJ, NST, PACK);
+  static_assert(RPL * PW % 2 == 0, "a lane's weights load as float4");
   static_assert(NST >= 2 && NST <= 8, "2..8 stages");
   static_assert(NJ * (NST - 2) <= 63, "vmcnt range");
   __shared__ int s_item;
@@ -270,10 +275,11 @@ im_stream_kernel(StreamArgs g) {
   const int slot = tid / LPS, q = tid % LPS;
   const int xcd = blockIdx.x & 7;
   const int plane = g.plane0 + blockIdx.z;
-  // Items of XCD queue x.  A workgroup starts on its own XCD's queue and,
-  // once that is empty, takes what is left in the other queues (in order
-  // x+1, x+2, ...), so no XCD idles while another still has items.  With
-  // the bounded-lag sync on, the workgroups of an XCD must stay on its queue.
+  // Items of XCD queue x.  The queues of a single-pair launch hold the same
+  // number of items, and a workgroup stays on its XCD's.  Those of a batch
+  // differ: there a workgroup whose queue is empty takes what is left in the
+  // others (in order x+1, x+2, ...), so no XCD idles while another still has
+  // items.
   auto queue_items = [&](int x) {
     if (BATCH && g.pairs != nullptr) {
       return g.xcd_items[x];
@@ -282,9 +288,9 @@ im_stream_kernel(StreamArgs g) {
       return nc_x * g.one.n_tiles;
     }
   };
-  const bool may_steal = !((!BATCH || g.pairs == nullptr) && g.sync_every > 0);
+  const bool may_steal = BATCH && g.pairs != nullptr;
   int qx = xcd;
-  int n_items = queue_items(qx);
+  int n_items = g.one_round == 2 ? g.one.n_chunks * g.one.n_tiles : queue_items(qx);
   int* ctr = g.counters + 8 * blockIdx.z + qx;
   // queues other than its own that still held items when the workgroup last
   // looked (bit i: queue xcd + 1 + i); -1 before the first look
@@ -295,13 +301,36 @@ im_stream_kernel(StreamArgs g) {
   // pipeline loop head would make the compiler drain the DMA queue there
   const int n_part = (!BATCH || g.pairs == nullptr) && g.sync_every > 0 ? *g.n_active : 0;
 
+  // items of each queue that its workgroups take without asking: workgroup b
+  // starts on item b / 8 of queue b mod 8, the counter hands out what follows
+  const int given = (int)gridDim.x >> 3;
+  bool first = true;
   for (;;) {
-    __syncthreads();   // the previous item's stage buffers and row table are free again
-    if (tid == 0) s_item = atomicAdd(ctr, 1);
-    __syncthreads();
-    const int item = s_item;
+    int item;
+    if (first) {
+      first = false;
+      item = g.one_round == 2 ? blockIdx.x : blockIdx.x >> 3;
+    } else {
+      if (g.one_round) break;
+      __syncthreads();   // the previous item's stage buffers and row table are free again
+      if (tid == 0) s_item = atomicAdd(ctr, 1) + given;
+      __syncthreads();
+      item = s_item;
+    }
     if (item >= n_items) {
-      if (!may_steal) break;
+      if (g.one_round || (!may_steal && item < given)) break;
+      if (!may_steal) {
+        // Every workgroup of the queue that had an item makes one claim too
+        // many; the last of them (its counter operations and those of the
+        // others have all returned) leaves the queue's counters zero for the
+        // next launch, with plain stores that the end of the kernel makes
+        // visible.
+        if (item - given == n_items - 1 && tid == 0) {
+          *ctr = 0;
+          if (g.sync_every > 0) g.sync_ctr[(8 * blockIdx.z + xcd) * SYNC_STRIDE] = 0;
+        }
+        break;
+      }
       if (others < 0) {
         // one parallel look at the other seven counters (they only grow, so
         // a queue seen exhausted stays exhausted)
@@ -311,7 +340,7 @@ im_stream_kernel(StreamArgs g) {
           const int x = (xcd + 1 + tid) & 7;
           const int c = __hip_atomic_load(g.counters + 8 * blockIdx.z + x, __ATOMIC_RELAXED,
                                           __HIP_MEMORY_SCOPE_AGENT);
-          if (c < queue_items(x)) atomicOr(&s_others, 1 << tid);
+          if (c + given < queue_items(x)) atomicOr(&s_others, 1 << tid);
         }
         __syncthreads();
         others = s_others;
@@ -331,7 +360,7 @@ im_stream_kernel(StreamArgs g) {
       P = g.one;
       const int m = item / P.n_tiles;
       tile = item - m * P.n_tiles;
-      chunk_id = qx + 8 * m;
+      chunk_id = g.one_round == 2 ? m : qx + 8 * m;
     } else {
       // the record holding this item, then the pair within its DM group
       const SuperChunk* rec = g.recs + g.rec_off[qx];
@@ -398,6 +427,9 @@ im_stream_kernel(StreamArgs g) {
     } else {
       kk = slot < P.ns ? P.slot_kk[(size_t)tile * P.ns + slot] : -1;
     }
+    // waves whose slots are all empty stage their share of the rows but have
+    // nothing to contract or store
+    const bool wave_on = __ballot(kk >= 0) != 0ull;
     const int2* rows = s_rows;
 
     int2 o = make_int2(0, 0), hr = make_int2(0, 0);
@@ -469,13 +501,19 @@ im_stream_kernel(StreamArgs g) {
     }
     float wx[RPL][PW], wy[RPL][PW];
     if (kk >= 0) {
-      const float* W = weights_l + ((size_t)plane * nv_l + kk) * 2 * E;
+      // this lane's floats (component, row, column), four to a load, the
+      // subaperture's lanes side by side
+      const float4* W = reinterpret_cast<const float4*>(
+                            weights_l + ((size_t)plane * nv_l + kk) * 2 * E) + q;
 #pragma unroll
-      for (int i = 0; i < RPL; ++i) {
+      for (int f4 = 0; f4 < RPL * PW / 2; ++f4) {
+        const float4 w4 = W[f4 * LPS];
+        const float w[4] = {w4.x, w4.y, w4.z, w4.w};
 #pragma unroll
-        for (int c = 0; c < PW; ++c) {
-          wx[i][c] = W[(q + LPS * i) * PW + c];
-          wy[i][c] = W[E + (q + LPS * i) * PW + c];
+        for (int u = 0; u < 4; ++u) {
+          const int f = 4 * f4 + u;
+          if (f < RPL * PW) wx[f / PW][f % PW] = w[u];
+          else wy[(f - RPL * PW) / PW][(f - RPL * PW) % PW] = w[u];
         }
       }
     } else {
@@ -497,7 +535,9 @@ im_stream_kernel(StreamArgs g) {
     int* sync_ctr = g.sync_ctr + (8 * blockIdx.z + xcd) * SYNC_STRIDE;
     bool sync_live = true;
 
-    auto consume = [&](const float4* buf, int gi) {
+    // (inlined by hand: left to the compiler, the packing variants with large
+    // patches kept a call here, and their weights in scratch memory with it)
+    auto consume = [&](const float4* buf, int gi) __attribute__((always_inline)) {
       const float* fb = reinterpret_cast<const float*>(buf);
 #pragma unroll
       for (int kp = 0; kp < KPMAX; ++kp) {
@@ -542,8 +582,8 @@ im_stream_kernel(StreamArgs g) {
           if (act && kk >= 0 && q == 0)
             vacc += (double)g.grad[row + kk] * sx + (double)g.grad[row + nv_l + kk] * sy;
         } else {
-          // exactly one store instruction per wave and actuator slot, whatever
-          // the lanes hold (the pipeline's wait counts rely on this number).
+          // exactly one store instruction per (contracting) wave and actuator
+          // slot, whatever the lanes hold (the pipeline's wait counts rely on this number).
           // Every lane of a subaperture holds both sums after the DPP
           // reduction: even lanes store s_x, odd lanes s_y, so the extra
           // lanes repeat a real store (same address, same value) and add no
@@ -566,7 +606,7 @@ im_stream_kernel(StreamArgs g) {
     // Loads group gi into stage k.  With the XCD sync on, lane 0 first adds
     // the workgroup's entry when gi opens a block, then snapshots the counter
     // into s_snap[k]; both precede the stage's DMA.
-    auto issue = [&](int k, float4* buf, int gi) {
+    auto issue = [&](int k, float4* buf, int gi) __attribute__((always_inline)) {
       if (sync_on && tid == 0) {
         if (gi % sync_e == 0) atomicAdd(sync_ctr, 1);
         snapshot_issue(sync_ctr, s_snap + k);
@@ -594,10 +634,10 @@ im_stream_kernel(StreamArgs g) {
     // too long stops waiting but keeps adding its entries, so the counts stay
     // exact).  Wave 0 also issues, per loaded group, the snapshot and
     // possibly an entry atomic; its wait counts them.
-    auto step = [&](auto kc, int gi) {
+    auto step = [&](auto kc, int gi) __attribute__((always_inline)) {
       constexpr int K = decltype(kc)::value;
       const int later = min(NST - 2, n_grp - 1 - gi);
-      const int stores = VJP ? 0 : KP * min(gi, NST - 1);
+      const int stores = VJP || !wave_on ? 0 : KP * min(gi, NST - 1);
       const int x = gi + NST - 1;   // the group this step starts loading
       int extra = 0;
       if (sync_on && wave == 0) extra = later + (gi + later) / sync_e - gi / sync_e;
@@ -618,7 +658,7 @@ im_stream_kernel(StreamArgs g) {
       }
       stage_barrier();
       if (x < n_grp) issue((K + NST - 1) % NST, stage_buf<(K + NST - 1) % NST, STAGE_F4>(), x);
-      consume(stage_buf<K, STAGE_F4>(), gi);
+      if (wave_on) consume(stage_buf<K, STAGE_F4>(), gi);
     };
     // every compiler-tracked load of the item (weights, rows) has landed
     // before the first DMA; otherwise the compiler would wait for them at
@@ -647,25 +687,7 @@ im_stream_kernel(StreamArgs g) {
       g.partials[(size_t)(plane - 1) * gridDim.x + blockIdx.x] = s;
     }
   }
-  if (g.finish != nullptr) {
-    // Every workgroup has taken its last item before it counts itself
-    // finished: its counter operations are device-scope atomics whose
-    // results it waited for, so they are performed before its finish count.
-    // The last one clears the counters with plain stores, which the end of
-    // the kernel makes visible to the next launch.  (No fence: a device-scope
-    // release here would write back the XCD's L2 at every workgroup's exit.)
-    __shared__ int s_last;
-    __syncthreads();
-    if (tid == 0)
-      s_last = atomicAdd(g.finish, 1) == (int)(gridDim.x * gridDim.y * gridDim.z) - 1;
-    __syncthreads();
-    if (s_last) {
-      for (int i = tid; i < g.n_counters; i += BLOCK) g.counters[i] = 0;
-      if (tid == 0) *g.finish = 0;
-    }
-  }
 }
-
 
 // ------------------------------------------------------------------- variants
 
