@@ -9,6 +9,7 @@
 // [B][len0 + len1] and compact column c feeds W1 column seg0 + c (c < len0) or
 // seg1 + c - len0; the zero inputs contribute nothing and are skipped exactly.
 #include <algorithm>
+#include <climits>
 #include <cmath>
 
 #include "common.hpp"
@@ -217,6 +218,292 @@ int gemm(int M, int N, int K, float alpha, const float* A, int lda, const float*
   return SYNIM_OK;
 }
 
+// ------------------------------------------------- direct FP32 products
+// C = X Y of small products whose operands allow 16-byte loads, without a
+// workgroup-wide staging pipeline.  What bounds such a product is latency (the
+// input layer, [256 x 2080] x [2080 x 512], is 0.55 GFLOP), so the W waves of a
+// workgroup split K over one 16 BM x 16 BN tile of C, each keeps several 32-deep
+// steps of loads in flight, and their partial tiles are added once, in wave
+// order, through LDS; no step of the product waits at a barrier.
+//   v_mfma_f32_16x16x4f32: lane l feeds A[l%16][l/16] and B[l/16][l%16] and holds
+// D[4(l/16) + r][l%16].  A 32-deep step is eight of them; a lane's k in the e-th is
+// 8(l/16) + e.  An operand contiguous across k (not AK, BK) is loaded as the lane
+// needs it, a BM- (BN-) wide vector per e, whose element i belongs to block i (row
+// BM r + i of the tile).  One contiguous in k is loaded in whole 128-byte row
+// segments, eight lanes each, and turned through LDS of the wave's own (loaded
+// as needed, no two neighbouring lanes would read one row: 62 cache accesses
+// per load, and the input layer took 16 us in place of 13).
+// Measured on the training step of the estimator (B = 256): input layer 28 us
+// before (column gather, staged product, split-K reduction), 13 now; a step
+// 162 us and 24 launches before, 70 us and 7 now, of which 18 are Adam's.
+struct DGemm {
+  int M, N, K;
+  const float* X;    // AK: X[m][k] (ldx), else X[k][m]
+  const float* Y;    // BK: Y[n][k] (ldy), else Y[k][n]
+  long ldx, ldy;
+  float* C;
+  long ldc;
+  const float* bias;   // [N], added (nullable)
+  const float* mask;   // [M][ldc]: C = 0 where it is not positive (nullable)
+  int relu;
+  // column maps (input layer): k of Y (BK), or column n of C, from len0 on
+  // lies at shift + itself
+  int len0, shift;     // len0 = INT_MAX: none
+  float* rowsum;       // [M]: sum over k of X(k, m) (nullable; !AK)
+  // zero fill of C's columns outside the map by the workgroups past the tiles
+  int zero_cols;       // full width of C (0: none)
+  int col0;            // first mapped column
+};
+
+template <int V>
+__device__ __forceinline__ void load_vec(const float* p, float (&r)[V]) {
+  if constexpr (V == 4) {
+    const float4 t = *reinterpret_cast<const float4*>(p);
+    r[0] = t.x; r[1] = t.y; r[2] = t.z; r[3] = t.w;
+  } else if constexpr (V == 2) {
+    const float2 t = *reinterpret_cast<const float2*>(p);
+    r[0] = t.x; r[1] = t.y;
+  } else {
+    r[0] = *p;
+  }
+}
+
+constexpr int DIRECT_PITCH = 36;   // floats from row to row of a turned step
+
+// Registers one operand of a 32-deep step takes per lane: 8 NB floats.
+// Contiguous in k: float4 j is row 8 j + l/8, k = 4(l%8); else element e NB + i.
+// Rows (or vectors) past the operand's extent repeat its last; k past ke reads
+// zero (ke is a multiple of 4 where the operand is contiguous in k).
+template <int NB, bool KC>
+__device__ __forceinline__ void direct_load(const float* P, long ld, int m0, int M, int k0, int ke,
+                                            int len0, int shift, int lane, float (&r)[8 * NB]) {
+  if constexpr (KC) {
+    const int k = k0 + 4 * (lane & 7);
+    const float* base = P + (k < len0 ? k : k + shift);
+#pragma unroll
+    for (int j = 0; j < 2 * NB; ++j) {
+      const int m = min(m0 + 8 * j + (lane >> 3), M - 1);
+      float t[4] = {0.f, 0.f, 0.f, 0.f};
+      if (k < ke) load_vec<4>(base + (long)m * ld, t);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) r[4 * j + u] = t[u];
+    }
+  } else {
+    const int m = min(m0 + NB * (lane & 15), M - NB);
+    const int k = k0 + 8 * (lane >> 4);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float t[NB];
+#pragma unroll
+      for (int i = 0; i < NB; ++i) t[i] = 0.f;
+      if (k + e < ke) load_vec<NB>(P + (long)(k + e) * ld + m, t);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) r[e * NB + i] = t[i];
+    }
+  }
+}
+
+// Orders a wave's own LDS writes before its lanes' reads of each other's (and
+// the other way round); the LDS serves a wave's operations in order.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+template <int NB>
+__device__ __forceinline__ void direct_put(const float (&r)[8 * NB], float* lds, int lane) {
+#pragma unroll
+  for (int j = 0; j < 2 * NB; ++j)
+    *reinterpret_cast<float4*>(lds + (8 * j + (lane >> 3)) * DIRECT_PITCH + 4 * (lane & 7)) =
+        make_float4(r[4 * j], r[4 * j + 1], r[4 * j + 2], r[4 * j + 3]);
+}
+// block i's values for the four e of half h
+template <int NB>
+__device__ __forceinline__ void direct_get(const float* lds, int h, int lane, float (&v)[4][NB]) {
+#pragma unroll
+  for (int i = 0; i < NB; ++i) {
+    float t[4];
+    load_vec<4>(lds + (16 * i + (lane & 15)) * DIRECT_PITCH + 8 * (lane >> 4) + 4 * h, t);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s][i] = t[s];
+  }
+}
+
+// LDS floats a wave turns its operands in
+constexpr int direct_turn(int bm, int bn, bool ak, bool bk) {
+  return ((ak ? bm : 0) + (bk ? bn : 0)) * 16 * DIRECT_PITCH;
+}
+
+template <int BM, int BN, bool AK, bool BK>
+__device__ __forceinline__ void direct_tile(const DGemm& g, int tile, float* lds) {
+  constexpr int TM = 16 * BM, TN = 16 * BN;
+  constexpr int DEPTH = BM * BN >= 4 ? 2 : 4;   // steps of loads in flight
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, W = blockDim.x >> 6;
+  // Consecutive workgroups go to the 8 XCDs in turn.  Where the column tiles
+  // divide by 8, an XCD takes an eighth of them with every row tile, so that
+  // its L2 reads its own eighth of Y (the weights) and X once; otherwise row by
+  // row of tiles.
+  const int tn = (g.N + TN - 1) / TN;
+  int tm_i = tile / tn, tn_i = tile % tn;
+  if (tn % 8 == 0) {
+    const int per = tn / 8, q = tile >> 3;
+    tn_i = (tile & 7) * per + q % per;
+    tm_i = q / per;
+  }
+  const int m0 = tm_i * TM, n0 = tn_i * TN;
+  const int steps = (g.K + 31) / 32;
+  const int s0 = (int)((long)steps * wave / W), s1 = (int)((long)steps * (wave + 1) / W);
+  f32x4 acc[BM][BN];
+#pragma unroll
+  for (int i = 0; i < BM; ++i)
+#pragma unroll
+    for (int j = 0; j < BN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float rs[BM];
+#pragma unroll
+  for (int i = 0; i < BM; ++i) rs[i] = 0.f;
+  float* const turn_a = lds + (size_t)wave * direct_turn(BM, BN, AK, BK);
+  float* const turn_b = turn_a + (AK ? BM * 16 * DIRECT_PITCH : 0);
+  float a[DEPTH][8 * BM], b[DEPTH][8 * BN];
+  auto load = [&](int d, int st) {
+    direct_load<BM, AK>(g.X, g.ldx, m0, g.M, 32 * st, g.K, INT_MAX, 0, lane, a[d]);
+    direct_load<BN, BK>(g.Y, g.ldy, n0, g.N, 32 * st, g.K, BK ? g.len0 : INT_MAX, g.shift, lane,
+                        b[d]);
+  };
+#pragma unroll
+  for (int d = 0; d < DEPTH; ++d)
+    if (s0 + d < s1) load(d, s0 + d);
+  for (int st = s0; st < s1; st += DEPTH) {
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+      if (st + d >= s1) break;
+      if constexpr (AK || BK) {
+        wave_sync();
+        if constexpr (AK) direct_put<BM>(a[d], turn_a, lane);
+        if constexpr (BK) direct_put<BN>(b[d], turn_b, lane);
+        wave_sync();
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        float va[4][BM], vb[4][BN];
+        if constexpr (AK) direct_get<BM>(turn_a, h, lane, va);
+        if constexpr (BK) direct_get<BN>(turn_b, h, lane, vb);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          if constexpr (!AK)
+#pragma unroll
+            for (int i = 0; i < BM; ++i) {
+              va[s][i] = a[d][(4 * h + s) * BM + i];
+              rs[i] += va[s][i];
+            }
+          if constexpr (!BK)
+#pragma unroll
+            for (int j = 0; j < BN; ++j) vb[s][j] = b[d][(4 * h + s) * BN + j];
+#pragma unroll
+          for (int i = 0; i < BM; ++i)
+#pragma unroll
+            for (int j = 0; j < BN; ++j)
+              acc[i][j] =
+                  __builtin_amdgcn_mfma_f32_16x16x4f32(va[s][i], vb[s][j], acc[i][j], 0, 0, 0);
+        }
+      }
+      if (st + d + DEPTH < s1) load(d, st + d + DEPTH);
+    }
+  }
+  if constexpr (AK || BK) __syncthreads();   // the turning space is the partial tiles' now
+  // The waves' partial tiles, row-major (+1 float per row against conflicts):
+  // the upper half of the waves hands its tiles to the lower half, whose sums
+  // then lie side by side (half the LDS of all tiles at once).
+  constexpr int LD = TN + 1;
+  const int H = W >> 1;
+  float* mine = lds + (size_t)(wave >= H ? wave - H : wave) * TM * LD;
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+      for (int j = 0; j < BN; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int rr = 4 * (lane >> 4) + r;
+          const int row = AK ? 16 * i + rr : BM * rr + i;
+          const int col = BK ? 16 * j + (lane & 15) : BN * (lane & 15) + j;
+          f(acc[i][j][r], mine[row * LD + col]);
+        }
+  };
+  if (wave >= H) each([](float v, float& slot) { slot = v; });
+  __syncthreads();
+  if (wave < H) each([](float v, float& slot) { slot = v + slot; });
+  const bool sums = !AK && g.rowsum != nullptr && n0 == 0;
+  float* rsl = lds + (size_t)H * TM * LD;   // [W][4][TM]
+  if (sums) {
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+      rsl[(wave * 4 + (lane >> 4)) * TM + BM * (lane & 15) + i] = rs[i];
+  }
+  __syncthreads();
+  for (int e = tid; e < TM * TN; e += blockDim.x) {
+    const int row = e / TN, col = e % TN;
+    float v = 0.f;
+    for (int w = 0; w < H; ++w) v += lds[((size_t)w * TM + row) * LD + col];
+    const int m = m0 + row, n = n0 + col;
+    if (m >= g.M || n >= g.N) continue;
+    if (g.bias) v += g.bias[n];
+    if (g.relu) v = fmaxf(v, 0.f);
+    if (g.mask && !(g.mask[(long)m * g.ldc + n] > 0.f)) v = 0.f;
+    g.C[(long)m * g.ldc + (BK ? n : (n < g.len0 ? n : n + g.shift))] = v;
+  }
+  if (sums)
+    for (int row = tid; row < TM; row += blockDim.x) {
+      float v = 0.f;
+      for (int w = 0; w < 4 * W; ++w) v += rsl[w * TM + row];
+      if (m0 + row < g.M) g.rowsum[m0 + row] = v;
+    }
+}
+
+// Tiles of one product (t1 = 0), or of two that share a launch; before them
+// (they only store, and overlap the tiles' loads) the nz workgroups that zero
+// C's unmapped columns, ZERO_ROWS rows each, rounded up to a multiple of 8.
+constexpr int ZERO_ROWS = 1;
+template <int BM, int BN, bool AK, bool BK, int BM1, int BN1, bool AK1, bool BK1>
+__global__ __launch_bounds__(512) void direct_kernel(int nz, DGemm g, int t0, DGemm h, int t1) {
+  extern __shared__ __align__(16) float dyn_lds[];
+  const int t = (int)blockIdx.x - nz;
+  if (t >= 0 && t < t0) {
+    direct_tile<BM, BN, AK, BK>(g, t, dyn_lds);
+  } else if (t >= t0) {
+    direct_tile<BM1, BN1, AK1, BK1>(h, t - t0, dyn_lds);
+  } else {
+    // columns [0, col0), the gap between the segments, and what follows them
+    const int m0 = (int)blockIdx.x * ZERO_ROWS;
+    const int end0 = g.col0 + g.len0;                       // end of the first segment
+    const int beg1 = g.col0 + g.len0 + g.shift;             // start of the second
+    const int end1 = g.col0 + g.shift + g.N;
+    float* C0 = g.C - g.col0;
+    for (int r = 0; r < ZERO_ROWS && m0 + r < g.M; ++r) {
+      float* row = C0 + (long)(m0 + r) * g.ldc;
+      for (int c = 4 * threadIdx.x; c < g.zero_cols; c += 4 * blockDim.x) {
+        const bool used = (c >= g.col0 && c < end0) || (c >= beg1 && c < end1);
+        if (!used) *reinterpret_cast<float4*>(row + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+      }
+    }
+  }
+}
+
+constexpr int direct_lds(int W, int bm, int bn, bool ak, bool bk) {
+  return std::max(W / 2 * 16 * bm * (16 * bn + 1) + W * 4 * 16 * bm,
+                  W * direct_turn(bm, bn, ak, bk)) * (int)sizeof(float);
+}
+inline int direct_tiles(int M, int N, int bm, int bn) {
+  return ((M + 16 * bm - 1) / (16 * bm)) * ((N + 16 * bn - 1) / (16 * bn));
+}
+// Waves per workgroup: as many as leave each at least two 32-deep steps, while
+// the tiles alone do not give every SIMD a few waves.
+inline int direct_waves(int tiles, int K, int most) {
+  int W = 4;
+  while (W < most && (long)tiles * W < 256 * 8 && (K + 31) / 32 >= 4 * W) W *= 2;
+  return W;
+}
+
 // Small batches (B <= 16): one workgroup per output unit, lanes split K, so the
 // weight rows stream once at full bandwidth.  x [B][ldx], W rows of length ldw
 // with the compact-to-full column map (seg0, len0, seg1) for the input layer.
@@ -405,6 +692,232 @@ Scratch scratch_layout(const synim_mlp& net, int B, float* base) {
   return S;
 }
 
+// y [B][N] = h W^T + bias for the few outputs of the last layer: one wave per row.
+constexpr int OUT_MAX = 8;
+__global__ __launch_bounds__(256) void out_layer_kernel(const float* __restrict__ h, int B, int K,
+                                                        const float* __restrict__ W, int N,
+                                                        const float* __restrict__ bias,
+                                                        float* __restrict__ y) {
+  const int b = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  if (b >= B) return;
+  float acc[OUT_MAX];
+#pragma unroll
+  for (int j = 0; j < OUT_MAX; ++j) acc[j] = 0.f;
+  for (int k = 4 * lane; k < K; k += 256) {   // K % 4 == 0
+    const float4 v = *reinterpret_cast<const float4*>(h + (size_t)b * K + k);
+#pragma unroll
+    for (int j = 0; j < OUT_MAX; ++j)
+      if (j < N) {
+        const float4 w = *reinterpret_cast<const float4*>(W + (size_t)j * K + k);
+        acc[j] = __fmaf_rn(v.x, w.x, acc[j]);
+        acc[j] = __fmaf_rn(v.y, w.y, acc[j]);
+        acc[j] = __fmaf_rn(v.z, w.z, acc[j]);
+        acc[j] = __fmaf_rn(v.w, w.w, acc[j]);
+      }
+  }
+#pragma unroll
+  for (int j = 0; j < OUT_MAX; ++j) {
+    if (j >= N) break;
+    float v = acc[j];
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    if (lane == 0) y[(size_t)b * N + j] = v + bias[j];
+  }
+}
+
+// Everything of the last layer's backward pass and the loss in one launch (its
+// products are too small for a launch each): dY = 2 (Y - T) / (B n_out),
+//   workgroups [0, n_w):  dW3 [N][K] = dY^T h for OUT_COLS columns of h each, the
+//                         rows split over OUT_PARTS thread groups added in order;
+//   workgroup n_w:        db3 = sum dY and the loss;
+//   the others:           dh [B][K] = dY W3 where h > 0, a row each.
+constexpr int OUT_COLS = 16, OUT_PARTS = 256 / OUT_COLS, OUT_CHUNK = 512;
+__global__ __launch_bounds__(256) void out_backward_kernel(
+    const float* __restrict__ y, const float* __restrict__ t, const float* __restrict__ h, int B,
+    int K, const float* __restrict__ W, int N, float scale, int n_w, float* __restrict__ dW,
+    float* __restrict__ db, float* __restrict__ dh, float* __restrict__ loss) {
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x < n_w) {
+    __shared__ float dy[OUT_CHUNK * OUT_MAX];
+    __shared__ float red[OUT_PARTS][OUT_COLS][OUT_MAX];
+    const int c = tid % OUT_COLS, part = tid / OUT_COLS;
+    const int k = min((int)blockIdx.x * OUT_COLS + c, K - 1);
+    float acc[OUT_MAX];
+#pragma unroll
+    for (int j = 0; j < OUT_MAX; ++j) acc[j] = 0.f;
+    for (int b0 = 0; b0 < B; b0 += OUT_CHUNK) {
+      const int nb = min(OUT_CHUNK, B - b0);
+      __syncthreads();
+      for (int e = tid; e < nb * N; e += 256)
+        dy[e] = 2.f * (y[(size_t)b0 * N + e] - t[(size_t)b0 * N + e]) * scale;
+      __syncthreads();
+      // eight rows' loads in flight per thread
+      for (int r0 = part; r0 < nb; r0 += 8 * OUT_PARTS) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          v[u] = r0 + OUT_PARTS * u < nb ? h[(size_t)(b0 + r0 + OUT_PARTS * u) * K + k] : 0.f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (r0 + OUT_PARTS * u >= nb) break;
+#pragma unroll
+          for (int j = 0; j < OUT_MAX; ++j)
+            if (j < N) acc[j] = __fmaf_rn(dy[(r0 + OUT_PARTS * u) * N + j], v[u], acc[j]);
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < OUT_MAX; ++j) red[part][c][j] = acc[j];
+    __syncthreads();
+    if (part < N && (int)blockIdx.x * OUT_COLS + c < K) {
+      float v = 0.f;
+      for (int q = 0; q < OUT_PARTS; ++q) v += red[q][c][part];
+      dW[(size_t)part * K + k] = v;
+    }
+    return;
+  }
+  if ((int)blockIdx.x == n_w) {
+    // thread (row group, output): rows in order, groups in a fixed tree
+    __shared__ float rd[256], rq[256];
+    const int ng = 256 / N, j = tid % N, q = tid / N;
+    float sd = 0.f, sq = 0.f;
+    if (q < ng)
+      for (int b = q; b < B; b += ng) {
+        const float d = y[(size_t)b * N + j] - t[(size_t)b * N + j];
+        sd += 2.f * d * scale;
+        sq += d * d;
+      }
+    rd[tid] = sd;
+    rq[tid] = sq;
+    __syncthreads();
+    for (int half = 1; half < ng; half *= 2) {
+      if (q < ng && q % (2 * half) == 0 && q + half < ng) {
+        rd[tid] += rd[tid + half * N];
+        rq[tid] += rq[tid + half * N];
+      }
+      __syncthreads();
+    }
+    if (tid < N) db[tid] = rd[tid];
+    if (tid == 0 && loss) {
+      float v = 0.f;
+      for (int o = 0; o < N; ++o) v += rq[o];
+      *loss = v * scale;
+    }
+    return;
+  }
+  const size_t b = blockIdx.x - n_w - 1;
+  float d[OUT_MAX];
+#pragma unroll
+  for (int j = 0; j < OUT_MAX; ++j)
+    d[j] = j < N ? 2.f * (y[b * N + j] - t[b * N + j]) * scale : 0.f;
+  for (int k = tid; k < K; k += 256) {
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < OUT_MAX; ++j)
+      if (j < N) v = __fmaf_rn(d[j], W[(size_t)j * K + k], v);
+    dh[b * K + k] = h[b * K + k] > 0.f ? v : 0.f;
+  }
+}
+
+// The direct products need 16-byte loads of every operand: layer widths and
+// segments in whole float4, aligned arrays, few outputs.  (Other shapes take
+// the staged products, with the input layer's columns gathered.)
+bool direct_ok(const synim_mlp& net, const float* params, const float* x, const Scratch& S) {
+  auto al = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+  return net.n_out <= OUT_MAX && net.h1 % 4 == 0 && net.h2 % 4 == 0 && net.n_in % 4 == 0 &&
+         net.len0 % 4 == 0 && net.len1 % 4 == 0 && net.seg0 % 4 == 0 && net.seg1 % 4 == 0 &&
+         net.seg1 >= net.seg0 + net.len0 && net.h1 >= 4 && net.h2 >= 4 && al(params) && al(x) &&
+         al(S.h1) && al(S.h2) && al(S.dh1) && al(S.dh2);
+}
+
+template <int BM, int BN, bool AK, bool BK>
+int direct_launch(const DGemm& g, hipStream_t st) {
+  const int tiles = direct_tiles(g.M, g.N, BM, BN);
+  const int zero = g.zero_cols > 0 ? ((g.M + ZERO_ROWS - 1) / ZERO_ROWS + 7) / 8 * 8 : 0;
+  const int W = direct_waves(tiles, g.K, BM * BN >= 4 ? 4 : 8);   // at most 64 KB of LDS
+  hipLaunchKernelGGL((direct_kernel<BM, BN, AK, BK, BM, BN, AK, BK>), dim3(tiles + zero),
+                     dim3(64 * W), direct_lds(W, BM, BN, AK, BK), st, zero, g, tiles, g, 0);
+  SYNIM_HIP_TRY(hipGetLastError());
+  return SYNIM_OK;
+}
+
+// 32 x 32 tiles once they alone give every CU one, else 16 x 32.  (64 x 64 tiles
+// halve the loads, but dW1 of the estimator, 264 of them, took 19 us against 16:
+// with one workgroup per CU nothing hides their latency.)
+template <bool AK, bool BK>
+int direct_product(const DGemm& g, hipStream_t st) {
+  if (direct_tiles(g.M, g.N, 2, 2) >= 256) return direct_launch<2, 2, AK, BK>(g, st);
+  return direct_launch<1, 2, AK, BK>(g, st);
+}
+
+DGemm dgemm(int M, int N, int K, const float* X, long ldx, const float* Y, long ldy, float* C,
+            long ldc) {
+  DGemm g{};
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.X = X;
+  g.ldx = ldx;
+  g.Y = Y;
+  g.ldy = ldy;
+  g.C = C;
+  g.ldc = ldc;
+  g.len0 = INT_MAX;
+  return g;
+}
+
+int forward_direct(const synim_mlp& net, const Layout& L, const float* P, const float* x, int B,
+                   const Scratch& S, float* y, hipStream_t st) {
+  const int K = net.len0 + net.len1;
+  // input layer on W1's own columns: compact k feeds column seg0 + k, from
+  // len0 on column seg1 + k - len0
+  DGemm g = dgemm(B, net.h1, K, x, K, P + L.w1 + net.seg0, net.n_in, S.h1, net.h1);
+  g.len0 = net.len0;
+  g.shift = net.seg1 - net.seg0 - net.len0;
+  g.bias = P + L.b1;
+  g.relu = 1;
+  int rc = direct_product<true, true>(g, st);
+  if (rc != SYNIM_OK) return rc;
+  DGemm h = dgemm(B, net.h2, net.h1, S.h1, net.h1, P + L.w2, net.h1, S.h2, net.h2);
+  h.bias = P + L.b2;
+  h.relu = 1;
+  if ((rc = direct_product<true, true>(h, st)) != SYNIM_OK) return rc;
+  hipLaunchKernelGGL(out_layer_kernel, dim3((B + 3) / 4), dim3(256), 0, st, S.h2, B, net.h2,
+                     P + L.w3, net.n_out, P + L.b3, y);
+  SYNIM_HIP_TRY(hipGetLastError());
+  return SYNIM_OK;
+}
+
+int backward_direct(const synim_mlp& net, const Layout& L, const float* P, const float* x, int B,
+                    const Scratch& S, const float* y, const float* t, float* G, float* loss,
+                    hipStream_t st) {
+  const int K = net.len0 + net.len1;
+  const int n_w = (net.h2 + OUT_COLS - 1) / OUT_COLS;
+  hipLaunchKernelGGL(out_backward_kernel, dim3(n_w + 1 + B), dim3(256), 0,
+                     st, y, t, S.h2, B, net.h2, P + L.w3, net.n_out, 1.f / (B * net.n_out), n_w,
+                     G + L.w3, G + L.b3, S.dh2, loss);
+  SYNIM_HIP_TRY(hipGetLastError());
+  // layer 2: dW2 = dh2^T h1 with db2, and dh1 = dh2 W2 where h1 > 0, in one launch
+  DGemm w2 = dgemm(net.h2, net.h1, B, S.dh2, net.h2, S.h1, net.h1, G + L.w2, net.h1);
+  w2.rowsum = G + L.b2;
+  DGemm d1 = dgemm(B, net.h1, net.h2, S.dh2, net.h2, P + L.w2, net.h1, S.dh1, net.h1);
+  d1.mask = S.h1;
+  const int tw = direct_tiles(w2.M, w2.N, 2, 2), td = direct_tiles(d1.M, d1.N, 2, 2);
+  const int W = direct_waves(tw + td, std::min(B, net.h2), 8);
+  hipLaunchKernelGGL((direct_kernel<2, 2, false, false, 2, 2, true, false>), dim3(tw + td),
+                     dim3(64 * W),
+                     std::max(direct_lds(W, 2, 2, false, false), direct_lds(W, 2, 2, true, false)),
+                     st, 0, w2, tw, d1, td);
+  SYNIM_HIP_TRY(hipGetLastError());
+  // layer 1: dW1 = dh1^T x into the used columns, zero elsewhere, db1
+  DGemm w1 = dgemm(net.h1, K, B, S.dh1, net.h1, x, K, G + L.w1 + net.seg0, net.n_in);
+  w1.rowsum = G + L.b1;
+  w1.len0 = net.len0;
+  w1.shift = net.seg1 - net.seg0 - net.len0;
+  w1.zero_cols = net.n_in;
+  w1.col0 = net.seg0;
+  return direct_product<false, false>(w1, st);
+}
+
 __global__ void fill_zero_kernel(float* __restrict__ p, long n) {
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0.f;
@@ -454,6 +967,7 @@ extern "C" int synim_mlp_forward(const synim_mlp* net, const float* params, cons
     SYNIM_HIP_TRY(hipGetLastError());
     return SYNIM_OK;
   }
+  if (direct_ok(*net, params, x, S)) return forward_direct(*net, L, P, x, B, S, y, st);
   // input layer: gather the used W1 columns once, then a dense GEMM
   float* w1c = S.w1c;
   const long nk = (long)net->h1 * K;
@@ -491,6 +1005,8 @@ extern "C" int synim_mlp_backward(const synim_mlp* net, const float* params, con
   float* dw1c = S.w1c;   // [h1][K] before scattering into W1's columns
   const float* P = params;
   float* G = grads;
+  if (B > 16 && direct_ok(*net, params, x, S) && (reinterpret_cast<uintptr_t>(grads) & 15) == 0)
+    return backward_direct(*net, L, P, x, B, S, y, t, G, loss, st);
   const int ny = B * net->n_out;
   hipLaunchKernelGGL(mse_grad_kernel, dim3(1), dim3(256), 0, st, y, t, ny, 1.f / ny, dy, loss);
   SYNIM_HIP_TRY(hipGetLastError());
