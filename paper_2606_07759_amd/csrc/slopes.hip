@@ -1,111 +1,199 @@
 // Standalone slope step (paper Sec. 2.2): central differences at every pupil
 // pixel of a haloed phase map, averaged over each valid subaperture.
+#include <algorithm>
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace synim {
 namespace {
 
-constexpr int SBLOCK = 256;   // pixel columns of one workgroup
-constexpr int SROWS = 8;      // subaperture rows one workgroup walks in turn
+constexpr int SBLOCK = 256;          // most threads of a workgroup, two pixel columns each
+constexpr int SROWS = 8;             // subaperture rows one workgroup walks in turn
 
-// Pixel (x, y)'s pupil-masked central differences and pupil count, added to
-// its column's sums.  The loads are unconditional (the halo keeps them in
-// bounds) so that many rows' loads can be in flight together.
-__device__ __forceinline__ void column_terms(const float* ph, const uint8_t* pupil, int W,
-                                             int Wh, int x, int y, float& gx, float& gy,
-                                             float& cnt) {
-  const bool in = pupil[(size_t)y * W + x] != 0;
-  const size_t c = (size_t)(y + 1) * Wh + (x + 1);
-  const float ex = 0.5f * (ph[c + 1] - ph[c - 1]);
-  const float ey = 0.5f * (ph[c + Wh] - ph[c - Wh]);
-  gx += in ? ex : 0.f;
-  gy += in ? ey : 0.f;
-  cnt += in ? 1.f : 0.f;
-}
+// Four neighbouring samples (any float alignment: one 16-byte load).
+struct __attribute__((packed, aligned(4))) Quad {
+  float v[4];
+};
 
-// One workgroup per (phase map, group of SROWS subaperture rows, run of whole
-// subapertures across SBLOCK pixel columns).  Thread t owns pixel column
-// x = x0 + t: for each subaperture row of the group it reads, row by row, the
-// four neighbours its central differences need (consecutive threads read
-// consecutive columns, so every load is coalesced) and sums the pupil-masked
-// differences and the pupil count down the subaperture row.  The
-// per-subaperture sums then add those column sums in column order (a fixed
-// order, so results are bit-reproducible).  Walking the group's rows in turn
-// reads the pixel rows two subaperture rows share while they are still in
-// cache.
-__global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict__ phase,
+// One workgroup per (group of SROWS subaperture rows, run of whole subapertures
+// across the block's pixel columns, run of phase maps).  Thread t owns pixel columns
+// x = x0 + 2t and x + 1 and walks down the group's pixel rows with three of them in
+// registers: one 16-byte load per row holds both columns' samples and their left
+// and right neighbours, and the rows above and below are the ones before and
+// after it (four separate loads and a pupil byte per pixel had taken 0.40 ms for
+// 1200 maps of 482 x 482; the loads' issue, not the 2.8 TB/s, bounded them).  The
+// pupil-masked differences and the pupil count are summed down each subaperture
+// row; the per-subaperture sums then add those column sums in column order (a
+// fixed order, so results are bit-reproducible).  The pupil of a thread's columns
+// is kept as bits over the run of maps where the group has at most 64 pixel rows.
+// A wave finds where a row's subapertures start in the valid list with 64-way
+// steps (three for 4632 entries).  Each XCD takes all blocks of a map before its
+// next, so that shared rows and lines meet in its L2.  Now 0.33.
+__global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict__ phase, int n,
                                                         const int32_t* __restrict__ valid,
                                                         const uint8_t* __restrict__ pupil,
                                                         int n_sub_x, int n_sub_y, int p, int nv,
-                                                        int subs_per_block,
-                                                        float* __restrict__ slopes) {
-  __shared__ float s_gx[2][SBLOCK], s_gy[2][SBLOCK], s_n[2][SBLOCK];
-  __shared__ int s_kk[SROWS * SBLOCK];
-  const int t = threadIdx.x;
+                                                        int subs_per_block, int maps_per_block,
+                                                        int by_xcd, float* __restrict__ slopes) {
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, T = blockDim.x;
+  // column sums [gx, gy, pupil count][subaperture row][2 T], then the valid-list
+  // index of the group's subapertures
+  extern __shared__ __align__(16) float s_sum[];
+  int* const s_kk = reinterpret_cast<int*>(s_sum + 12 * T);
+  auto sum_at = [&](int what, int r, int c) -> float& { return s_sum[(2 * what + r) * 2 * T + c]; };
   const int n_runs = (n_sub_x + subs_per_block - 1) / subs_per_block;
-  const int grp = blockIdx.x / n_runs;
-  const int u0 = (blockIdx.x - grp * n_runs) * subs_per_block;
-  const int i = blockIdx.y;
+  const int n_blk = (n_sub_y + SROWS - 1) / SROWS * n_runs;
+  const int sb = by_xcd ? blockIdx.x >> 3 : blockIdx.x;
+  const int blk = sb % n_blk;
+  const int i0 = (by_xcd ? sb / n_blk * 8 + (blockIdx.x & 7) : sb / n_blk) * maps_per_block;
+  if (i0 >= n) return;
+  const int grp = blk / n_runs;
+  const int u0 = (blk - grp * n_runs) * subs_per_block;
   const int W = n_sub_x * p, H = n_sub_y * p;
   const int Wh = W + 2;
   const int nu = min(subs_per_block, n_sub_x - u0);
-  const int x = u0 * p + t;
-  const float* ph = phase + (size_t)i * (size_t)(H + 2) * (size_t)Wh;
-  float* out = slopes + (size_t)i * 2 * nv;
+  const int x = u0 * p + 2 * t;
   const int v0 = grp * SROWS, v_end = min(n_sub_y, v0 + SROWS);
-  // valid-list index of every subaperture of the group (-1: not valid), all
-  // looked up at once so that the binary searches' load chains overlap
-  for (int e = t; e < (v_end - v0) * nu; e += SBLOCK) {
-    const int k = (v0 + e / nu) * n_sub_x + u0 + e % nu;
-    int lo = 0, hi = nv - 1, kk = -1;
-    while (lo <= hi) {
-      const int mid = (lo + hi) >> 1;
-      const int vm = valid[mid];
-      if (vm == k) {
-        kk = mid;
-        break;
-      }
-      if (vm < k) lo = mid + 1; else hi = mid - 1;
+  // valid-list index of every subaperture of the group (-1: not valid)
+  for (int e = t; e < (v_end - v0) * nu; e += T) s_kk[e] = -1;
+  __syncthreads();
+  for (int v = v0 + wave; v < v_end; v += T >> 6) {
+    const int k0 = v * n_sub_x + u0;
+    // first entry >= k0 in [lo, hi): every lane tests one of 64 spread entries
+    int lo = 0, hi = nv;
+    while (lo < hi) {
+      const int step = (hi - lo + 63) / 64;
+      const int at = lo + lane * step;
+      const unsigned long long below = __ballot(at < hi && valid[min(at, nv - 1)] < k0);
+      const int c = __popcll(below);   // entries are ascending: the first c lanes
+      if (c == 0) break;
+      lo = lo + (c - 1) * step + 1;
+      hi = min(hi, lo - 1 + step);
     }
-    s_kk[e] = kk;
+    for (int j = lo + lane; j < min(nv, lo + nu); j += 64) {
+      const int u = valid[j] - k0;
+      if (u < nu) s_kk[(v - v0) * nu + u] = j;
+    }
   }
-  // two subaperture rows per step: twice the loads in flight between barriers
-  for (int v = v0; v < v_end; v += 2) {
-    const int nr = min(2, v_end - v);
-    float gx[2] = {0.f, 0.f}, gy[2] = {0.f, 0.f}, cnt[2] = {0.f, 0.f};
-    if (t < nu * p) {
-      if (nr == 2) {
-#pragma unroll 2
-        for (int dy = 0; dy < p; ++dy)
+  // this thread's columns: on (the first lies in the block), two (the second too)
+  const bool on = 2 * t < nu * p, two = 2 * t + 1 < nu * p;
+  const int y_beg = v0 * p, y_end = v_end * p;
+  const bool keep = y_end - y_beg <= 64;
+  unsigned long long in0 = 0, in1 = 0;   // pupil bits of rows y_beg.. of the two columns
+  if (keep && on) {
+    const int second = two ? 1 : 0;
+    for (int y = y_beg; y < y_end; y += 8) {
+      uint8_t q[8][2];
 #pragma unroll
-          for (int r = 0; r < 2; ++r) column_terms(ph, pupil, W, Wh, x, (v + r) * p + dy,
-                                                   gx[r], gy[r], cnt[r]);
+      for (int k = 0; k < 8; ++k) {
+        const uint8_t* at = pupil + (size_t)min(y + k, y_end - 1) * W + x;
+        q[k][0] = at[0];
+        q[k][1] = at[second];
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (y + k < y_end) {
+          in0 |= (unsigned long long)(q[k][0] != 0) << (y + k - y_beg);
+          in1 |= (unsigned long long)(two && q[k][1] != 0) << (y + k - y_beg);
+        }
+    }
+  }
+  for (int i = i0; i < min(n, i0 + maps_per_block); ++i) {
+    const float* ph = phase + (size_t)i * (size_t)(H + 2) * (size_t)Wh;
+    float* out = slopes + (size_t)i * 2 * nv;
+    // samples x - 1 .. x + 2 of pixel row y (haloed row y + 1); the last only for
+    // a second column
+    auto row = [&](int y) {
+      const float* q = ph + (size_t)(y + 1) * Wh + x;
+      Quad r;
+      if (two) {
+        r = *reinterpret_cast<const Quad*>(q);
       } else {
-#pragma unroll 4
-        for (int dy = 0; dy < p; ++dy)
-          column_terms(ph, pupil, W, Wh, x, v * p + dy, gx[0], gy[0], cnt[0]);
+        r.v[0] = q[0];
+        r.v[1] = q[1];
+        r.v[2] = q[2];
+        r.v[3] = 0.f;
       }
+      return r;
+    };
+    Quad prev{}, cur{};
+    if (on) {
+      prev = row(y_beg - 1);
+      cur = row(y_beg);
     }
-    __syncthreads();   // the previous step's sums have been read (and s_kk written)
+    // two subaperture rows per step between barriers
+    for (int v = v0; v < v_end; v += 2) {
+      const int nr = min(2, v_end - v);
+      float gx[2][2] = {}, gy[2][2] = {}, cnt[2][2] = {};   // [subaperture row][column]
+      // U rows' loads in flight (a divisor of p where there is one, so that no
+      // row is loaded twice)
+      auto walk = [&](auto uc) {
+        constexpr int U = decltype(uc)::value;
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      s_gx[r][t] = gx[r];
-      s_gy[r][t] = gy[r];
-      s_n[r][t] = cnt[r];
-    }
-    __syncthreads();
-    for (int e = t; e < nr * nu; e += SBLOCK) {
-      const int r = e / nu, u = e - r * nu;
-      const int kk = s_kk[(v - v0 + r) * nu + u];
-      if (kk < 0) continue;
-      float sx = 0.f, sy = 0.f, n = 0.f;
-      for (int c = u * p; c < u * p + p; ++c) {
-        sx += s_gx[r][c];
-        sy += s_gy[r][c];
-        n += s_n[r][c];
+        for (int r = 0; r < 2; ++r) {
+          if (r >= nr) break;
+          const int ya = (v + r) * p;
+          for (int d0 = 0; d0 < p; d0 += U) {
+            Quad nx[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) nx[u] = row(min(ya + d0 + u + 1, y_end));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              if (d0 + u >= p) break;
+              const int y = ya + d0 + u;
+              bool a, b;
+              if (keep) {
+                a = (in0 >> (y - y_beg)) & 1;
+                b = (in1 >> (y - y_beg)) & 1;
+              } else {
+                const uint8_t* q = pupil + (size_t)y * W + x;
+                a = q[0] != 0;
+                b = two && q[1] != 0;
+              }
+              const float ex0 = 0.5f * (cur.v[2] - cur.v[0]), ex1 = 0.5f * (cur.v[3] - cur.v[1]);
+              const float ey0 = 0.5f * (nx[u].v[1] - prev.v[1]);
+              const float ey1 = 0.5f * (nx[u].v[2] - prev.v[2]);
+              gx[r][0] += a ? ex0 : 0.f;
+              gy[r][0] += a ? ey0 : 0.f;
+              cnt[r][0] += a ? 1.f : 0.f;
+              gx[r][1] += b ? ex1 : 0.f;
+              gy[r][1] += b ? ey1 : 0.f;
+              cnt[r][1] += b ? 1.f : 0.f;
+              prev = cur;
+              cur = nx[u];
+            }
+          }
+        }
+      };
+      if (on) {
+        if (p % 6 == 0) walk(std::integral_constant<int, 6>{});
+        else if (p % 7 == 0) walk(std::integral_constant<int, 7>{});
+        else if (p % 5 == 0) walk(std::integral_constant<int, 5>{});
+        else if (p % 3 == 0) walk(std::integral_constant<int, 3>{});
+        else walk(std::integral_constant<int, 4>{});
       }
-      out[kk] = n > 0.f ? sx / n : 0.f;
-      out[nv + kk] = n > 0.f ? sy / n : 0.f;
+      __syncthreads();   // the previous step's sums have been read (and s_kk written)
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        *reinterpret_cast<float2*>(&sum_at(0, r, 2 * t)) = make_float2(gx[r][0], gx[r][1]);
+        *reinterpret_cast<float2*>(&sum_at(1, r, 2 * t)) = make_float2(gy[r][0], gy[r][1]);
+        *reinterpret_cast<float2*>(&sum_at(2, r, 2 * t)) = make_float2(cnt[r][0], cnt[r][1]);
+      }
+      __syncthreads();
+      for (int e = t; e < nr * nu; e += T) {
+        const int r = e / nu, u = e - r * nu;
+        const int kk = s_kk[(v - v0 + r) * nu + u];
+        if (kk < 0) continue;
+        float sx = 0.f, sy = 0.f, cn = 0.f;
+        for (int c = u * p; c < u * p + p; ++c) {
+          sx += sum_at(0, r, c);
+          sy += sum_at(1, r, c);
+          cn += sum_at(2, r, c);
+        }
+        out[kk] = cn > 0.f ? sx / cn : 0.f;
+        out[nv + kk] = cn > 0.f ? sy / cn : 0.f;
+      }
     }
   }
 }
@@ -120,12 +208,27 @@ extern "C" int synim_sa_slopes(const float* phase, int n, const synim_wfs* wfs, 
   if (st != SYNIM_OK) return st;
   if (n < 1 || n > 65535) return SYNIM_E_SHAPE;
   if (wfs->p > SBLOCK) return SYNIM_E_SHAPE;
-  const int spb = SBLOCK / wfs->p;
+  // as many threads as half the grid's columns need, up to four waves (any of 64,
+  // 128, 256 threads within 3% of each other on 480 columns)
+  const int T = std::min(SBLOCK, ((wfs->n_sub_x * wfs->p + 1) / 2 + 63) / 64 * 64);
+  const int spb = std::min(wfs->n_sub_x, 2 * T / wfs->p);
   const long bx = (long)((wfs->n_sub_y + SROWS - 1) / SROWS) * ((wfs->n_sub_x + spb - 1) / spb);
-  if (bx > 0x7fffffffL) return SYNIM_E_SHAPE;
-  hipLaunchKernelGGL(slopes_kernel, dim3((unsigned)bx, n), dim3(SBLOCK), 0, (hipStream_t)stream,
-                     phase, wfs->valid_idx, wfs->pupil, wfs->n_sub_x, wfs->n_sub_y, wfs->p,
-                     wfs->n_valid, spb, slopes);
+  // 48 waves per CU, each a run of maps (1200 ELT maps: runs of 2 to 8 maps 347 to
+  // 327 us, of 16 363, where the last round of workgroups is short); eight runs or
+  // more in whole eights, an equal number for each XCD, fewer spread over all
+  long mpb = std::min<long>(n, std::max(1L, n * bx * (T / 64) / 12288));
+  long runs = (n + mpb - 1) / mpb;
+  const bool by_xcd = runs >= 8;
+  if (by_xcd) {
+    runs = (runs + 7) / 8 * 8;
+    mpb = (n + runs - 1) / runs;
+  }
+  if (runs * bx > 0x7fffffffL) return SYNIM_E_SHAPE;
+  hipLaunchKernelGGL(slopes_kernel, dim3((unsigned)(runs * bx)),
+                     dim3(T),
+                     (12 * T + SROWS * spb) * sizeof(float),
+                     (hipStream_t)stream, phase, n, wfs->valid_idx, wfs->pupil, wfs->n_sub_x,
+                     wfs->n_sub_y, wfs->p, wfs->n_valid, spb, (int)mpb, by_xcd ? 1 : 0, slopes);
   SYNIM_HIP_TRY(hipGetLastError());
   return SYNIM_OK;
 }

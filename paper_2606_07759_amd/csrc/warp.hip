@@ -1,5 +1,6 @@
 // Standalone single-step bilinear resampling of an IF stack onto the WFS grid
 // (paper Sec. 2.1: the composite map is applied once, with one interpolation).
+#include <algorithm>
 #include <cmath>
 
 #include "common.hpp"
@@ -7,20 +8,41 @@
 namespace synim {
 namespace {
 
-constexpr int WX = 256, WY = 4;   // four waves cover 256 consecutive output columns
-// Workgroups per launch the IF loop is split for: enough to fill 256 CUs many
-// times over, while each workgroup still reuses its FP64 source coordinates
-// over tens of IFs (16k, 32k and 128k measured within 8% of each other).
-constexpr long kTargetBlocks = 131072;
+constexpr int WX = 128, WY = 2;   // a workgroup's output pixels
+constexpr int UNR = 8;            // IFs of a workgroup at most, in one pass
+// What bounds the step is memory: each source pixel under the window once, the
+// window written.  A workgroup covers 128 x 2 output pixels of a run of IFs, its
+// FP64 source coordinates formed once and the taps of up to 8 IFs in flight.  1200
+// ELT IFs of 512^2 onto 482^2: runs of 4 IFs 0.95 ms, of 8 0.60, of 16 0.64, of 64
+// 0.70 (256 x 4 pixels: 0.65 with 8; runs of two, four separate taps waited for in
+// turn: 1.15).  Fewer IFs a run where there would be fewer than kMinBlocks
+// workgroups.
+// Consecutive workgroups go to the 8 XCDs in turn; each XCD takes every window
+// block of one run of IFs before the next run, so that the source rows
+// neighbouring blocks share, and the output lines they share, meet in its L2
+// (eight runs or more, in whole eights; fewer are spread over all XCDs).
+constexpr long kMinBlocks = 4096;
+
+// Two neighbouring taps (any float alignment: one 8-byte load).
+struct __attribute__((packed, aligned(4))) Pair {
+  float x, y;
+};
 
 __global__ __launch_bounds__(WX* WY) void warp_kernel(const float* __restrict__ ifs, int n,
                                                       int H_in, int W_in, MapD m, int H_out,
                                                       int W_out, int halo, int if_per_block,
+                                                      int by_xcd,
                                                       float* __restrict__ out,
                                                       int32_t* __restrict__ oob) {
   const int Wh = W_out + 2 * halo, Hh = H_out + 2 * halo;
-  const int ox = blockIdx.x * WX + (threadIdx.x % WX);
-  const int oy = blockIdx.y * WY + (threadIdx.x / WX);
+  const int bx = (Wh + WX - 1) / WX, by = (Hh + WY - 1) / WY, nxy = bx * by;
+  const int s = by_xcd ? blockIdx.x >> 3 : blockIdx.x;
+  const int run = by_xcd ? s / nxy * 8 + (blockIdx.x & 7) : s / nxy, xy = s % nxy;
+  const int i_begin = run * if_per_block;
+  if (i_begin >= n) return;
+  const int i_end = min(n, i_begin + if_per_block);
+  const int ox = xy % bx * WX + (threadIdx.x % WX);
+  const int oy = xy / bx * WY + (threadIdx.x / WX);
   const bool active = ox < Wh && oy < Hh;
 
   double xs, ys;
@@ -43,7 +65,7 @@ __global__ __launch_bounds__(WX* WY) void warp_kernel(const float* __restrict__ 
   const size_t r0 = (size_t)j0 * W_in + i0;
   const size_t r1 = r0 + W_in;
 
-  if (oob != nullptr && blockIdx.z == 0) {
+  if (oob != nullptr && run == 0) {
     const bool o = active && (xs < 0.0 || xs > W_in - 1.0 || ys < 0.0 || ys > H_in - 1.0);
     const int cnt = __syncthreads_count(o);
     if (threadIdx.x == 0 && cnt > 0) atomicAdd(oob, cnt);
@@ -52,18 +74,35 @@ __global__ __launch_bounds__(WX* WY) void warp_kernel(const float* __restrict__ 
 
   const size_t plane_in = (size_t)H_in * W_in;
   const size_t plane_out = (size_t)Hh * Wh;
-  const int i_begin = blockIdx.z * if_per_block;
-  const int i_end = min(n, i_begin + if_per_block);
   const size_t o0 = (size_t)oy * Wh + ox;
-  // UNR IFs per pass: all 4*UNR taps are loaded before the first one is used,
-  // so a thread keeps that many gathers in flight instead of one IF's four.
-  constexpr int UNR = 8;
-  int i = i_begin;
-  for (; i + UNR <= i_end; i += UNR) {
+  // UNR IFs per pass: all taps are loaded before the first one is used, so a
+  // thread keeps that many gathers in flight instead of one IF's.  (Past the
+  // run's end the last IF is read again and not stored.)
+  if (__all(t00 && t01 && t10 && t11)) {   // the wave's taps all lie on the grid
+    for (int i = i_begin; i < i_end; i += UNR) {
+      Pair a[UNR], b[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const float* F = ifs + (size_t)min(i + u, i_end - 1) * plane_in;
+        a[u] = *reinterpret_cast<const Pair*>(F + r0);
+        b[u] = *reinterpret_cast<const Pair*>(F + r1);
+      }
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        float acc = __fmaf_rn(w00, a[u].x, 0.0f);
+        acc = __fmaf_rn(w01, a[u].y, acc);
+        acc = __fmaf_rn(w10, b[u].x, acc);
+        acc = __fmaf_rn(w11, b[u].y, acc);
+        if (i + u < i_end) out[(size_t)(i + u) * plane_out + o0] = acc;
+      }
+    }
+    return;
+  }
+  for (int i = i_begin; i < i_end; i += UNR) {
     float v[UNR][4];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const float* F = ifs + (size_t)(i + u) * plane_in;
+      const float* F = ifs + (size_t)min(i + u, i_end - 1) * plane_in;
       v[u][0] = t00 ? F[r0] : 0.0f;
       v[u][1] = t01 ? F[r0 + 1] : 0.0f;
       v[u][2] = t10 ? F[r1] : 0.0f;
@@ -76,17 +115,8 @@ __global__ __launch_bounds__(WX* WY) void warp_kernel(const float* __restrict__ 
       if (t01) acc = __fmaf_rn(w01, v[u][1], acc);
       if (t10) acc = __fmaf_rn(w10, v[u][2], acc);
       if (t11) acc = __fmaf_rn(w11, v[u][3], acc);
-      out[(size_t)(i + u) * plane_out + o0] = acc;
+      if (i + u < i_end) out[(size_t)(i + u) * plane_out + o0] = acc;
     }
-  }
-  for (; i < i_end; ++i) {
-    const float* F = ifs + (size_t)i * plane_in;
-    float acc = 0.0f;
-    if (t00) acc = __fmaf_rn(w00, F[r0], acc);
-    if (t01) acc = __fmaf_rn(w01, F[r0 + 1], acc);
-    if (t10) acc = __fmaf_rn(w10, F[r1], acc);
-    if (t11) acc = __fmaf_rn(w11, F[r1 + 1], acc);
-    out[(size_t)i * plane_out + o0] = acc;
   }
 }
 
@@ -104,12 +134,18 @@ extern "C" int synim_affine_warp(const float* ifs, int n, int H_in, int W_in,
   const int Wh = W_out + 2 * halo, Hh = H_out + 2 * halo;
   const int bx = (Wh + WX - 1) / WX, by = (Hh + WY - 1) / WY;
   const long xy = (long)bx * by;
-  int ipb = (int)std::max(1L, (long)n * xy / kTargetBlocks);
-  ipb = std::min(ipb, n);
-  const int bz = (n + ipb - 1) / ipb;
-  if (bz > 65535) return SYNIM_E_SHAPE;
-  hipLaunchKernelGGL(warp_kernel, dim3(bx, by, bz), dim3(WX * WY), 0, (hipStream_t)stream, ifs,
-                     n, H_in, W_in, to_map(*A), H_out, W_out, halo, ipb, out, oob_count);
+  long ipb = std::min<long>(n, std::clamp((long)n * xy / kMinBlocks, 1L, (long)UNR));
+  long runs = (n + ipb - 1) / ipb;
+  const bool by_xcd = runs >= 8;
+  if (by_xcd) {
+    runs = (runs + 7) / 8 * 8;   // an equal number for each XCD
+    ipb = (n + runs - 1) / runs;
+  }
+  const long blocks = runs * xy;
+  if (blocks > 0x7fffffffL) return SYNIM_E_SHAPE;
+  hipLaunchKernelGGL(warp_kernel, dim3((unsigned)blocks), dim3(WX * WY), 0, (hipStream_t)stream, ifs,
+                     n, H_in, W_in, to_map(*A), H_out, W_out, halo, (int)ipb,
+                     by_xcd ? 1 : 0, out, oob_count);
   SYNIM_HIP_TRY(hipGetLastError());
   return SYNIM_OK;
 }
