@@ -8,6 +8,7 @@
 // function's samples are contiguous (the sampler writes them coalesced) and
 // the products are  G = Pt_dm Pt_dm^T  and  B = Pt_dm Pt_layer^T.
 #include <algorithm>
+#include <cfloat>
 #include <climits>
 #include <cmath>
 #include <vector>
@@ -20,10 +21,12 @@ namespace {
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 // ------------------------------------------------------------------ sampling
-// One thread per (row, basis function): the mean over the block's fine pupil
-// pixels of the bilinear sample of the basis function at
-// c + (r + h theta) / s (zero outside the component grid).  Grid: x over rows,
-// y over the component's functions.
+// Row (direction, block) of basis function a: the mean over the block's fine
+// pupil pixels of the bilinear sample of the function at c + (r + h theta) / s
+// (zero outside the component grid).
+constexpr int PT = 128;        // columns of a product's tile (and of an occupancy row)
+constexpr int PK = 16;         // matrix rows of a product's step (and of an occupancy bit)
+
 struct SampleArgs {
   const float* basis;          // [n][H][W]
   int n, H, W;
@@ -37,12 +40,18 @@ struct SampleArgs {
   double sp;                   // pupil pixel (m)
   double* Pt;                  // column base: Pt + col0 * ld
   long ld;
+  long col0;                   // this component's first column in its matrix
+  // per tile of PT columns, a bit for each PK matrix rows that hold a non-zero
+  // sample (null: not wanted), words 64-bit words a tile; *wild is set where a
+  // sample is not finite
+  unsigned long long* occ;
+  int words;
+  int* wild;
+  int group;                   // functions of a workgroup's loop
 };
 
-__global__ __launch_bounds__(256) void proj_sample_kernel(SampleArgs g) {
-  const long row = (long)blockIdx.x * 256 + threadIdx.x;
-  const int a = blockIdx.y;
-  if (row >= (long)g.n_dir * g.n_blocks) return;
+// The sample by its definition, pixel by pixel.
+__device__ double proj_sample(const SampleArgs& g, long row, int a) {
   const int d = (int)(row / g.n_blocks), blk = (int)(row - (long)d * g.n_blocks);
   const int2 bb = g.blocks[blk];
   const double2 th = g.dirs[d];
@@ -68,7 +77,136 @@ __global__ __launch_bounds__(256) void proj_sample_kernel(SampleArgs g) {
              (1.0 - u) * v * tap(i, j + 1) + u * v * tap(i + 1, j + 1);
       ++cnt;
     }
-  g.Pt[(size_t)a * g.ld + row] = cnt > 0 ? acc / cnt : 0.0;
+  return cnt > 0 ? acc / cnt : 0.0;
+}
+
+// One thread per (row, basis function), for blocks whose taps span more than the
+// largest window below.
+__global__ __launch_bounds__(256) void proj_sample_kernel(SampleArgs g) {
+  const long row = (long)blockIdx.x * 256 + threadIdx.x;
+  const int a = blockIdx.y;
+  if (row >= (long)g.n_dir * g.n_blocks) return;
+  const double out = proj_sample(g, row, a);
+  g.Pt[(size_t)a * g.ld + row] = out;
+  if (g.occ == nullptr) return;
+  if (out != 0.0)
+    atomicOr(g.occ + (g.col0 + a) / PT * g.words + row / (64 * PK), 1ull << (row / PK % 64));
+  if (!(fabs(out) <= DBL_MAX)) *g.wild = 1;
+}
+
+// A row's sample is linear in the function, with weights that depend on the row
+// alone: a thread forms its row's weights over the NT x NT grid points its taps
+// span once, keeps them in registers and takes one small dot product per
+// function of its group.  Read pixel by pixel a binned row took 64 taps of one
+// float and, per pixel, two FP64 divisions, for every function again: 72 ms for
+// 12278 functions of 512^2 on 94104 rows (4 x 4 pixels each), now 19; reading
+// the functions once and writing the matrix takes 5.  Consecutive lanes are
+// neighbouring blocks, whose window rows lie next to each other in memory.  The
+// rows' workgroups of one group of functions run on one XCD, whose L2 then holds
+// the functions for all directions.  Grid points of the window that are no
+// tap carry weight zero; where a sample comes out not finite it is formed again
+// by its definition, so that such a point's value never enters one.
+template <int NT>
+struct __attribute__((packed, aligned(4))) Window {   // NT neighbouring points
+  float v[NT];
+};
+template <int NT>
+__global__ __launch_bounds__(256) void proj_window_kernel(SampleArgs g, int n_rb, int by_xcd) {
+  const int sb = by_xcd ? blockIdx.x >> 3 : blockIdx.x;
+  const long grp = by_xcd ? (long)(sb / n_rb) * 8 + (blockIdx.x & 7) : sb / n_rb;
+  const long row = (long)(sb % n_rb) * 256 + threadIdx.x;
+  // the functions of this group: a whole number of groups per tile of columns
+  const long c0 = g.col0 / g.group * g.group + grp * g.group;
+  const int a_begin = (int)max(0L, c0 - g.col0);
+  const int a_end = (int)min((long)g.n, c0 + g.group - g.col0);
+  if (a_begin >= a_end) return;   // the whole workgroup
+  const bool on = row < (long)g.n_dir * g.n_blocks;
+  double w[NT][NT];
+#pragma unroll
+  for (int j = 0; j < NT; ++j)
+#pragma unroll
+    for (int i = 0; i < NT; ++i) w[j][i] = 0.0;
+  int i0 = 0, j0 = 0;
+  double mean = 0.0;
+  if (on) {
+    const int d = (int)(row / g.n_blocks), blk = (int)(row - (long)d * g.n_blocks);
+    const int2 bb = g.blocks[blk];
+    const double2 th = g.dirs[d];
+    const double cy = (g.H - 1) * 0.5, cx = (g.W - 1) * 0.5;
+    const double cpy = (g.Hp - 1) * 0.5, cpx = (g.Wp - 1) * 0.5;
+    auto at_x = [&](int fx) { return cx + ((bb.y * g.bin + fx - cpx) * g.sp + g.h * th.x) / g.s; };
+    auto at_y = [&](int fy) { return cy + ((bb.x * g.bin + fy - cpy) * g.sp + g.h * th.y) / g.s; };
+    // the window's corner, moved inside the grid; cells outside the grid are
+    // brought next to it, where they have no tap on it either
+    auto cell = [](double f, int n) { return (int)fmin(fmax(f, -2.0), (double)n); };
+    i0 = min(max(cell(floor(at_x(0)), g.W), 0), g.W - NT);
+    j0 = min(max(cell(floor(at_y(0)), g.H), 0), g.H - NT);
+    int cnt = 0;
+    for (int fy = 0; fy < g.bin; ++fy) {
+      double wx[NT];
+#pragma unroll
+      for (int i = 0; i < NT; ++i) wx[i] = 0.0;
+      for (int fx = 0; fx < g.bin; ++fx) {
+        if (!g.pupil[(size_t)(bb.x * g.bin + fy) * g.Wp + bb.y * g.bin + fx]) continue;
+        const double gx = at_x(fx), fi = floor(gx), u = gx - fi;
+        const int i = cell(fi, g.W) - i0;
+#pragma unroll
+        for (int k = 0; k < NT; ++k) wx[k] += k == i ? 1.0 - u : k == i + 1 ? u : 0.0;
+        ++cnt;
+      }
+      const double gy = at_y(fy), fj = floor(gy), v = gy - fj;
+      const int j = cell(fj, g.H) - j0;
+#pragma unroll
+      for (int k = 0; k < NT; ++k) {
+        const double wy = k == j ? 1.0 - v : k == j + 1 ? v : 0.0;
+#pragma unroll
+        for (int i = 0; i < NT; ++i) w[k][i] = __fma_rn(wy, wx[i], w[k][i]);
+      }
+    }
+    mean = cnt > 0 ? 1.0 / cnt : 0.0;
+  }
+  const size_t plane = (size_t)g.H * g.W;
+  const float* F = g.basis + (size_t)j0 * g.W + i0;
+  bool nz = false, wild = false;
+  for (int a = a_begin; a < a_end; ++a) {
+    Window<NT> f[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+      f[j] = *reinterpret_cast<const Window<NT>*>(F + a * plane + (size_t)j * g.W);
+    double acc = 0.0;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+      double s = w[j][0] * (double)f[j].v[0];
+#pragma unroll
+      for (int i = 1; i < NT; ++i) s = __fma_rn(w[j][i], (double)f[j].v[i], s);
+      acc += s;
+    }
+    acc *= mean;
+    if (on) g.Pt[(size_t)a * g.ld + row] = acc;
+    nz = nz || (on && acc != 0.0);
+    wild = wild || (on && !(fabs(acc) <= DBL_MAX));
+  }
+  if (wild) {   // by the definition: such a point need not be a tap
+    wild = false;
+    nz = true;
+    for (int a = a_begin; a < a_end; ++a) {
+      double* at = g.Pt + (size_t)a * g.ld + row;
+      if (fabs(*at) <= DBL_MAX) continue;
+      *at = proj_sample(g, row, a);
+      wild = wild || !(fabs(*at) <= DBL_MAX);
+    }
+  }
+  if (g.occ == nullptr) return;
+  const unsigned long long bits = __ballot(nz);
+  if (wild) *g.wild = 1;
+  if ((threadIdx.x & 63) != 0) return;
+  unsigned long long m = 0;
+#pragma unroll
+  for (int q = 0; q < 64 / PK; ++q)
+    if ((bits >> (q * PK)) & ((1ull << PK) - 1)) m |= 1ull << q;
+  if (m != 0)
+    atomicOr(g.occ + (g.col0 + a_begin) / PT * g.words + row / (64 * PK),
+             m << (row / PK % 64));
 }
 
 // ---------------------------------------------------------------- FP64 GEMM
@@ -213,6 +351,252 @@ int gemm(const GemmArgs& a, hipStream_t st) {
   }
   SYNIM_HIP_TRY(hipGetLastError());
   return SYNIM_OK;
+}
+
+// ------------------------------------------------- products of sampled columns
+// C = Pt_x Pt_y^T over the steps of PK rows in which both tiles of PT columns hold
+// a non-zero sample: an influence function reaches a small part of the pupil
+// (FP32 Gaussians 14 widths around the actuator, measured ones less), so that of
+// the steps of a system of three mirrors and three layers 8% (Gram) and 12%
+// (cross) are left.  A step of zeros adds exact zeros, so the sums are the same
+// bits; where a sample is not finite (0 x inf) every step is taken.
+// 128 x 128 tiles, 4 x 4 matrix-core blocks per wave, two workgroups a CU so that
+// one's steps cover the other's loads and barriers.  Tiles differ in their number
+// of steps: those with the most come first.  Where the tiles alone leave the chip
+// idle each is split into `parts` of equally many steps, added in order after.
+// The two products of 8171 x 94104 (lower half) and 8171 x 4107 x 94104: 180 and
+// 149 ms dense in 256 x 128 tiles, now 12 and 15.
+struct SkipArgs {
+  int M, N, K;
+  const double *X, *Y;         // X(k, m) = X[m ld + k], Y(k, n) = Y[n ld + k]
+  long ld;
+  double* C;
+  long ldc;
+  int lower;
+  const unsigned long long *ox, *oy;   // occupancy of X's and Y's column tiles
+  int words;
+  const int* wild;
+  const int* order;            // [tiles] (m tile << 16) | n tile
+  int tiles, parts;
+  double* part;                // [tiles][parts][PT][PT] (parts > 1)
+};
+
+// Steps both tiles share, one wave per tile of the mt x nt grid (-1 above the
+// diagonal of a lower product).
+__global__ __launch_bounds__(256) void skip_count_kernel(SkipArgs g, int mt, int nt,
+                                                         int* __restrict__ count) {
+  const int t = (int)((blockIdx.x * 256 + threadIdx.x) >> 6), lane = threadIdx.x & 63;
+  if (t >= mt * nt) return;
+  const int m = t / nt, n = t % nt;
+  int c = 0;
+  for (int w = lane; w < g.words; w += 64)
+    c += __popcll(g.ox[(size_t)m * g.words + w] & g.oy[(size_t)n * g.words + w]);
+  for (int o = 32; o >= 1; o >>= 1) c += __shfl_xor(c, o, 64);
+  if (lane == 0) count[t] = g.lower && n > m ? -1 : c;
+}
+
+// The tiles in descending order of their steps (by 1024ths of the most there are).
+__global__ __launch_bounds__(1024) void skip_order_kernel(const int* __restrict__ count, int total,
+                                                          int nt, int most, int* __restrict__ order) {
+  __shared__ int s_at[1024], s_sum[1024];
+  const int tid = threadIdx.x;
+  auto bucket = [&](int c) { return 1023 - (int)((long)c * 1023 / max(1, most)); };
+  s_at[tid] = 0;
+  __syncthreads();
+  for (int t = tid; t < total; t += 1024)
+    if (count[t] >= 0) atomicAdd(&s_at[bucket(count[t])], 1);
+  __syncthreads();
+  const int own = s_at[tid];
+  s_sum[tid] = own;
+  __syncthreads();
+  for (int o = 1; o < 1024; o <<= 1) {
+    const int add = tid >= o ? s_sum[tid - o] : 0;
+    __syncthreads();
+    s_sum[tid] += add;
+    __syncthreads();
+  }
+  s_at[tid] = s_sum[tid] - own;
+  __syncthreads();
+  for (int t = tid; t < total; t += 1024)
+    if (count[t] >= 0) order[atomicAdd(&s_at[bucket(count[t])], 1)] = (t / nt) << 16 | (t % nt);
+}
+
+struct __attribute__((packed, aligned(8))) Two {   // rows k, k + 1 of a column
+  double a, b;
+};
+
+__global__ __launch_bounds__(256, 2) void skip_gemm_kernel(SkipArgs g) {
+  constexpr int LDT = PT + GPAD;
+  __shared__ double Xs[2][PK][LDT], Ys[2][PK][LDT];
+  extern __shared__ unsigned long long s_occ[];
+  __shared__ int s_steps;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int item = blockIdx.x / g.parts, q = blockIdx.x % g.parts;
+  const int mn = g.order[item];
+  const int m0 = (mn >> 16) * PT, n0 = (mn & 0xffff) * PT;
+  const int nk = (g.K + PK - 1) / PK;
+  if (tid == 0) s_steps = 0;
+  __syncthreads();
+  const bool all = *g.wild != 0;
+  int c = 0;
+  for (int w = tid; w < g.words; w += 256) {
+    const int left = nk - 64 * w;
+    const unsigned long long v =
+        all ? (left >= 64 ? ~0ull : (1ull << left) - 1)
+            : g.ox[(size_t)(mn >> 16) * g.words + w] & g.oy[(size_t)(mn & 0xffff) * g.words + w];
+    s_occ[w] = v;
+    c += __popcll(v);
+  }
+  if (c != 0) atomicAdd(&s_steps, c);
+  __syncthreads();
+  // this part's steps: numbers [first, first + left) of the tile's
+  const int steps = s_steps;
+  const int first = (int)((long)steps * q / g.parts);
+  int left = (int)((long)steps * (q + 1) / g.parts) - first;
+  int word = -1;
+  unsigned long long bits = 0;
+  for (int before = 0; left > 0;) {
+    bits = s_occ[++word];
+    const int n = __popcll(bits);
+    if (before + n > first) {
+      for (int k = first - before; k > 0; --k) bits &= bits - 1;
+      break;
+    }
+    before += n;
+  }
+  // row of the next step (left > 0)
+  auto next = [&]() {
+    while (bits == 0) bits = s_occ[++word];
+    const int k = (64 * word + __ffsll(bits) - 1) * PK;
+    bits &= bits - 1;
+    --left;
+    return __builtin_amdgcn_readfirstlane(k);
+  };
+  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+  d4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  // this thread's eight pairs of rows: rows 2 (tid % 8) and the next of columns
+  // tid / 8 + 32 u
+  const int kk = 2 * (tid & 7), mm = tid >> 3;
+  Two rx[4], ry[4];
+  auto fetch = [&](const double* P, int c0, int M, int k0, Two (&r)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int col = c0 + mm + 32 * u, k = k0 + kk;
+      r[u] = Two{0.0, 0.0};
+      if (col < M) {
+        const double* at = P + (long)col * g.ld + k;
+        if (k + 1 < g.K) r[u] = *reinterpret_cast<const Two*>(at);
+        else if (k < g.K) r[u].a = *at;
+      }
+    }
+  };
+  auto put = [&](const Two (&r)[4], double (*S)[LDT]) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      S[kk][mm + 32 * u] = r[u].a;
+      S[kk + 1][mm + 32 * u] = r[u].b;
+    }
+  };
+  bool more = left > 0;
+  if (more) {
+    const int k0 = next();
+    fetch(g.X, m0, g.M, k0, rx);
+    fetch(g.Y, n0, g.N, k0, ry);
+  }
+  for (int buf = 0; more; buf ^= 1) {
+    put(rx, Xs[buf]);
+    put(ry, Ys[buf]);
+    __syncthreads();   // the other buffer has been read by everyone, too
+    more = left > 0;
+    if (more) {
+      const int k0 = next();
+      fetch(g.X, m0, g.M, k0, rx);
+      fetch(g.Y, n0, g.N, k0, ry);
+    }
+#pragma unroll
+    for (int s = 0; s < PK / 4; ++s) {
+      const int kr = 4 * s + (lane >> 4);
+      double a[4], b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = Xs[buf][kr][wm + 16 * i + (lane & 15)];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = Ys[buf][kr][wn + 16 * j + (lane & 15)];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+  }
+  double* part = g.parts > 1 ? g.part + (size_t)blockIdx.x * PT * PT : nullptr;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = wm + 16 * i + 4 * r + (lane >> 4), n = wn + 16 * j + (lane & 15);
+        if (part != nullptr)
+          part[m * PT + n] = acc[i][j][r];
+        else if (m0 + m < g.M && n0 + n < g.N && (!g.lower || m0 + m >= n0 + n))
+          g.C[(long)(m0 + m) * g.ldc + n0 + n] = acc[i][j][r];
+      }
+}
+
+// The parts of each tile added in order.
+__global__ __launch_bounds__(256) void skip_reduce_kernel(SkipArgs g) {
+  const int item = blockIdx.y, e = blockIdx.x * 256 + threadIdx.x;
+  const int mn = g.order[item];
+  const int m = (mn >> 16) * PT + e / PT, n = (mn & 0xffff) * PT + e % PT;
+  if (m >= g.M || n >= g.N || (g.lower && m < n)) return;
+  double s = 0.0;
+  for (int q = 0; q < g.parts; ++q) s += g.part[((size_t)item * g.parts + q) * PT * PT + e];
+  g.C[(long)m * g.ldc + n] = s;
+}
+
+// Column tiles of an M x N product, and the parts each is split into: one round of
+// two workgroups a CU, parts of 16 steps or more.
+long skip_tiles(long M, long N, bool lower) {
+  const long mt = (M + PT - 1) / PT, nt = (N + PT - 1) / PT;
+  return lower ? mt * (mt + 1) / 2 : mt * nt;
+}
+int skip_parts(long tiles, long rows) {
+  return (int)std::clamp(std::min(512 / tiles, rows / PK / 16), 1L, 64L);
+}
+// Occupancy words a workgroup keeps beside its tiles, two workgroups in a CU's LDS
+// (1.6 million rows).
+constexpr int SKIP_WORDS = 1600;
+
+int skip_gemm(SkipArgs g, int* count, hipStream_t st) {
+  const int mt = (g.M + PT - 1) / PT, nt = (g.N + PT - 1) / PT;
+  g.tiles = (int)skip_tiles(g.M, g.N, g.lower);
+  g.parts = skip_parts(g.tiles, g.K);
+  int* order = count + (long)mt * nt;
+  g.order = order;
+  hipLaunchKernelGGL(skip_count_kernel, dim3((unsigned)((mt * nt + 3) / 4)), dim3(256), 0, st, g,
+                     mt, nt, count);
+  SYNIM_HIP_TRY(hipGetLastError());
+  hipLaunchKernelGGL(skip_order_kernel, dim3(1), dim3(1024), 0, st, count, mt * nt, nt,
+                     (g.K + PK - 1) / PK, order);
+  SYNIM_HIP_TRY(hipGetLastError());
+  hipLaunchKernelGGL(skip_gemm_kernel, dim3((unsigned)(g.tiles * g.parts)), dim3(256),
+                     g.words * sizeof(unsigned long long), st, g);
+  SYNIM_HIP_TRY(hipGetLastError());
+  if (g.parts > 1) {
+    hipLaunchKernelGGL(skip_reduce_kernel, dim3(PT * PT / 256, (unsigned)g.tiles), dim3(256), 0, st,
+                       g);
+    SYNIM_HIP_TRY(hipGetLastError());
+  }
+  return SYNIM_OK;
+}
+
+__global__ void zero_words_kernel(unsigned long long* __restrict__ p, long n) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = 0;
 }
 
 __global__ void zero_status_kernel(int* s) {
@@ -592,10 +976,12 @@ std::vector<int2> pupil_blocks(const uint8_t* pupil, int Hp, int Wp, int bin) {
 }
 
 struct ProjLayout {
-  size_t dirs, blocks, pupil, status, pt_dm, pt_l, gram, total;
+  size_t dirs, blocks, pupil, status, pt_dm, pt_l, gram, occ_dm, occ_l, count, part, total;
+  int words;       // occupancy words per column tile (0: the products take every step)
 };
 
-ProjLayout proj_layout(int n_dir, int n_blocks, int Hp, int Wp, long rows, long n_dm, long n_l) {
+ProjLayout proj_layout(int n_dir, int n_blocks, int Hp, int Wp, long rows, long n_dm, long n_l,
+                       bool with_skip = true) {
   ProjLayout L{};
   size_t off = 0;
   auto take = [&](size_t n) {
@@ -610,6 +996,22 @@ ProjLayout proj_layout(int n_dir, int n_blocks, int Hp, int Wp, long rows, long 
   L.pt_dm = take((size_t)n_dm * rows * sizeof(double));
   L.pt_l = take((size_t)n_l * rows * sizeof(double));
   L.gram = take((size_t)n_dm * n_dm * sizeof(double));
+  // the products' occupancy, tile lists and split sums (a single matrix has none)
+  const long mt = (n_dm + PT - 1) / PT, nt = (n_l + PT - 1) / PT, w = (rows + 64 * PK - 1) / (64 * PK);
+  const bool skip = with_skip && n_dm > 0 && n_l > 0 && w <= SKIP_WORDS && mt < 0x8000 && nt < 0x10000 &&
+                    mt * std::max(mt, nt) < INT_MAX / 64;
+  L.words = skip ? (int)w : 0;
+  L.occ_dm = take(skip ? mt * w * sizeof(unsigned long long) : 0);
+  L.occ_l = take(skip ? nt * w * sizeof(unsigned long long) : 0);
+  L.count = take(skip ? 2 * mt * std::max(mt, nt) * sizeof(int) : 0);
+  size_t part = 0;
+  if (skip)
+    for (const bool lower : {true, false}) {
+      const long tiles = skip_tiles(n_dm, lower ? n_dm : n_l, lower);
+      const int parts = skip_parts(tiles, rows);
+      if (parts > 1) part = std::max(part, (size_t)tiles * parts * PT * PT * sizeof(double));
+    }
+  L.part = take(part);
   L.total = off;
   return L;
 }
@@ -630,11 +1032,20 @@ long total_cols(const synim_proj_component* c, int n) {
   return t;
 }
 
+// Whether the directions and the pupil pixel are plain numbers (the window sampler
+// takes no others).
+bool plain_numbers(const double* dirs, int n_dir, double sp) {
+  bool ok = std::isfinite(sp);
+  for (int i = 0; i < 2 * n_dir; ++i) ok = ok && std::isfinite(dirs[i]);
+  return ok;
+}
+
 // Samples every component into Pt (columns in component order) from the
 // device tables at ws.
 int sample_all(const synim_proj_component* comps, int n_comp, const double2* dirs_dev, int n_dir,
                const int2* blocks_dev, int n_blocks, int bin, const uint8_t* pupil_dev, int Hp,
-               int Wp, double sp, double* Pt, long ld, hipStream_t st) {
+               int Wp, double sp, double* Pt, long ld, unsigned long long* occ, int words, int* wild,
+               bool plain, hipStream_t st) {
   long col = 0;
   const long rows = (long)n_dir * n_blocks;
   for (int c = 0; c < n_comp; ++c) {
@@ -656,15 +1067,43 @@ int sample_all(const synim_proj_component* comps, int n_comp, const double2* dir
     g.sp = sp;
     g.Pt = Pt + col * ld;
     g.ld = ld;
-    for (int a0 = 0; a0 < g.n; a0 += 65535) {
-      SampleArgs gg = g;
-      gg.basis = g.basis + (size_t)a0 * g.H * g.W;
-      gg.Pt = g.Pt + (long)a0 * ld;
-      gg.n = std::min(65535, g.n - a0);
-      hipLaunchKernelGGL(proj_sample_kernel,
-                         dim3((unsigned)((rows + 255) / 256), (unsigned)gg.n), dim3(256), 0, st,
-                         gg);
+    g.col0 = col;
+    g.occ = occ;
+    g.words = words;
+    g.wild = wild;
+    // grid points a block's taps can span along a side
+    const double span = (bin - 1) * sp / g.s;
+    const int need = bin == 1 ? 2 : span < 8.0 ? (int)(span * (1 + 1e-9) + 1e-9) + 3 : 99;
+    const int NT = (need + 1) / 2 * 2;
+    if (NT <= 8 && NT <= std::min(g.H, g.W) && plain && std::isfinite(g.h) && std::isfinite(g.s)) {
+      const int n_rb = (int)((rows + 255) / 256);
+      // functions per workgroup: 64 spread the weights' cost best, fewer where that
+      // would leave less than eight workgroups a CU
+      g.group = 64;
+      while (g.group > 8 && (long)n_rb * ((g.n + g.group - 1) / g.group) < 2048) g.group /= 2;
+      long groups = (col + g.n - 1) / g.group - col / g.group + 1;
+      const bool by_xcd = groups >= 8;
+      if (by_xcd) groups = (groups + 7) / 8 * 8;
+      if (groups * n_rb > INT_MAX) return SYNIM_E_SHAPE;
+      const auto kernel = NT == 2   ? proj_window_kernel<2>
+                          : NT == 4 ? proj_window_kernel<4>
+                          : NT == 6 ? proj_window_kernel<6>
+                                    : proj_window_kernel<8>;
+      hipLaunchKernelGGL(kernel, dim3((unsigned)(groups * n_rb)), dim3(256), 0, st, g, n_rb,
+                         by_xcd ? 1 : 0);
       SYNIM_HIP_TRY(hipGetLastError());
+    } else {
+      for (int a0 = 0; a0 < g.n; a0 += 65535) {
+        SampleArgs gg = g;
+        gg.basis = g.basis + (size_t)a0 * g.H * g.W;
+        gg.Pt = g.Pt + (long)a0 * ld;
+        gg.col0 = col + a0;
+        gg.n = std::min(65535, g.n - a0);
+        hipLaunchKernelGGL(proj_sample_kernel,
+                           dim3((unsigned)((rows + 255) / 256), (unsigned)gg.n), dim3(256), 0, st,
+                           gg);
+        SYNIM_HIP_TRY(hipGetLastError());
+      }
     }
     col += g.n;
   }
@@ -732,7 +1171,7 @@ extern "C" int synim_proj_matrix(const synim_proj_component* comps, int n_comp,
   rc = sample_all(comps, n_comp, reinterpret_cast<const double2*>(w + L.dirs), n_dir,
                   reinterpret_cast<const int2*>(w + L.blocks), (int)blocks.size(), bin,
                   reinterpret_cast<const uint8_t*>(w + L.pupil), Hp, Wp, pupil_pixel_m, Pt, ld,
-                  st);
+                  nullptr, 0, nullptr, plain_numbers(dirs, n_dir, pupil_pixel_m), st);
   if (rc != SYNIM_OK) return rc;
   // the host vectors must outlive the copies
   SYNIM_HIP_TRY(hipStreamSynchronize(st));
@@ -780,7 +1219,10 @@ extern "C" int synim_proj_opt(const synim_proj_component* dms, int n_dm,
   const long rows = (long)blocks.size() * n_dir;
   const long ndm = total_cols(dms, n_dm), nl = total_cols(layers, n_layer);
   if (ndm > INT_MAX || nl > INT_MAX || rows > INT_MAX) return SYNIM_E_SHAPE;
-  const ProjLayout L = proj_layout(n_dir, (int)blocks.size(), Hp, Wp, rows, ndm, nl);
+  ProjLayout L = proj_layout(n_dir, (int)blocks.size(), Hp, Wp, rows, ndm, nl);
+  // a workspace that holds the matrices alone is enough for the dense products
+  if (ws_bytes < L.total)
+    L = proj_layout(n_dir, (int)blocks.size(), Hp, Wp, rows, ndm, nl, false);
   if (ws_bytes < L.total) return SYNIM_E_WORKSPACE;
   char* w = static_cast<char*>(ws);
   SYNIM_HIP_TRY(hipMemcpyAsync(w + L.dirs, dirs, (size_t)n_dir * sizeof(double2),
@@ -797,21 +1239,54 @@ extern "C" int synim_proj_opt(const synim_proj_component* dms, int n_dm,
   const auto* dirs_dev = reinterpret_cast<const double2*>(w + L.dirs);
   const auto* blocks_dev = reinterpret_cast<const int2*>(w + L.blocks);
   const auto* pupil_dev = reinterpret_cast<const uint8_t*>(w + L.pupil);
+  int* status = reinterpret_cast<int*>(w + L.status);
+  auto* occ_dm = reinterpret_cast<unsigned long long*>(w + L.occ_dm);
+  auto* occ_l = reinterpret_cast<unsigned long long*>(w + L.occ_l);
+  if (L.words > 0) {
+    const long n = (long)(L.count - L.occ_dm) / 8;   // both occupancies
+    hipLaunchKernelGGL(zero_words_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                       occ_dm, n);
+    SYNIM_HIP_TRY(hipGetLastError());
+  } else {
+    occ_dm = occ_l = nullptr;
+  }
+  const bool plain = plain_numbers(dirs, n_dir, pupil_pixel_m);
   rc = sample_all(dms, n_dm, dirs_dev, n_dir, blocks_dev, (int)blocks.size(), bin, pupil_dev, Hp,
-                  Wp, pupil_pixel_m, pt_dm, rows, st);
+                  Wp, pupil_pixel_m, pt_dm, rows, occ_dm, L.words, status + 1, plain, st);
   if (rc == SYNIM_OK)
     rc = sample_all(layers, n_layer, dirs_dev, n_dir, blocks_dev, (int)blocks.size(), bin,
-                    pupil_dev, Hp, Wp, pupil_pixel_m, pt_l, rows, st);
+                    pupil_dev, Hp, Wp, pupil_pixel_m, pt_l, rows, occ_l, L.words, status + 1,
+                    plain, st);
   if (rc != SYNIM_OK) return rc;
   // G = Pt_dm Pt_dm^T (lower triangle) + lambda I;  B = Pt_dm Pt_l^T into popt
-  GemmArgs g{(int)ndm, (int)ndm, (int)rows, pt_dm, 1, rows, pt_dm, 1, rows, G, ndm, 1.0, 0.0, 1};
-  if ((rc = gemm(g, st)) != SYNIM_OK) return rc;
+  auto product = [&](const double* Y, const unsigned long long* oy, long N, double* C, long ldc,
+                     int lower) {
+    if (L.words == 0) {
+      return gemm(GemmArgs{(int)ndm, (int)N, (int)rows, pt_dm, 1, rows, Y, 1, rows, C, ldc, 1.0, 0.0,
+                           lower}, st);
+    }
+    SkipArgs g{};
+    g.M = (int)ndm;
+    g.N = (int)N;
+    g.K = (int)rows;
+    g.X = pt_dm;
+    g.Y = Y;
+    g.ld = rows;
+    g.C = C;
+    g.ldc = ldc;
+    g.lower = lower;
+    g.ox = occ_dm;
+    g.oy = oy;
+    g.words = L.words;
+    g.wild = status + 1;
+    g.part = reinterpret_cast<double*>(w + L.part);
+    return skip_gemm(g, reinterpret_cast<int*>(w + L.count), st);
+  };
+  if ((rc = product(pt_dm, occ_dm, ndm, G, ndm, 1)) != SYNIM_OK) return rc;
   hipLaunchKernelGGL(add_diag_kernel, dim3((unsigned)((ndm + 255) / 256)), dim3(256), 0, st, G,
                      (int)ndm, ndm, lambda);
   SYNIM_HIP_TRY(hipGetLastError());
-  GemmArgs b{(int)ndm, (int)nl, (int)rows, pt_dm, 1, rows, pt_l, 1, rows, popt, nl, 1.0, 0.0, 0};
-  if ((rc = gemm(b, st)) != SYNIM_OK) return rc;
-  int* status = reinterpret_cast<int*>(w + L.status);
+  if ((rc = product(pt_l, occ_l, nl, popt, nl, 0)) != SYNIM_OK) return rc;
   // the sampled matrices are spent: their memory holds the inverted diagonal
   // blocks and the copies the solves work from
   // (where they are too small, the substitution forms need no memory)
