@@ -28,6 +28,22 @@ __device__ __forceinline__ void src_xy(const MapD& m, int x, int y, double& xs, 
   ys = __fma_rn(m.a11, (double)y, __fma_rn(m.a10, (double)x, m.b1));
 }
 
+// First index j of the ascending list valid[0..n) with valid[j] >= k (n if none),
+// by a whole wave: every lane tests one of 64 spread entries, three steps for
+// 4632 of them.
+__device__ __forceinline__ int first_at_least(const int32_t* valid, int n, int k, int lane) {
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int step = (hi - lo + 63) / 64;
+    const int at = lo + lane * step;
+    const int c = __popcll(__ballot(at < hi && valid[min(at, n - 1)] < k));
+    if (c == 0) break;   // the first c lanes' entries are below k
+    lo = lo + (c - 1) * step + 1;
+    hi = min(hi, lo - 1 + step);
+  }
+  return lo;
+}
+
 #define SYNIM_HIP_TRY(expr)                              \
   do {                                                   \
     hipError_t _e = (expr);                              \

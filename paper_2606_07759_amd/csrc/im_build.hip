@@ -13,9 +13,9 @@
 // pixels starting at its origin) with s_x[k](a) = <W_k^x, F_a[patch_k]>.
 //
 // Plan (FP64, on the device, once per geometry):
-//   plan_subaps   origin and 1/(2 n_k) of each valid subaperture;
-//   plan_weights  one thread per patch entry gathers every (q, tap) that lands
-//                 on it; the Jacobian planes use d w_tap / d theta_j from the
+//   plan_weights  origin and 1/(2 n_k) of each valid subaperture, then one
+//                 thread per patch entry gathers every (q, tap) that lands on
+//                 it; the Jacobian planes use d w_tap / d theta_j from the
 //                 floor-cell bilinear gradient and the derivative maps;
 //   plan_rows     groups subapertures into tiles and lists, for every tile,
 //                 the IF rows its patches touch, each trimmed to the columns
@@ -76,16 +76,13 @@ struct PlanJob {
   int engine;                 // slope engine: ENGINE_CD or ENGINE_TSUM
   int2* origin;
   int2* hrows;                // [nv] patch rows [x, y) holding a non-zero weight
-  double* inv2nk;
+  int2* info;                 // [nv] (status bits, samples outside the IF grid)
   float* weights;             // [plane][kk][2*PH*PW], in lane order (plan_weight_entry)
   int* slot_kk;               // [tile][NSLOT]
   int4* tile_info;            // [tile] (y0, rows, packed floats, 0)
   int2* rows;                 // [tile][BHmax] (first column, packed offset)
   int* status;
   int* counters;              // the stream kernel's work and sync counters
-  // [nv] pupil pixels of each subaperture, bit y*p + x (x, y within it), for
-  // p <= 8; null otherwise (the weights then read the pupil itself)
-  unsigned long long* submask;
   MapD minv;                  // inverse of m's linear part (used when m_dev is null)
 };
 
@@ -207,67 +204,51 @@ __device__ __forceinline__ int in_sub(const uint8_t* __restrict__ pupil, int W, 
   return (x >= x0 && x < x0 + p && y >= y0 && y < y0 + p && pupil[(size_t)y * W + x]) ? 1 : 0;
 }
 
-// Origin (patch corner) and 1/(2 n_k) of each valid subaperture: one wave
-// per subaperture, its lanes splitting the haloed window's samples and the
-// subaperture's pixels (min, max and counts do not depend on the order).
-constexpr int PLAN_SUBAPS_BLOCK = 256;
-__device__ __forceinline__ double wave_min(double v) {
-  for (int o = 32; o >= 1; o >>= 1) v = fmin(v, __shfl_xor(v, o, 64));
-  return v;
-}
-__device__ __forceinline__ double wave_max(double v) {
-  for (int o = 32; o >= 1; o >>= 1) v = fmax(v, __shfl_xor(v, o, 64));
-  return v;
-}
-template <bool TABLE>
-__global__ __launch_bounds__(PLAN_SUBAPS_BLOCK) void plan_subaps_kernel(
-    PlanJob one, const PlanJob* __restrict__ jobs) {
-  const PlanJob& J = job_of<TABLE>(one, jobs);
-  const int kk = (int)((blockIdx.x * PLAN_SUBAPS_BLOCK + threadIdx.x) >> 6);
-  const int lane = threadIdx.x & 63;
-  if (kk >= J.nv) return;   // whole waves
-  const MapD m = J.m_dev ? *J.m_dev : J.m;
+// What the weights of a subaperture need, kept in LDS by their workgroup.
+struct SubPlan {
+  int2 origin;                // patch corner
+  double inv2nk;              // 1 / (2 n_k), 0 without pupil pixels
+  unsigned long long mask;    // its pupil pixels, bit y*p + x, for p <= 8
+  int lo, hi;                 // patch rows [lo, hi) holding a non-zero weight
+  int x0, y0;                 // its first pixel
+};
+
+// Subaperture kk, by one wave.
+__device__ __forceinline__ void plan_sub(const PlanJob& J, const MapD& m, int kk, int lane,
+                                         SubPlan& out) {
   const int p = J.p;
   const int k = J.valid[kk];
   const int u = k % J.n_sub_x, v = k / J.n_sub_x;
   const int W = J.n_sub_x * p, H = J.n_sub_y * p;
   const bool repair = J.dm_mask != nullptr;
   const int pad = repair ? REPAIR_PAD : 0;
-  double xmin = 1e300, xmax = -1e300, ymin = 1e300, ymax = -1e300;
-  const int hw = sample_window(p, repair);   // (grown) haloed window side
-  for (int i = lane; i < hw * hw; i += 64) {
-    const int y = v * p - 1 - pad + i / hw, x = u * p - 1 - pad + i % hw;
-    if (x < -1 || x > W || y < -1 || y > H) continue;   // outside the WFS window
-    double xs, ys;
-    src_xy(m, x, y, xs, ys);
-    xmin = fmin(xmin, xs);
-    xmax = fmax(xmax, xs);
-    ymin = fmin(ymin, ys);
-    ymax = fmax(ymax, ys);
-  }
-  xmin = wave_min(xmin);
-  ymin = wave_min(ymin);
-  xmax = wave_max(xmax);
-  ymax = wave_max(ymax);
+  const int x0 = u * p, y0 = v * p;
   int nk = 0;
-  for (int i = lane; i < p * p; i += 64) {
-    const int y = v * p + i / p, x = u * p + i % p;
-    nk += J.pupil[(size_t)y * W + x] ? 1 : 0;
+  unsigned long long mask = 0;
+  for (int i = lane; i - lane < p * p; i += 64) {
+    const unsigned long long in =
+        __ballot(i < p * p && J.pupil[(size_t)(y0 + i / p) * W + x0 + i % p]);
+    nk += __popcll(in);
+    mask = in;
   }
-  for (int o = 32; o >= 1; o >>= 1) nk += __shfl_xor(nk, o, 64);
-  if (J.submask != nullptr) {
-    // lane i holds pixel (i % p, i / p) of the subaperture (p * p <= 64)
-    const bool in = lane < p * p && J.pupil[(size_t)(v * p + lane / p) * W + u * p + lane % p];
-    const unsigned long long mk = __ballot(in);
-    if (lane == 0) J.submask[kk] = mk;
-  }
+  // The source coordinates of the (grown) haloed window, inside the WFS window,
+  // lie between those of two of its corners: a rounded multiply-add is monotone
+  // in its argument, so this is the minimum over its samples to the bit.
+  const int xl = max(x0 - 1 - pad, -1), xh = min(x0 + p + pad, W);
+  const int yl = max(y0 - 1 - pad, -1), yh = min(y0 + p + pad, H);
+  double xmin, xmax, ymin, ymax, other;
+  src_xy(m, m.a00 >= 0.0 ? xl : xh, m.a01 >= 0.0 ? yl : yh, xmin, other);
+  src_xy(m, m.a00 >= 0.0 ? xh : xl, m.a01 >= 0.0 ? yh : yl, xmax, other);
+  src_xy(m, m.a10 >= 0.0 ? xl : xh, m.a11 >= 0.0 ? yl : yh, other, ymin);
+  src_xy(m, m.a10 >= 0.0 ? xh : xl, m.a11 >= 0.0 ? yh : yl, other, ymax);
   // samples this subaperture's central differences read (a non-zero c_x or
   // c_y) whose source point lies outside the IF grid: their bilinear taps
   // are zero-filled
   // (with edge repair: a non-zero effective coefficient)
   int oob = 0;
-  if (J.W_in > 0) {
-    const int x0 = u * p, y0 = v * p;
+  const double xe = J.W_in - 1.0, ye = J.H_in - 1.0;
+  if (J.W_in > 0 && !(xmin >= 0.0 && xmax <= xe && ymin >= 0.0 && ymax <= ye)) {
+    const int hw = sample_window(p, repair);   // (grown) haloed window side
     for (int i = lane; i < hw * hw; i += 64) {
       const int y = y0 - 1 - pad + i / hw, x = x0 - 1 - pad + i % hw;
       bool used;
@@ -282,74 +263,173 @@ __global__ __launch_bounds__(PLAN_SUBAPS_BLOCK) void plan_subaps_kernel(
       if (!used) continue;
       double xs, ys;
       src_xy(m, x, y, xs, ys);
-      if (!(xs >= 0.0 && xs <= J.W_in - 1.0 && ys >= 0.0 && ys <= J.H_in - 1.0)) ++oob;
+      if (!(xs >= 0.0 && xs <= xe && ys >= 0.0 && ys <= ye)) ++oob;
     }
     for (int o = 32; o >= 1; o >>= 1) oob += __shfl_xor(oob, o, 64);
   }
   if (lane != 0) return;
-  if (oob > 0) atomicAdd(J.status + 2, oob);
-  int ox = 0, oy = 0;
+  int ox = 0, oy = 0, bits = nk == 0 ? 4 : 0;
   if (fabs(xmin) < 1e9 && fabs(xmax) < 1e9 && fabs(ymin) < 1e9 && fabs(ymax) < 1e9) {
     ox = (int)floor(xmin);
     oy = (int)floor(ymin);
     // the last tap column is floor(xmax) + 1
-    if ((int)floor(xmax) + 2 - ox > J.PW || (int)floor(ymax) + 2 - oy > J.PH)
-      atomicOr(J.status, 1);
+    if ((int)floor(xmax) + 2 - ox > J.PW || (int)floor(ymax) + 2 - oy > J.PH) bits |= 1;
   } else {
-    atomicOr(J.status, 1);
+    bits |= 1;
   }
-  if (nk == 0) atomicOr(J.status, 4);
-  J.origin[kk] = make_int2(ox, oy);
-  J.hrows[kk] = make_int2(J.PH, 0);   // narrowed by plan_weights
-  J.inv2nk[kk] = nk > 0 ? 1.0 / (2.0 * nk) : 0.0;
+  out.origin = make_int2(ox, oy);
+  out.inv2nk = nk > 0 ? 1.0 / (2.0 * nk) : 0.0;
+  out.mask = mask;
+  out.lo = J.PH;
+  out.hi = 0;
+  out.x0 = x0;
+  out.y0 = y0;
+  J.info[kk] = make_int2(bits, oob);
 }
 
-
-// Weight patch entry gid = (valid subaperture, patch entry): gathers, in a
-// fixed order, every haloed-window sample q whose bilinear cell has this entry
-// as a tap.  Weights layout: [plane][kk][2*PH*PW] in lane order.  A used entry
-// widens its subaperture's row range in s_lo/s_hi (index kk - kk0).
-// MULTI = false: the IM plane alone (J.n_planes == 1); the derivative maps and
-// their accumulators then take no registers.
-template <bool MULTI>
-__device__ __forceinline__ void plan_weight_entry(const PlanJob& J, int E, long gid, int kk0,
-                                                  int* s_lo, int* s_hi) {
-  const MapD m = J.m_dev ? *J.m_dev : J.m;
-  const int p = J.p;
-  // inverse of the linear part, for the window of candidate samples
+// Inverse of the map's linear part and the half sides of the box of output pixels
+// whose source points can have a tap at a given grid point.
+struct Inverse {
+  double a00, a01, a10, a11, rx, ry;
+};
+__device__ __forceinline__ Inverse plan_inverse(const PlanJob& J, const MapD& m) {
   MapD inv = J.minv;
   if (J.m_dev) {
     const double det = m.a00 * m.a11 - m.a01 * m.a10;
     inv = MapD{m.a11 / det, -m.a01 / det, -m.a10 / det, m.a00 / det, 0, 0};
   }
-  const double rx = fabs(inv.a00) + fabs(inv.a01) + 0.01;
-  const double ry = fabs(inv.a10) + fabs(inv.a11) + 0.01;
-  const int kk = (int)(gid / E);
-  const int e = (int)(gid - (long)kk * E);
+  return Inverse{inv.a00, inv.a01, inv.a10, inv.a11, fabs(inv.a00) + fabs(inv.a01) + 0.01,
+                 fabs(inv.a10) + fabs(inv.a11) + 0.01};
+}
+
+// Scales and stores the weights of patch entry (r, c).  Where the stream kernel's
+// lanes read it: lane q of a subaperture holds patch rows q + LPS i; its floats
+// (component, i, column) are stored four at a time, the lanes side by side, so
+// that one 16-byte load of a wave touches one line per subaperture (rows stored
+// whole took one line per lane: 64 for a wave).
+template <int NP>
+__device__ __forceinline__ bool plan_store(const PlanJob& J, int n_planes, int E, int kk, int r,
+                                           int c, const double (&acc)[NP][2], double s) {
+  const int LPS = J.LPS, sh = 31 - __clz(LPS);   // a power of two
+  const int ri = r >> sh, rq = r & (LPS - 1);
+  const int fe = ri * J.PW + c, FX = (J.PH >> sh) * J.PW;
+  const int at_x = ((fe >> 2) * LPS + rq) * 4 + (fe & 3);
+  const int at_y = (((fe + FX) >> 2) * LPS + rq) * 4 + ((fe + FX) & 3);
+  bool used = false;
+#pragma unroll
+  for (int j = 0; j < NP; ++j) {
+    if (j >= n_planes) break;
+    used = used || acc[j][0] != 0.0 || acc[j][1] != 0.0;
+    float* w = J.weights + ((size_t)j * J.nv + kk) * 2 * E;
+    w[at_x] = (float)(acc[j][0] * s);
+    w[at_y] = (float)(acc[j][1] * s);
+  }
+  return used;
+}
+
+// The haloed-window samples of a workgroup's subapertures (central differences
+// without edge repair), formed once: where in its cell the source point lies, and
+// the cell relative to the patch corner with the difference coefficients, packed.
+constexpr int PLAN_SAMPLES = 512;
+struct SampleTable {
+  double2 ab[PLAN_SAMPLES];   // position within the cell
+  int word[PLAN_SAMPLES];     // (column << 16 | row << 4 | (c_x + 1) << 2 | c_y + 1), -1: unread
+};
+
+// plan_weight_entry from the table, the same operations in the same order.  Three
+// candidates of a row are fetched together.
+template <bool MULTI>
+__device__ __forceinline__ bool plan_table_entry(const PlanJob& J, const MapD& m, int E, int kk,
+                                                 int e, const Inverse& q, const SubPlan& sub,
+                                                 const SampleTable& tab, int tab0, int sx0,
+                                                 int sy0) {
+  const int p = J.p, RW = p + 2;
+  const int r = e / J.PW, c = e - (e / J.PW) * J.PW;
+  const double dx = (double)(sub.origin.x + c) - m.b0, dy = (double)(sub.origin.y + r) - m.b1;
+  const double qx = q.a00 * dx + q.a01 * dy;
+  const double qy = q.a10 * dx + q.a11 * dy;
+  const int xl = max(-1, (int)ceil(qx - q.rx) - sx0), xh = min(p, (int)floor(qx + q.rx) - sx0);
+  const int yl = max(-1, (int)ceil(qy - q.ry) - sy0), yh = min(p, (int)floor(qy + q.ry) - sy0);
+  const int n_planes = MULTI ? J.n_planes : 1;
+  constexpr int NP = MULTI ? 5 : 1;
+  double acc[NP][2];
+#pragma unroll
+  for (int j = 0; j < NP; ++j) acc[j][0] = acc[j][1] = 0.0;
+  for (int y = yl; y <= yh; ++y)
+    for (int x = xl; x <= xh; x += 3) {
+      const int at = tab0 + (y + 1) * RW + x + 1;
+      const int n = xh - x;   // this one and n more
+      int word[3];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) word[k] = tab.word[at + min(k, n)];
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        const unsigned di = (unsigned)(c - (word[k] >> 16));
+        const unsigned dj = (unsigned)(r - ((word[k] >> 4) & 0xfff));
+        if (k > n || word[k] < 0 || di > 1u || dj > 1u) continue;
+        const double2 ab = tab.ab[at + k];
+        const double cx = ((word[k] >> 2) & 3) - 1, cy = (word[k] & 3) - 1;
+        const double wx = di == 0u ? 1.0 - ab.x : ab.x;
+        const double wy = dj == 0u ? 1.0 - ab.y : ab.y;
+        const double w = wx * wy;
+        acc[0][0] += cx * w;
+        acc[0][1] += cy * w;
+        if constexpr (MULTI) {
+          if (n_planes > 1) {
+            const Map4& dm = J.dm_dev ? *J.dm_dev : J.dm;
+            // floor-cell gradient of the tap weight w.r.t. the source point
+            const double dwa = (di == 0u ? -1.0 : 1.0) * wy;
+            const double dwb = (dj == 0u ? -1.0 : 1.0) * wx;
+            const int gx = sx0 + x + k, gy = sy0 + y;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              const double dxs = dm.m[j].a00 * gx + dm.m[j].a01 * gy + dm.m[j].b0;
+              const double dys = dm.m[j].a10 * gx + dm.m[j].a11 * gy + dm.m[j].b1;
+              const double d = dwa * dxs + dwb * dys;
+              acc[1 + j][0] += cx * d;
+              acc[1 + j][1] += cy * d;
+            }
+          }
+        }
+      }
+    }
+  return plan_store<NP>(J, n_planes, E, kk, r, c, acc, sub.inv2nk);
+}
+
+// Weight patch entry e of valid subaperture kk: gathers, in a fixed order, every
+// haloed-window sample q whose bilinear cell has this entry as a tap.  Weights
+// layout: [plane][kk][2*PH*PW] in lane order.  Returns whether any plane's weight
+// is used.
+// MULTI = false: the IM plane alone (J.n_planes == 1); the derivative maps and
+// their accumulators then take no registers.
+template <bool MULTI>
+__device__ __forceinline__ bool plan_weight_entry(const PlanJob& J, const MapD& m, int E, int kk,
+                                                  int e, const Inverse& q, SubPlan& sub) {
+  const int p = J.p;
   const int r = e / J.PW, c = e - (e / J.PW) * J.PW;
   const int k = J.valid[kk];
   const int u = k % J.n_sub_x, v = k / J.n_sub_x;
   const int W = J.n_sub_x * p;
-  const int2 o = J.origin[kk];
+  const int2 o = sub.origin;
   const int X = o.x + c, Y = o.y + r;
 
   // candidate window: p_o = A^-1 (p_s - b) with p_s in [X-1, X+1) x [Y-1, Y+1)
   const double dx = (double)X - m.b0, dy = (double)Y - m.b1;
-  const double qx = inv.a00 * dx + inv.a01 * dy;
-  const double qy = inv.a10 * dx + inv.a11 * dy;
+  const double qx = q.a00 * dx + q.a01 * dy;
+  const double qy = q.a10 * dx + q.a11 * dy;
   const bool repair = J.dm_mask != nullptr;
   const int pad = repair ? REPAIR_PAD : 0;
   const int RW = sample_window(p, repair);
   const int H = J.n_sub_y * p;
-  const int xl = max(max(u * p - 1 - pad, -1), (int)ceil(qx - rx));
-  const int xh = min(min(u * p + p + pad, W), (int)floor(qx + rx));
-  const int yl = max(max(v * p - 1 - pad, -1), (int)ceil(qy - ry));
-  const int yh = min(min(v * p + p + pad, H), (int)floor(qy + ry));
+  const int xl = max(max(u * p - 1 - pad, -1), (int)ceil(qx - q.rx));
+  const int xh = min(min(u * p + p + pad, W), (int)floor(qx + q.rx));
+  const int yl = max(max(v * p - 1 - pad, -1), (int)ceil(qy - q.ry));
+  const int yh = min(min(v * p + p + pad, H), (int)floor(qy + q.ry));
   const int sx0 = u * p, sy0 = v * p;
   // pixel (x, y) of the WFS grid is a pupil pixel of subaperture kk
-  const unsigned long long mk = J.submask ? J.submask[kk] : 0ull;
+  const unsigned long long mk = sub.mask;
   auto in_k = [&](int x, int y) -> int {
-    if (J.submask == nullptr) return in_sub(J.pupil, W, sx0, sy0, p, x, y);
+    if (p > 8) return in_sub(J.pupil, W, sx0, sy0, p, x, y);
     return (x >= sx0 && x < sx0 + p && y >= sy0 && y < sy0 + p &&
             ((mk >> ((y - sy0) * p + (x - sx0))) & 1ull))
                ? 1
@@ -429,68 +509,98 @@ __device__ __forceinline__ void plan_weight_entry(const PlanJob& J, int E, long 
         }
       }
     }
-  const double s = J.inv2nk[kk];
-  // where the stream kernel's lanes read it: lane q of a subaperture holds
-  // patch rows q + LPS i; its floats (component, i, column) are stored four at
-  // a time, the lanes side by side, so that one 16-byte load of a wave
-  // touches one line per subaperture (rows stored whole took one line per
-  // lane: 64 for a wave)
-  const int LPS = J.LPS, fe = (r / LPS) * J.PW + c, FX = (J.PH / LPS) * J.PW;
-  const int at_x = ((fe >> 2) * LPS + r % LPS) * 4 + (fe & 3);
-  const int at_y = (((fe + FX) >> 2) * LPS + r % LPS) * 4 + ((fe + FX) & 3);
-  bool used = false;
-#pragma unroll
-  for (int j = 0; j < NP; ++j)
-    if (j < n_planes) used = used || acc[j][0] != 0.0 || acc[j][1] != 0.0;
-  if (used) {
-    atomicMin(&s_lo[kk - kk0], r);
-    atomicMax(&s_hi[kk - kk0], r + 1);
-  }
-#pragma unroll
-  for (int j = 0; j < NP; ++j) {
-    if (j >= n_planes) break;
-    float* w = J.weights + ((size_t)j * J.nv + kk) * 2 * E;
-    w[at_x] = (float)(acc[j][0] * s);
-    w[at_y] = (float)(acc[j][1] * s);
-  }
+  return plan_store<NP>(J, n_planes, E, kk, r, c, acc, sub.inv2nk);
 }
 
-// One thread per (valid subaperture, patch entry), PLAN_WEIGHTS_BLOCK per
-// workgroup.  MULTI: some job has derivative planes (n_planes > 1).
-constexpr int PLAN_WEIGHTS_BLOCK = 256;
-template <bool MULTI, bool TABLE>
-__global__ __launch_bounds__(PLAN_WEIGHTS_BLOCK) void plan_weights_kernel(
-    PlanJob one, const PlanJob* __restrict__ jobs) {
+// Words a launch clears for the kernels behind it.
+struct ClearWords {
+  int* p[2];
+  int n[2];
+};
+
+// One workgroup per run of whole subapertures, as many as its threads have patch
+// entries for: a wave forms each one's origin, count and mask into LDS, then the
+// threads its table of samples, then a thread gathers an entry.  Bound by the
+// FP64 and index instructions of the entries (a few microseconds of latency at
+// small sizes).  In three launches, the first clearing the status words and the
+// second for the subapertures alone, and with every entry forming its candidates'
+// coordinates, cells and pupil tests, the 14 plans of a group of six sensors of
+// 3352 subapertures took 236 us, now 178; 52 subapertures 17, now 7 (a whole build
+// of 49 actuators on them 38.8, now 32.3).  Nothing is summed over workgroups here: a
+// subaperture's status bits and out-of-grid samples are left in `info` for
+// plan_rows.  MULTI: some job has derivative planes (n_planes > 1).
+constexpr int PLAN_BLOCK = 256, PLAN_SUBS = 8;   // threads, subapertures at most
+// SAMPLES: every job's samples fit the table (plan_table), no edge repair or
+// telescoping sums.
+template <bool MULTI, bool TABLE, bool SAMPLES>
+__global__ __launch_bounds__(PLAN_BLOCK) void plan_weights_kernel(
+    PlanJob one, const PlanJob* __restrict__ jobs, int spb, ClearWords z) {
   const PlanJob& J = job_of<TABLE>(one, jobs);
+  __shared__ SubPlan s_sub[PLAN_SUBS];
+  __shared__ Inverse s_inv;
+  __shared__ SampleTable s_tab;   // (SAMPLES)
+  const int tid = threadIdx.x, lane = tid & 63, T = blockDim.x;
+  if (blockIdx.x == 0 && tid < 16) J.status[tid] = 0;
+  if (blockIdx.y == 0)
+    for (int k = 0; k < 2; ++k)
+      for (int i = blockIdx.x * T + tid; i < z.n[k]; i += gridDim.x * T) z.p[k][i] = 0;
   const int E = J.PH * J.PW;
-  const long g0 = (long)blockIdx.x * PLAN_WEIGHTS_BLOCK;
-  const long gid = g0 + threadIdx.x;
-  // rows holding a weight, per subaperture of this workgroup (at most
-  // PLAN_WEIGHTS_BLOCK of them, relative to the first): reduced in LDS, then
-  // one global atomic pair per subaperture and workgroup
-  __shared__ int s_lo[PLAN_WEIGHTS_BLOCK], s_hi[PLAN_WEIGHTS_BLOCK];
-  const int kk0 = (int)(g0 / E);
-  s_lo[threadIdx.x] = INT_MAX;
-  s_hi[threadIdx.x] = INT_MIN;
+  const int kk0 = blockIdx.x * spb;
+  if (kk0 >= J.nv) return;
+  const int ns = min(spb, J.nv - kk0);
+  const MapD m = J.m_dev ? *J.m_dev : J.m;
+  if (tid == T - 1) s_inv = plan_inverse(J, m);
+  for (int i = tid >> 6; i < ns; i += T >> 6) plan_sub(J, m, kk0 + i, lane, s_sub[i]);
   __syncthreads();
-  if (gid < (long)J.nv * E) plan_weight_entry<MULTI>(J, E, gid, kk0, s_lo, s_hi);
+  const int p = J.p;
+  if constexpr (SAMPLES) {
+    const int RW = p + 2, RR = RW * RW, W = J.n_sub_x * p;
+    for (int q = tid; q < ns * RR; q += T) {
+      const int i = q / RR, at = q - i * RR;
+      const SubPlan& sub = s_sub[i];
+      const int y = at / RW - 1, x = at - (y + 1) * RW - 1;   // within the subaperture
+      const unsigned long long mk = sub.mask;
+      auto in_k = [&](int u, int v) -> int {
+        if (p > 8) return in_sub(J.pupil, W, sub.x0, sub.y0, p, sub.x0 + u, sub.y0 + v);
+        return u >= 0 && u < p && v >= 0 && v < p && ((mk >> (v * p + u)) & 1ull) ? 1 : 0;
+      };
+      const int cx = in_k(x - 1, y) - in_k(x + 1, y);
+      const int cy = in_k(x, y - 1) - in_k(x, y + 1);
+      double xs, ys;
+      src_xy(m, sub.x0 + x, sub.y0 + y, xs, ys);
+      const double fi = floor(xs), fj = floor(ys);
+      s_tab.ab[q] = make_double2(xs - fi, ys - fj);
+      // a cell that no patch entry touches (a plan whose status says so) is not read
+      const double u = fi - sub.origin.x, v = fj - sub.origin.y;
+      const bool read = (cx != 0 || cy != 0) && u >= 0.0 && u < 4096.0 && v >= 0.0 && v < 4096.0;
+      s_tab.word[q] = read ? (int)u << 16 | (int)v << 4 | (cx + 1) << 2 | (cy + 1) : -1;
+    }
+    __syncthreads();
+  }
+  for (int e0 = tid - lane; e0 < ns * E; e0 += T) {   // whole waves
+    const int e = e0 + lane, i = min(e / E, ns - 1), r = (e - i * E) / J.PW;
+    bool used = false;
+    if (e < ns * E) {
+      if constexpr (SAMPLES)
+        used = plan_table_entry<MULTI>(J, m, E, kk0 + i, e - i * E, s_inv, s_sub[i], s_tab,
+                                       i * (p + 2) * (p + 2), s_sub[i].x0, s_sub[i].y0);
+      else
+        used = plan_weight_entry<MULTI>(J, m, E, kk0 + i, e - i * E, s_inv, s_sub[i]);
+    }
+    // the first and the last used entry of each subaperture in the wave (entries
+    // run down the patch rows)
+    for (int k = e0 / E; k < ns && k * E < e0 + 64; ++k) {
+      const unsigned long long b = __ballot(used && i == k);
+      if (b == 0) continue;
+      if (lane == __ffsll(b) - 1) atomicMin(&s_sub[k].lo, r);
+      if (lane == 63 - __clzll(b)) atomicMax(&s_sub[k].hi, r + 1);
+    }
+  }
   __syncthreads();
-  const int kk = kk0 + threadIdx.x;
-  if (kk < J.nv && s_lo[threadIdx.x] != INT_MAX) {
-    atomicMin(&J.hrows[kk].x, s_lo[threadIdx.x]);
-    atomicMax(&J.hrows[kk].y, s_hi[threadIdx.x]);
+  if (tid < ns) {
+    J.origin[kk0 + tid] = s_sub[tid].origin;
+    J.hrows[kk0 + tid] = make_int2(s_sub[tid].lo, s_sub[tid].hi);
   }
-}
-
-__device__ int find_valid(const int32_t* __restrict__ valid, int nv, int k) {
-  int lo = 0, hi = nv - 1;
-  while (lo <= hi) {
-    const int mid = (lo + hi) >> 1;
-    const int vm = valid[mid];
-    if (vm == k) return mid;
-    if (vm < k) lo = mid + 1; else hi = mid - 1;
-  }
-  return -1;
 }
 
 // One workgroup per tile: the IF rows its patches touch, each trimmed to the
@@ -663,31 +773,52 @@ __global__ __launch_bounds__(256) void plan_rows_kernel(PlanJob one,
   const int t = blockIdx.x;
   if (t >= J.n_tiles) return;
   const int NS = J.NSLOT;
+  // the valid subapertures of the tile: a wave per row of it finds where the
+  // row's run starts in the (ascending) valid list
+  __shared__ int s_kk[MAX_SLOTS], s_bits, s_oob;
+  const int tid = threadIdx.x, lane = tid & 63;
+  for (int s = tid; s < min(NS, MAX_SLOTS); s += blockDim.x) s_kk[s] = -1;
+  if (tid == 0) s_bits = s_oob = 0;
+  __syncthreads();
+  for (int ty = tid >> 6; ty < J.TY; ty += blockDim.x >> 6) {
+    const int u0 = (t % J.n_tiles_x) * J.TX, v = (t / J.n_tiles_x) * J.TY + ty;
+    if (v >= J.n_sub_y) break;
+    const int k0 = v * J.n_sub_x + u0, nu = min(J.TX, J.n_sub_x - u0);
+    const int lo = first_at_least(J.valid, J.nv, k0, lane);
+    for (int j = lo + lane; j < min(J.nv, lo + nu); j += 64) {
+      const int u = J.valid[j] - k0;
+      if (u < nu && ty * J.TX + u < MAX_SLOTS) s_kk[ty * J.TX + u] = j;
+    }
+  }
+  __syncthreads();
   build_tile_rows(
       t, NS, J.PW, J.BHmax, J.cap_floats,
       [&](int s, int2& o, int2& hr) {
         // the valid subaperture (if any) slot s of tile t holds, kept for the
         // stream kernel
-        const int u = (t % J.n_tiles_x) * J.TX + s % J.TX;
-        const int v = (t / J.n_tiles_x) * J.TY + s / J.TX;
-        int kk = -1;
-        if (u < J.n_sub_x && v < J.n_sub_y) kk = find_valid(J.valid, J.nv, v * J.n_sub_x + u);
+        const int kk = s_kk[s];
         J.slot_kk[(size_t)t * NS + s] = kk;
         o = make_int2(0, 0);
         hr = make_int2(0, 0);
         if (kk >= 0) {
           o = J.origin[kk];
           hr = J.hrows[kk];
+          const int2 f = J.info[kk];
+          if (f.x != 0) atomicOr(&s_bits, f.x);
+          if (f.y != 0) atomicAdd(&s_oob, f.y);
         }
       },
       J.rows, J.tile_info, J.status);
+  __syncthreads();
+  if (tid == 0 && s_bits != 0) atomicOr(J.status, s_bits);
+  if (tid == 0 && s_oob != 0) atomicAdd(J.status + 2, s_oob);
 }
 
 // Shared tiles of a batch: slot (pair << 20 | subaperture), the pair by its
 // position in the job table, reads that pair's plan (origins and row ranges).
 __global__ __launch_bounds__(256) void plan_rows_shared_kernel(
-    const PlanJob* __restrict__ jobs, const int* __restrict__ jslots, int n_jt, int NS, int PW,
-    int BHmax, int cap_floats, int2* rows_out, int4* tile_info, int* status) {
+    const PlanJob* __restrict__ jobs, int n_jobs, const int* __restrict__ jslots, int n_jt, int NS,
+    int PW, int BHmax, int cap_floats, int2* rows_out, int4* tile_info, int* status) {
   const int t = blockIdx.x;
   if (t >= n_jt) return;
   build_tile_rows(
@@ -700,6 +831,11 @@ __global__ __launch_bounds__(256) void plan_rows_shared_kernel(
           const PlanJob& J = jobs[e >> 20];
           o = J.origin[e & 0xFFFFF];
           hr = J.hrows[e & 0xFFFFF];
+          if (e >> 20 < n_jobs) {   // planned with this launch
+            const int2 f = J.info[e & 0xFFFFF];
+            if (f.x != 0) atomicOr(J.status, f.x);
+            if (f.y != 0) atomicAdd(J.status + 2, f.y);
+          }
         }
       },
       rows_out, tile_info, status, true);
@@ -708,21 +844,6 @@ __global__ __launch_bounds__(256) void plan_rows_shared_kernel(
 __global__ void zero_ints_kernel(int* __restrict__ p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
-}
-
-// A single plan's status words and the counters of the stream launch that
-// follows it, in the plan's first kernel launch.
-__global__ void zero_plan_kernel(int* __restrict__ status, int* __restrict__ counters,
-                                 int n_counters) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < 16) status[i] = 0;
-  if (i < n_counters) counters[i] = 0;
-}
-
-__global__ void zero_job_status_kernel(const PlanJob* __restrict__ jobs, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n)
-    for (int k = 0; k < 16; ++k) jobs[i].status[k] = 0;
 }
 
 // The streaming kernel (im_stream_kernel) and its variant record live in
@@ -794,8 +915,8 @@ struct Dims {
 };
 
 struct WsLayout {
-  size_t status, counters, scratch, origin, hrows, inv2nk, weights, slot_kk, tile_info, rows,
-      partials, core, ceff, submask, total;
+  size_t status, counters, scratch, origin, hrows, info, weights, slot_kk, tile_info, rows,
+      partials, core, ceff, total;
 };
 
 constexpr int MAX_PLANES = 5;
@@ -1039,7 +1160,7 @@ WsLayout layout(const synim_wfs& w, const Dims& d, int planes, bool repair = fal
   L.scratch = take(64 * sizeof(float));
   L.origin = take(nv * sizeof(int2));
   L.hrows = take(nv * sizeof(int2));
-  L.inv2nk = take(nv * sizeof(double));
+  L.info = take(nv * sizeof(int2));
   L.weights = take((size_t)planes * nv * 2 * d.PH * d.PW * sizeof(float));
   L.slot_kk = take((size_t)d.n_tiles * d.NSLOT * sizeof(int));
   L.tile_info = take((size_t)d.n_tiles * sizeof(int4));
@@ -1048,7 +1169,6 @@ WsLayout layout(const synim_wfs& w, const Dims& d, int planes, bool repair = fal
   const size_t rw = (size_t)sample_window(w.p, true);
   L.core = take(repair ? (size_t)(w.n_sub_x * w.p + 2) * (w.n_sub_y * w.p + 2) : 0);
   L.ceff = take(repair ? nv * rw * rw * 2 * sizeof(double) : 0);
-  L.submask = take(nv * sizeof(unsigned long long));
   L.total = off;
   return L;
 }
@@ -1062,7 +1182,7 @@ struct Plan {
   float* scratch() const { return reinterpret_cast<float*>(ws + L.scratch); }
   int2* origin() const { return reinterpret_cast<int2*>(ws + L.origin); }
   int2* hrows() const { return reinterpret_cast<int2*>(ws + L.hrows); }
-  double* inv2nk() const { return reinterpret_cast<double*>(ws + L.inv2nk); }
+  int2* info() const { return reinterpret_cast<int2*>(ws + L.info); }
   float* weights() const { return reinterpret_cast<float*>(ws + L.weights); }
   int* slot_kk() const { return reinterpret_cast<int*>(ws + L.slot_kk); }
   int4* tile_info() const { return reinterpret_cast<int4*>(ws + L.tile_info); }
@@ -1070,9 +1190,6 @@ struct Plan {
   double* partials() const { return reinterpret_cast<double*>(ws + L.partials); }
   uint8_t* core() const { return reinterpret_cast<uint8_t*>(ws + L.core); }
   double* ceff() const { return reinterpret_cast<double*>(ws + L.ceff); }
-  unsigned long long* submask() const {
-    return reinterpret_cast<unsigned long long*>(ws + L.submask);
-  }
 };
 
 // Largest workspace any candidate configuration of this geometry needs, so a
@@ -1145,14 +1262,13 @@ PlanJob make_job(const synim_wfs& w, const MapD& m, const MapD* m_dev, const Map
   J.W_in = W_in;
   J.origin = P.origin();
   J.hrows = P.hrows();
-  J.inv2nk = P.inv2nk();
+  J.info = P.info();
   J.weights = P.weights();
   J.slot_kk = P.slot_kk();
   J.tile_info = P.tile_info();
   J.rows = P.rows();
   J.status = P.status();
   J.counters = P.counters();
-  J.submask = w.p <= 8 ? P.submask() : nullptr;
   const double det = m.a00 * m.a11 - m.a01 * m.a10;
   J.minv = MapD{m.a11 / det, -m.a01 / det, -m.a10 / det, m.a00 / det, 0, 0};
   return J;
@@ -1160,8 +1276,8 @@ PlanJob make_job(const synim_wfs& w, const MapD& m, const MapD* m_dev, const Map
 
 template <bool TABLE>
 int enqueue_plan_kernels(const PlanJob& one, const PlanJob* jobs_dev, int n, int max_nv,
-                         int max_e, int max_tiles, int planes, hipStream_t st,
-                         bool tiles) {
+                         int max_e, int max_tiles, int max_p, int planes, hipStream_t st,
+                         bool tiles, ClearWords clear) {
   if (!TABLE && one.dm_mask) {
     // edge repair (single builds): strict core, then the effective coefficients
     const long cells = (long)(one.n_sub_x * one.p + 2) * (one.n_sub_y * one.p + 2);
@@ -1177,19 +1293,19 @@ int enqueue_plan_kernels(const PlanJob& one, const PlanJob* jobs_dev, int n, int
   for (int j0 = 0; j0 < n; j0 += 65535) {
     const int nj = std::min(65535, n - j0);
     const PlanJob* jt = TABLE ? jobs_dev + j0 : nullptr;
-    hipLaunchKernelGGL(plan_subaps_kernel<TABLE>,
-                       dim3((unsigned)(((long)max_nv * 64 + PLAN_SUBAPS_BLOCK - 1) / PLAN_SUBAPS_BLOCK),
-                            nj),
-                       dim3(PLAN_SUBAPS_BLOCK), 0, st, one, jt);
-    SYNIM_HIP_TRY(hipGetLastError());
-    const long nthr = (long)max_nv * max_e;
-    const dim3 wgrid((unsigned)((nthr + PLAN_WEIGHTS_BLOCK - 1) / PLAN_WEIGHTS_BLOCK), nj);
-    if (planes > 1)
-      hipLaunchKernelGGL((plan_weights_kernel<true, TABLE>), wgrid, dim3(PLAN_WEIGHTS_BLOCK), 0,
-                         st, one, jt);
-    else
-      hipLaunchKernelGGL((plan_weights_kernel<false, TABLE>), wgrid, dim3(PLAN_WEIGHTS_BLOCK), 0,
-                         st, one, jt);
+    // whole waves that a patch's entries fill in equal passes
+    const int passes = (max_e + PLAN_BLOCK - 1) / PLAN_BLOCK;
+    const int T = max_e <= PLAN_BLOCK / 2 ? PLAN_BLOCK
+                                          : ((max_e + passes - 1) / passes + 63) / 64 * 64;
+    const int spb = std::clamp(T / max_e, 1, PLAN_SUBS);
+    const dim3 wgrid((unsigned)((max_nv + spb - 1) / spb), nj);
+    const bool samples = (TABLE || (!one.dm_mask && one.engine == ENGINE_CD)) &&
+                         spb * (max_p + 2) * (max_p + 2) <= PLAN_SAMPLES;
+    const auto kernel = planes > 1 ? (samples ? plan_weights_kernel<true, TABLE, true>
+                                              : plan_weights_kernel<true, TABLE, false>)
+                                   : (samples ? plan_weights_kernel<false, TABLE, true>
+                                              : plan_weights_kernel<false, TABLE, false>);
+    hipLaunchKernelGGL(kernel, wgrid, dim3(T), 0, st, one, jt, spb, j0 == 0 ? clear : ClearWords{});
     SYNIM_HIP_TRY(hipGetLastError());
     if (!tiles) continue;
     hipLaunchKernelGGL(plan_rows_kernel<TABLE>, dim3(max_tiles, nj), dim3(256), 0, st, one, jt);
@@ -1201,28 +1317,23 @@ int enqueue_plan_kernels(const PlanJob& one, const PlanJob* jobs_dev, int n, int
 // Enqueue the plan kernels for `n` jobs: one job by value (jobs_dev null) or
 // a device table of n jobs (maxima give the grid extents).
 // tiles = false: origins, row ranges and weights only (the batch's shared
-// tiles replace the per-pair tile tables).
+// tiles replace the per-pair tile tables).  The first launch also clears the
+// jobs' status words and `clear` (a single job's: its stream counters).
 int enqueue_plans(const PlanJob& one, const PlanJob* jobs_dev, int n, int max_nv, int max_e,
-                  int max_tiles, int planes, hipStream_t st, bool tiles = true) {
-  if (jobs_dev) {
-    hipLaunchKernelGGL(zero_job_status_kernel, dim3((n + 255) / 256), dim3(256), 0, st, jobs_dev,
-                       n);
-  } else {
-    hipLaunchKernelGGL(zero_plan_kernel, dim3((COUNTER_INTS + 255) / 256), dim3(256), 0,
-                       st, one.status, one.counters, COUNTER_INTS);
-  }
-  SYNIM_HIP_TRY(hipGetLastError());
+                  int max_tiles, int max_p, int planes, hipStream_t st, bool tiles = true,
+                  ClearWords clear = {}) {
   if (jobs_dev)
     return enqueue_plan_kernels<true>(one, jobs_dev, n, max_nv, max_e, max_tiles,
-                                      planes, st, tiles);
+                                      max_p, planes, st, tiles, clear);
+  clear = ClearWords{{one.counters, nullptr}, {COUNTER_INTS, 0}};
   return enqueue_plan_kernels<false>(one, nullptr, 1, max_nv, max_e, max_tiles,
-                                     planes, st, tiles);
+                                     max_p, planes, st, tiles, clear);
 }
 
 int enqueue_plan(const synim_wfs& w, const MapD& m, const MapD* m_dev, const Map4& dm, int planes,
                  int H_in, int W_in, const Plan& P, hipStream_t st) {
   const PlanJob J = make_job(w, m, m_dev, dm, nullptr, planes, P, H_in, W_in);
-  return enqueue_plans(J, nullptr, 1, J.nv, J.PH * J.PW, J.n_tiles, J.n_planes, st);
+  return enqueue_plans(J, nullptr, 1, J.nv, J.PH * J.PW, J.n_tiles, J.p, J.n_planes, st);
 }
 
 // Resident workgroups of a stream kernel on the current device (cached).
@@ -1641,7 +1752,7 @@ extern "C" int synim_im_build_tsum(const float* ifs, int n_act, int H_in, int W_
   // no out-of-grid count: it is defined on the central-difference samples
   PlanJob J = make_job(*wfs, m, nullptr, Map4{}, nullptr, 1, P, 0, 0);
   J.engine = ENGINE_TSUM;
-  rc = enqueue_plans(J, nullptr, 1, J.nv, J.PH * J.PW, J.n_tiles, 1, st);
+  rc = enqueue_plans(J, nullptr, 1, J.nv, J.PH * J.PW, J.n_tiles, J.p, 1, st);
   if (rc != SYNIM_OK) return rc;
   return launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);
 }
@@ -1681,7 +1792,7 @@ extern "C" int synim_im_build_repaired(const float* ifs, int n_act, int H_in, in
   J.thresh = threshold;
   J.core = P.core();
   J.ceff = P.ceff();
-  rc = enqueue_plans(J, nullptr, 1, J.nv, J.PH * J.PW, J.n_tiles, 1, st);
+  rc = enqueue_plans(J, nullptr, 1, J.nv, J.PH * J.PW, J.n_tiles, J.p, 1, st);
   if (rc != SYNIM_OK) return rc;
   return launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);
 }
@@ -1843,7 +1954,7 @@ struct synim_batch {
   size_t ws_bytes = 0;
   size_t off_maps = 0, off_pairs = 0, off_recs = 0, off_groups = 0, off_ctr = 0, off_scratch = 0;
   size_t off_jobs = 0, off_dmaps = 0;
-  int max_nv = 0, max_e = 0, max_tiles = 0;
+  int max_nv = 0, max_e = 0, max_tiles = 0, max_p = 0;
   int n_recs = 0;
   int rec_off[8] = {}, rec_cnt[8] = {}, xcd_items[8] = {};
   std::vector<SuperChunk> recs_host;   // to count the items of the first groups
@@ -2253,7 +2364,7 @@ int batch_bind(synim_batch* b, const Variant& v, hipStream_t st) {
   b->recs_host = recs;
   std::vector<PlanJob> jobs(np);
   const MapD* maps_dev = reinterpret_cast<const MapD*>(b->ws + b->off_maps);
-  b->max_nv = b->max_e = b->max_tiles = 0;
+  b->max_nv = b->max_e = b->max_tiles = b->max_p = 0;
   // jobs in group order (the order of the pair table): shared-tile slots and
   // the group prefixes of batch_enqueue index them that way
   for (int pos = 0; pos < np; ++pos) {
@@ -2266,6 +2377,7 @@ int batch_bind(synim_batch* b, const Variant& v, hipStream_t st) {
     b->max_nv = std::max(b->max_nv, jobs[pos].nv);
     b->max_e = std::max(b->max_e, jobs[pos].PH * jobs[pos].PW);
     b->max_tiles = std::max(b->max_tiles, jobs[pos].n_tiles);
+    b->max_p = std::max(b->max_p, jobs[pos].p);
   }
   SYNIM_HIP_TRY(hipMemcpyAsync(b->ws + b->off_jobs, jobs.data(), np * sizeof(PlanJob),
                                hipMemcpyHostToDevice, st));
@@ -2284,6 +2396,10 @@ int batch_bind(synim_batch* b, const Variant& v, hipStream_t st) {
                                  b->jgroups_host.size() * sizeof(int2), hipMemcpyHostToDevice,
                                  st));
   }
+  // a batch that has not run yet has nothing to report
+  for (const auto& P : b->plans)
+    SYNIM_HIP_TRY(hipMemsetAsync(P.status(), 0, 16 * sizeof(int), st));
+  if (b->shared) SYNIM_HIP_TRY(hipMemsetAsync(b->ws + b->off_jstatus, 0, 16 * sizeof(int), st));
   SYNIM_HIP_TRY(hipStreamSynchronize(st));   // the host vectors go out of scope
   return SYNIM_OK;
 }
@@ -2310,17 +2426,17 @@ int batch_enqueue(synim_batch* b, hipStream_t st, int n_groups = -1) {
     }
   }
   const PlanJob* jobs = reinterpret_cast<const PlanJob*>(b->ws + b->off_jobs);
+  int* const jstatus = reinterpret_cast<int*>(b->ws + b->off_jstatus);
+  int* const counters = reinterpret_cast<int*>(b->ws + b->off_ctr);
   int rc = enqueue_plans(PlanJob{}, jobs, np, b->max_nv, b->max_e, b->max_tiles,
-                         b->planes, st, !b->shared);
+                         b->max_p, b->planes, st, !b->shared,
+                         ClearWords{{counters, jstatus}, {8 * b->planes, b->shared ? 16 : 0}});
   if (rc != SYNIM_OK) return rc;
   StreamArgs g{};
   if (b->shared) {
-    int* jstatus = reinterpret_cast<int*>(b->ws + b->off_jstatus);
-    hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, jstatus, 16);
-    SYNIM_HIP_TRY(hipGetLastError());
     if (b->n_jt > 0) {
       hipLaunchKernelGGL(plan_rows_shared_kernel, dim3((unsigned)b->n_jt), dim3(256), 0, st, jobs,
-                         reinterpret_cast<const int*>(b->ws + b->off_jslots), b->n_jt, b->jNS,
+                         np, reinterpret_cast<const int*>(b->ws + b->off_jslots), b->n_jt, b->jNS,
                          b->var->PW, b->jBHmax, b->var->cap_floats(),
                          reinterpret_cast<int2*>(b->ws + b->off_jrows),
                          reinterpret_cast<int4*>(b->ws + b->off_jinfo), jstatus);
@@ -2344,10 +2460,8 @@ int batch_enqueue(synim_batch* b, hipStream_t st, int n_groups = -1) {
   g.one_round = 1;
   for (int x = 0; x < 8; ++x)
     if (8 * b->xcd_items[x] > b->G) g.one_round = 0;
-  g.counters = reinterpret_cast<int*>(b->ws + b->off_ctr);
+  g.counters = counters;
   g.scratch = reinterpret_cast<float*>(b->ws + b->off_scratch);
-  hipLaunchKernelGGL(zero_ints_kernel, dim3(1), dim3(64), 0, st, g.counters, 8 * b->planes);
-  SYNIM_HIP_TRY(hipGetLastError());
   StreamFn fn = pick_fn(*b->var, b->vec4, false, true);
   hipLaunchKernelGGL(fn, dim3((unsigned)b->G, 1, b->planes), dim3(b->var->BLOCK), 0, st, g);
   SYNIM_HIP_TRY(hipGetLastError());

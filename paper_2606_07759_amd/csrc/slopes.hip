@@ -27,8 +27,7 @@ struct __attribute__((packed, aligned(4))) Quad {
 // row; the per-subaperture sums then add those column sums in column order (a
 // fixed order, so results are bit-reproducible).  The pupil of a thread's columns
 // is kept as bits over the run of maps where the group has at most 64 pixel rows.
-// A wave finds where a row's subapertures start in the valid list with 64-way
-// steps (three for 4632 entries).  Each XCD takes all blocks of a map before its
+// Each XCD takes all blocks of a map before its
 // next, so that shared rows and lines meet in its L2.  Now 0.33.
 __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict__ phase, int n,
                                                         const int32_t* __restrict__ valid,
@@ -60,17 +59,7 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
   __syncthreads();
   for (int v = v0 + wave; v < v_end; v += T >> 6) {
     const int k0 = v * n_sub_x + u0;
-    // first entry >= k0 in [lo, hi): every lane tests one of 64 spread entries
-    int lo = 0, hi = nv;
-    while (lo < hi) {
-      const int step = (hi - lo + 63) / 64;
-      const int at = lo + lane * step;
-      const unsigned long long below = __ballot(at < hi && valid[min(at, nv - 1)] < k0);
-      const int c = __popcll(below);   // entries are ascending: the first c lanes
-      if (c == 0) break;
-      lo = lo + (c - 1) * step + 1;
-      hi = min(hi, lo - 1 + step);
-    }
+    const int lo = first_at_least(valid, nv, k0, lane);
     for (int j = lo + lane; j < min(nv, lo + nu); j += 64) {
       const int u = valid[j] - k0;
       if (u < nu) s_kk[(v - v0) * nu + u] = j;
