@@ -1431,12 +1431,35 @@ PairDesc pair_desc(const Plan& P, const float* ifs, int n_act, int H_in, int W_i
   return pd;
 }
 
-int launch_stream(const Plan& P, const float* ifs, int n_act, int H_in, int W_in, int nv,
-                  int plane0, int nplanes, float* out, const float* grad, hipStream_t st,
-                  int* grid_out = nullptr) {
+// Whether every 16-byte vector the plan's rows stage lies in one IF row or outside
+// the grid.  Vectors start at columns that are multiples of 4, so on a grid whose
+// rows are no multiple of 4 long only the row's last vector does not, and the
+// rows of a sensor that stays left of it (by its largest patch corner, found at
+// one of its corner subapertures) take the 16-byte DMA: it reads from any 4-byte
+// address.  (A stack of edge-repaired actuators of 293^2: 370 us with 4-byte DMA, a
+// quarter of the bytes in flight, now 161.)
+bool whole_vectors(const synim_wfs& w, const synim_affine& A, int pad, int PW, int W_in) {
+  if (W_in % 4 == 0) return true;
+  const MapD m = to_map(A);
+  const int W = w.n_sub_x * w.p, H = w.n_sub_y * w.p;
+  double most = -1e300;
+  for (const int x0 : {0, W - w.p})
+    for (const int y0 : {0, H - w.p}) {
+      const int x = m.a00 >= 0 ? std::max(x0 - 1 - pad, -1) : std::min(x0 + w.p + pad, W);
+      const int y = m.a01 >= 0 ? std::max(y0 - 1 - pad, -1) : std::min(y0 + w.p + pad, H);
+      most = std::max(most, m.a00 * x + m.a01 * y + m.b0);
+    }
+  return most < 1e6 && ((long)std::floor(most + 1e-3) + PW + 3) / 4 * 4 <= W_in;
+}
+
+int launch_stream(const Plan& P, const synim_wfs& w, const synim_affine& A, const float* ifs,
+                  int n_act, int H_in, int W_in, int plane0, int nplanes, float* out,
+                  const float* grad, hipStream_t st, int* grid_out = nullptr, int pad = 0) {
+  const int nv = w.n_valid;
   const Dims& d = P.d;
   const Variant& v = *d.var;
-  const bool vec4 = (W_in % 4 == 0) && ((reinterpret_cast<uintptr_t>(ifs) & 15) == 0);
+  const bool vec4 = (reinterpret_cast<uintptr_t>(ifs) & 3) == 0 &&
+                    whole_vectors(w, A, pad, d.PW, W_in);
   if ((long)H_in * W_in * 4 > INT_MAX) return SYNIM_E_SHAPE;   // 32-bit DMA offsets
   StreamFn fn = pick_fn(v, vec4, grad != nullptr);
   int G = persistent_grid(fn, v.BLOCK);
@@ -1527,12 +1550,12 @@ extern "C" int synim_im_autotune(const float* ifs, int n_act, int H_in, int W_in
     P.d = cand[c];
     rc = build_plan_with(*wfs, *A, nullptr, 1, H_in, W_in, ws, ws_bytes, st, &P);
     if (rc != SYNIM_OK) break;
-    rc = launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);   // warm
+    rc = launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 0, 1, im, nullptr, st);   // warm
     if (rc != SYNIM_OK) break;
     const int reps = 3;
     if (hipEventRecord(e0, st) != hipSuccess) { rc = SYNIM_E_HIP; break; }
     for (int r = 0; r < reps && rc == SYNIM_OK; ++r)
-      rc = launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);
+      rc = launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 0, 1, im, nullptr, st);
     if (rc != SYNIM_OK) break;
     float ms = 0.f;
     if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
@@ -1729,7 +1752,7 @@ extern "C" int synim_im_build(const float* ifs, int n_act, int H_in, int W_in,
   Plan P{};
   rc = build_plan(*wfs, *A, nullptr, 1, H_in, W_in, ws, ws_bytes, st, &P);
   if (rc != SYNIM_OK) return rc;
-  return launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);
+  return launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 0, 1, im, nullptr, st);
 }
 
 // ------------------------------------------------- telescoping-sum engine
@@ -1754,7 +1777,7 @@ extern "C" int synim_im_build_tsum(const float* ifs, int n_act, int H_in, int W_
   J.engine = ENGINE_TSUM;
   rc = enqueue_plans(J, nullptr, 1, J.nv, J.PH * J.PW, J.n_tiles, J.p, 1, st);
   if (rc != SYNIM_OK) return rc;
-  return launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);
+  return launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 0, 1, im, nullptr, st);
 }
 
 // ------------------------------------------------------- edge-repaired build
@@ -1794,7 +1817,8 @@ extern "C" int synim_im_build_repaired(const float* ifs, int n_act, int H_in, in
   J.ceff = P.ceff();
   rc = enqueue_plans(J, nullptr, 1, J.nv, J.PH * J.PW, J.n_tiles, J.p, 1, st);
   if (rc != SYNIM_OK) return rc;
-  return launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);
+  return launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 0, 1, im, nullptr, st, nullptr,
+                       REPAIR_PAD);
 }
 
 // ------------------------------------------------- build without allocation
@@ -1842,7 +1866,7 @@ extern "C" int synim_im_build_noalloc(const float* ifs, int n_act, int H_in, int
   hipStream_t st = (hipStream_t)stream;
   rc = build_plan_with(*wfs, *A, nullptr, 1, H_in, W_in, ws, kNoallocBytes, st, &P);
   if (rc != SYNIM_OK) return rc;
-  return launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);
+  return launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 0, 1, im, nullptr, st);
 }
 
 extern "C" int synim_im_jacobian(const float* ifs, int n_act, int H_in, int W_in,
@@ -1857,10 +1881,10 @@ extern "C" int synim_im_jacobian(const float* ifs, int n_act, int H_in, int W_in
   rc = build_plan(*wfs, *A, dA, 5, H_in, W_in, ws, ws_bytes, st, &P);
   if (rc != SYNIM_OK) return rc;
   if (im) {
-    rc = launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 0, 1, im, nullptr, st);
+    rc = launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 0, 1, im, nullptr, st);
     if (rc != SYNIM_OK) return rc;
   }
-  return launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 1, 4, dim, nullptr, st);
+  return launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 1, 4, dim, nullptr, st);
 }
 
 extern "C" int synim_im_vjp(const float* ifs, int n_act, int H_in, int W_in,
@@ -1875,7 +1899,7 @@ extern "C" int synim_im_vjp(const float* ifs, int n_act, int H_in, int W_in,
   rc = build_plan(*wfs, *A, dA, 5, H_in, W_in, ws, ws_bytes, st, &P);
   if (rc != SYNIM_OK) return rc;
   int G = 0;
-  rc = launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, 1, 4, nullptr, grad_im, st, &G);
+  rc = launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, 1, 4, nullptr, grad_im, st, &G);
   if (rc != SYNIM_OK) return rc;
   hipLaunchKernelGGL(vjp_finalize_kernel, dim3(4), dim3(256), 0, st, P.partials(), G,
                      grad_theta);
@@ -1909,7 +1933,7 @@ extern "C" int synim_im_apply(const float* ifs, int n_act, int H_in, int W_in,
   P.L = layout(*wfs, P.d, planes);
   if (ws_bytes < P.L.total) return SYNIM_E_WORKSPACE;
   P.ws = static_cast<char*>(const_cast<void*>(ws));
-  return launch_stream(P, ifs, n_act, H_in, W_in, wfs->n_valid, plane, 1, out, nullptr,
+  return launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, plane, 1, out, nullptr,
                        (hipStream_t)stream);
 }
 
@@ -2301,7 +2325,7 @@ int batch_bind(synim_batch* b, const Variant& v, hipStream_t st) {
   for (auto& P : b->plans) P.ws = b->ws + reinterpret_cast<size_t>(P.ws);
   b->vec4 = true;
   for (const auto& d : b->dms)
-    if (d.W_in % 4 != 0 || (reinterpret_cast<uintptr_t>(d.ifs) & 15) != 0) b->vec4 = false;
+    if (d.W_in % 4 != 0 || (reinterpret_cast<uintptr_t>(d.ifs) & 3) != 0) b->vec4 = false;
   StreamFn fn = pick_fn(v, b->vec4, false, true);
   b->G = persistent_grid(fn, v.BLOCK);
   if (b->G < 0) return SYNIM_E_HIP;
