@@ -212,16 +212,17 @@ __global__ __launch_bounds__(256) void proj_window_kernel(SampleArgs g, int n_rb
 // ---------------------------------------------------------------- FP64 GEMM
 // C[m][n] = alpha sum_k X(k, m) Y(k, n) + beta C[m][n], X(k, m) = X[k sxk + m sxm],
 // Y(k, n) = Y[k syk + n syn], C row-major with ldc.  One workgroup of 256
-// threads per (32 BI) x (32 BJ) tile of C; each wave owns a (16 BI) x (16 BJ)
-// quarter as BI x BJ blocks of v_mfma_f64_16x16x4f64 (lane l feeds
-// A[l%16][l/16] and B[l/16][l%16] and holds D[4r + l/16][l%16], r = 0..3).  K
-// advances in chunks of 16 through two LDS buffers: the next chunk's global
-// loads are in flight while the current one feeds the matrix cores.  lower:
-// only tiles with some m >= n (a symmetric result's lower triangle) are
-// computed.  Two shapes: 128 x 128 (two workgroups per CU) for small products,
-// 256 x 128 (one per CU, each wave's 8 x 4 accumulator blocks in the
-// accumulation registers) for large ones, which halves the operand bytes each
-// flop needs from L2 along m.
+// threads per 128 x 128 tile of C; each wave owns a 64 x 64 quarter as 4 x 4
+// blocks of v_mfma_f64_16x16x4f64 (lane l feeds A[l%16][l/16] and B[l/16][l%16]
+// and holds D[4r + l/16][l%16], r = 0..3).  K advances in chunks of 16 through two
+// LDS buffers: the next chunk's global loads are in flight while the current one
+// feeds the matrix cores, and a second workgroup of the CU covers the barriers and
+// the pass over C.  An operand is read along its unit stride from one pointer a
+// thread; XCD x takes the tile rows x, x + 8, ..., so that a row's operand stays
+// in its L2.  lower: only tiles with some m >= n (a symmetric result's lower
+// triangle) are computed.  An update of 7915 x 4107 over 256 columns: 0.62 ms
+// with 256 x 128 tiles of one workgroup a CU, 0.52 with these tiles, now 0.43 with
+// the addresses out of the loop and C read ahead.
 constexpr int GK = 16, GPAD = 2;
 
 struct GemmArgs {
@@ -236,119 +237,127 @@ struct GemmArgs {
   int lower;
 };
 
-// (kk, mm) of element q of this thread in a GK x T chunk, reading along the
-// operand's unit stride
-template <int T>
-__device__ __forceinline__ void gemm_elem(long sk, int tid, int q, int& kk, int& mm) {
-  const int e = tid + 256 * q;
-  if (sk == 1) {
-    kk = e % GK;
-    mm = e / GK;
-  } else {
-    kk = e / T;
-    mm = e % T;
-  }
-}
+constexpr int GT = 128;          // tile side
+constexpr int GQ = GK * GT / 256;   // elements of an operand chunk a thread moves
 
-template <int T>
-__device__ __forceinline__ void gemm_fetch(const double* P, long sk, long sm, int k0, int m0,
-                                           int K, int M, int tid, double (&r)[GK * T / 256]) {
+// One thread's share of an operand's chunks: elements q = 0.. GQ - 1 at rows
+// k = k0 + kk + q dk and columns mm + q dm of the tile, read along the operand's
+// unit stride.
+struct GOperand {
+  const double* p;   // element 0 of the next chunk
+  long step, chunk;  // to the next element, to the next chunk
+  int kk, mm, dk, dm, left;   // left: columns of the operand from the tile's first
+  __device__ __forceinline__ GOperand(const double* base, long sk, long sm, int m0, int M, int tid) {
+    if (sk == 1) {
+      kk = tid % GK;
+      mm = tid / GK;
+      dk = 0;
+      dm = 256 / GK;
+    } else {
+      kk = tid / GT;
+      mm = tid % GT;
+      dk = 256 / GT;
+      dm = 0;
+    }
+    p = base + (long)kk * sk + (long)(m0 + mm) * sm;
+    step = dk * sk + dm * sm;
+    chunk = GK * sk;
+    left = M - m0;
+  }
+  // rows: of the chunk that exist
+  __device__ __forceinline__ void fetch(int rows, double (&r)[GQ]) {
 #pragma unroll
-  for (int q = 0; q < GK * T / 256; ++q) {
-    int kk, mm;
-    gemm_elem<T>(sk, tid, q, kk, mm);
-    const int k = k0 + kk, m = m0 + mm;
-    r[q] = (k < K && m < M) ? P[(long)k * sk + (long)m * sm] : 0.0;
+    for (int q = 0; q < GQ; ++q)
+      r[q] = kk + q * dk < rows && mm + q * dm < left ? p[q * step] : 0.0;
+    p += chunk;
   }
-}
-
-template <int T>
-__device__ __forceinline__ void gemm_put(long sk, int tid, const double (&r)[GK * T / 256],
-                                         double (*S)[T + GPAD]) {
+  __device__ __forceinline__ void put(const double (&r)[GQ], double (*S)[GT + GPAD]) const {
 #pragma unroll
-  for (int q = 0; q < GK * T / 256; ++q) {
-    int kk, mm;
-    gemm_elem<T>(sk, tid, q, kk, mm);
-    S[kk][mm] = r[q];
+    for (int q = 0; q < GQ; ++q) S[kk + q * dk][mm + q * dm] = r[q];
   }
-}
+};
 
-template <int BI, int BJ>
-__global__ __launch_bounds__(256) void gemm_f64_kernel(GemmArgs g) {
-  constexpr int TM = 32 * BI, TN = 32 * BJ;
-  const int m0 = blockIdx.y * TM, n0 = blockIdx.x * TN;
-  if (g.lower && m0 + TM - 1 < n0) return;   // tile wholly above the diagonal
-  __shared__ double Xs[2][GK][TM + GPAD], Ys[2][GK][TN + GPAD];
+__global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g, int nt) {
+  const int row = (int)(blockIdx.x >> 3) / nt * 8 + (int)(blockIdx.x & 7);
+  const int m0 = row * GT, n0 = (int)(blockIdx.x >> 3) % nt * GT;
+  if (m0 >= g.M || (g.lower && m0 + GT - 1 < n0)) return;   // tile wholly above the diagonal
+  __shared__ double Xs[2][GK][GT + GPAD], Ys[2][GK][GT + GPAD];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * 16 * BI, wn = (wave & 1) * 16 * BJ;
-  d4 acc[BI][BJ];
+  const int wm = (wave >> 1) * 64, wn = (wave & 1) * 64;
+  d4 acc[4][4];
 #pragma unroll
-  for (int i = 0; i < BI; ++i)
+  for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
-  double rx[GK * TM / 256], ry[GK * TN / 256];
-  gemm_fetch<TM>(g.X, g.sxk, g.sxm, 0, m0, g.K, g.M, tid, rx);
-  gemm_fetch<TN>(g.Y, g.syk, g.syn, 0, n0, g.K, g.N, tid, ry);
-  gemm_put<TM>(g.sxk, tid, rx, Xs[0]);
-  gemm_put<TN>(g.syk, tid, ry, Ys[0]);
+    for (int j = 0; j < 4; ++j) acc[i][j] = d4{0.0, 0.0, 0.0, 0.0};
+  GOperand X(g.X, g.sxk, g.sxm, m0, g.M, tid), Y(g.Y, g.syk, g.syn, n0, g.N, tid);
+  double rx[GQ], ry[GQ];
+  X.fetch(g.K, rx);
+  Y.fetch(g.K, ry);
+  X.put(rx, Xs[0]);
+  Y.put(ry, Ys[0]);
   __syncthreads();
   const int nk = (g.K + GK - 1) / GK;
   for (int c = 0; c < nk; ++c) {
     const int buf = c & 1;
     const bool more = c + 1 < nk;
     if (more) {
-      gemm_fetch<TM>(g.X, g.sxk, g.sxm, (c + 1) * GK, m0, g.K, g.M, tid, rx);
-      gemm_fetch<TN>(g.Y, g.syk, g.syn, (c + 1) * GK, n0, g.K, g.N, tid, ry);
+      X.fetch(g.K - (c + 1) * GK, rx);
+      Y.fetch(g.K - (c + 1) * GK, ry);
     }
-    // the large shape keeps one k-step's operands live at a time (its
-    // accumulators fill the accumulation registers)
-#pragma unroll(BI * BJ > 16 ? 1 : GK / 4)
+#pragma unroll
     for (int s = 0; s < GK / 4; ++s) {
       const int kr = 4 * s + (lane >> 4);
-      double a[BI], b[BJ];
+      double a[4], b[4];
 #pragma unroll
-      for (int i = 0; i < BI; ++i) a[i] = Xs[buf][kr][wm + 16 * i + (lane & 15)];
+      for (int i = 0; i < 4; ++i) a[i] = Xs[buf][kr][wm + 16 * i + (lane & 15)];
 #pragma unroll
-      for (int j = 0; j < BJ; ++j) b[j] = Ys[buf][kr][wn + 16 * j + (lane & 15)];
+      for (int j = 0; j < 4; ++j) b[j] = Ys[buf][kr][wn + 16 * j + (lane & 15)];
 #pragma unroll
-      for (int i = 0; i < BI; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int j = 0; j < BJ; ++j)
+        for (int j = 0; j < 4; ++j)
           acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
     }
     if (more) {
       // the other buffer was last read in iteration c - 1, before its closing barrier
-      gemm_put<TM>(g.sxk, tid, rx, Xs[buf ^ 1]);
-      gemm_put<TN>(g.syk, tid, ry, Ys[buf ^ 1]);
+      X.put(rx, Xs[buf ^ 1]);
+      Y.put(ry, Ys[buf ^ 1]);
     }
     __syncthreads();
   }
+  // (a block row's elements of C are all read before the first is written: one
+  // by one, each read would wait for the write before it, which may be the same
+  // memory for all the compiler knows)
 #pragma unroll
-  for (int i = 0; i < BI; ++i)
+  for (int i = 0; i < 4; ++i) {
+    double* at[4];
+    bool on[4][4];
+    double old[4][4];
 #pragma unroll
-    for (int j = 0; j < BJ; ++j)
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + wm + 16 * i + 4 * r + (lane >> 4);
+      at[r] = g.C + (long)m * g.ldc + n0 + wn + (lane & 15);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + 16 * i + 4 * r + (lane >> 4);
+      for (int j = 0; j < 4; ++j) {
         const int n = n0 + wn + 16 * j + (lane & 15);
-        if (m < g.M && n < g.N && (!g.lower || m >= n)) {
-          double* cp = g.C + (long)m * g.ldc + n;
-          *cp = g.alpha * acc[i][j][r] + (g.beta == 0.0 ? 0.0 : g.beta * *cp);
-        }
+        on[r][j] = m < g.M && n < g.N && (!g.lower || m >= n);
+        old[r][j] = on[r][j] && g.beta != 0.0 ? at[r][16 * j] : 0.0;
       }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (on[r][j])
+          at[r][16 * j] = g.alpha * acc[i][j][r] + (g.beta == 0.0 ? 0.0 : g.beta * old[r][j]);
+  }
 }
 
 int gemm(const GemmArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return SYNIM_OK;
-  // 256 x 128 tiles once there are enough of them to fill the CUs
-  const long big_tiles = (long)((a.M + 255) / 256) * ((a.N + 127) / 128);
-  if (big_tiles >= 256) {
-    const dim3 grid((unsigned)((a.N + 127) / 128), (unsigned)((a.M + 255) / 256));
-    hipLaunchKernelGGL((gemm_f64_kernel<8, 4>), grid, dim3(256), 0, st, a);
-  } else {
-    const dim3 grid((unsigned)((a.N + 127) / 128), (unsigned)((a.M + 127) / 128));
-    hipLaunchKernelGGL((gemm_f64_kernel<4, 4>), grid, dim3(256), 0, st, a);
-  }
+  const long nt = (a.N + GT - 1) / GT, mt = ((a.M + GT - 1) / GT + 7) / 8 * 8;
+  if (nt * mt > INT_MAX) return SYNIM_E_SHAPE;
+  hipLaunchKernelGGL(gemm_f64_kernel, dim3((unsigned)(nt * mt)), dim3(256), 0, st, a, (int)nt);
   SYNIM_HIP_TRY(hipGetLastError());
   return SYNIM_OK;
 }
@@ -617,11 +626,8 @@ constexpr int CB = 64;
 // One workgroup: the nb x nb diagonal block at (k, k), unblocked, in LDS.  A
 // pivot that is not positive sets *status (the matrix is not positive
 // definite) and the block is left as it is.
-// Linv (nullable): also writes the block's inverse L_kk^-1 there (CB x CB,
-// row-major, zero above the diagonal and outside nb x nb), each column by
-// forward substitution against the unit vector.
 __global__ __launch_bounds__(256) void potrf_diag_kernel(double* A, long ld, int k, int nb,
-                                                         int* status, double* Linv = nullptr) {
+                                                         int* status) {
   __shared__ double L[CB][CB + 1];
   __shared__ int bad;
   const int tid = threadIdx.x;
@@ -654,21 +660,6 @@ __global__ __launch_bounds__(256) void potrf_diag_kernel(double* A, long ld, int
     if (j <= i) A[(long)(k + i) * ld + k + j] = L[i][j];
   }
   if (tid == 0 && bad) atomicOr(status, 1);
-  if (Linv == nullptr) return;
-  __shared__ double X[CB][CB + 1];
-  for (int e = tid; e < CB * (CB + 1); e += 256) (&X[0][0])[e] = 0.0;
-  __syncthreads();
-  if (tid < nb) {
-    // column c = tid of L^-1: x_r = (delta_rc - sum_{c <= q < r} L[r][q] x_q) / L[r][r]
-    const int c = tid;
-    for (int r = c; r < nb; ++r) {
-      double v = r == c ? 1.0 : 0.0;
-      for (int q = c; q < r; ++q) v -= L[r][q] * X[q][c];
-      X[r][c] = v / L[r][r];
-    }
-  }
-  __syncthreads();
-  for (int e = tid; e < CB * CB; e += 256) Linv[e] = X[e / CB][e % CB];
 }
 
 // Panel rows i in [r0, n): row i of block column k becomes x with
@@ -819,141 +810,414 @@ int potrs(const double* L, int n, long ld, double* B, int m, long ldb, hipStream
   return SYNIM_OK;
 }
 
-// dst[r][c] = src[r][c] for r < rows, c < cols (row-major, leading dimensions
-// lds, ldd).
-__global__ __launch_bounds__(256) void copy2d_kernel(const double* __restrict__ src, long lds,
-                                                     double* __restrict__ dst, long ldd,
-                                                     int rows, int cols) {
-  const long e = (long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= (long)rows * cols) return;
-  const int r = (int)(e / cols), c = (int)(e - (long)r * cols);
-  dst[(long)r * ldd + c] = src[(long)r * lds + c];
+// ------------------------------------- factorisation and solves in two levels
+// Blocked Cholesky and solves with the diagonal blocks inverted, for a matrix of
+// thousands of columns: blocks of CB within panels of CW columns.  Within a panel
+// two launches a block: its diagonal block is brought up to date, factored and
+// inverted by one workgroup, then each workgroup brings 64 rows below it up to
+// date and multiplies them by L_kk^-T, in place.  The rest of the matrix is
+// updated once per panel, so that it is read and written n / CW times and not
+// n / CB (both bound by that traffic and by launches: blocks of 64 alone took 87 ms
+// for n = 8171 and 4107 right-hand sides, 16 of them in the diagonal blocks, now
+// 29).  Linv: ceil(n / CB) blocks of CB x CB doubles.
+constexpr int CW = 4 * CB;
+constexpr int CPAD = 2;
+typedef double CBlock[CB][CB + CPAD];
+
+// 16 elements a thread of a 64 x 64 block: rows r0 + 0..63 below row end, columns
+// c0 + 0..63 below column end (else 0), to registers and from there to LDS.
+__device__ __forceinline__ void block_fetch(const double* A, long ld, int r0, int rend, int c0,
+                                            int cend, int tid, double (&v)[16]) {
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int r = (tid >> 6) + 4 * u, c = tid & 63;
+    v[u] = r0 + r < rend && c0 + c < cend ? A[(long)(r0 + r) * ld + c0 + c] : 0.0;
+  }
+}
+__device__ __forceinline__ void block_put(const double (&v)[16], int tid, CBlock& S) {
+#pragma unroll
+  for (int u = 0; u < 16; ++u) S[(tid >> 6) + 4 * u][tid & 63] = v[u];
 }
 
-int copy2d(const double* src, long lds, double* dst, long ldd, int rows, int cols,
-           hipStream_t st) {
-  const long n = (long)rows * cols;
-  if (n == 0) return SYNIM_OK;
-  hipLaunchKernelGGL(copy2d_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, src,
-                     lds, dst, ldd, rows, cols);
-  SYNIM_HIP_TRY(hipGetLastError());
-  return SYNIM_OK;
+// acc (16 rows of a wave, 4 blocks of 16 columns) += a X Y^T over 64 terms, X's
+// rows from x0, Y's all.
+__device__ __forceinline__ void mul_nt(const CBlock& X, int x0, const CBlock& Y, double a, int lane,
+                                       d4 (&acc)[4]) {
+#pragma unroll 4
+  for (int s = 0; s < CB / 4; ++s) {
+    const int k = 4 * s + (lane >> 4);
+    const double x = a * X[x0 + (lane & 15)][k];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, Y[16 * j + (lane & 15)][k], acc[j], 0, 0, 0);
+  }
 }
 
-// Blocked Cholesky and solves with the diagonal blocks inverted: the panel
-// below each diagonal block and the block rows of the solves become matrix-
-// core GEMMs against L_kk^-1 instead of substitutions with one thread per row
-// or column.  Linv: ceil(n / CB) blocks of CB x CB doubles, written by potrf_inv
-// and read by potrs_inv; tmp: max(n, m) x CB doubles.
-int potrf_inv(double* A, int n, long ld, int* status, double* Linv, double* tmp,
-              hipStream_t st) {
-  for (int k = 0; k < n; k += CB) {
-    const int nb = std::min(CB, n - k);
-    double* Li = Linv + (long)(k / CB) * CB * CB;
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, st, A, ld, k, nb, status, Li);
-    SYNIM_HIP_TRY(hipGetLastError());
-    const int r0 = k + nb;
-    if (r0 >= n) break;
-    // panel: A[r0:, k:k+nb] <- A[r0:, k:k+nb] L_kk^-T (from a copy)
-    int rc = copy2d(A + (long)r0 * ld + k, ld, tmp, nb, n - r0, nb, st);
-    if (rc != SYNIM_OK) return rc;
-    GemmArgs p{};
-    p.M = n - r0;
-    p.N = nb;
-    p.K = nb;
-    p.X = tmp;   // X(q, i) = tmp[i][q]
-    p.sxk = 1;
-    p.sxm = nb;
-    p.Y = Li;    // Y(q, j) = L_kk^-1[j][q]
-    p.syk = 1;
-    p.syn = CB;
-    p.C = A + (long)r0 * ld + k;
-    p.ldc = ld;
-    p.alpha = 1.0;
-    p.beta = 0.0;
-    if ((rc = gemm(p, st)) != SYNIM_OK) return rc;
-    // trailing lower triangle: A[r0:, r0:] -= P P^T, P = A[r0:, k:k+nb]
+// One 16 x 16 block of X Y (16 terms): X at (xr, xc), Y at (yr, yc).
+__device__ __forceinline__ d4 mul16(const CBlock& X, int xr, int xc, const CBlock& Y, int yr, int yc,
+                                    int lane, d4 acc) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int k = 4 * s + (lane >> 4);
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(X[xr + (lane & 15)][xc + k],
+                                               Y[yr + k][yc + (lane & 15)], acc, 0, 0, 0);
+  }
+  return acc;
+}
+__device__ __forceinline__ void put16(CBlock& S, int r, int c, int lane, const d4& v, double a) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) S[r + 4 * e + (lane >> 4)][c + (lane & 15)] = a * v[e];
+}
+
+__device__ __forceinline__ double from_lane(double v, int lane) {
+  const unsigned long long b = __double_as_longlong(v);
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)b, lane);
+  const unsigned hi = __builtin_amdgcn_readlane((unsigned)(b >> 32), lane);
+  return __longlong_as_double((unsigned long long)hi << 32 | lo);
+}
+
+// Diagonal block k of the panel from column K: brought up to date with the panel's
+// columns before it, factored (written back) and inverted (to Linv, CB x CB, zero
+// above the diagonal and outside nb x nb).  A pivot that is not positive sets
+// *status and counts as 1.  One workgroup: the chain of 64 pivots is all latency,
+// so it runs in 16 columns of one wave, lane i holding row i in registers (no
+// barrier and no LDS between pivots), with the rest by matrix products (64
+// columns with two barriers each and an inverse of one thread per column: 125 us,
+// now 29).
+__global__ __launch_bounds__(256) void panel_diag_kernel(double* A, long ld, int K, int k, int nb,
+                                                         int* status, double* Linv) {
+  __shared__ CBlock L, P, X;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double v[16];
+  block_fetch(A, ld, k, k + nb, k, k + nb, tid, v);
+  d4 acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] = d4{0.0, 0.0, 0.0, 0.0};
+  for (int c = K; c < k; c += CB) {
+    double w[16];
+    block_fetch(A, ld, k, k + nb, c, k, tid, w);
+    __syncthreads();
+    block_put(w, tid, P);
+    __syncthreads();
+    mul_nt(P, 16 * wave, P, -1.0, lane, acc);
+  }
+  block_put(v, tid, L);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 16 * wave + 4 * e + (lane >> 4), c = 16 * j + (lane & 15);
+      // (above the diagonal the matrix holds nothing; past nb the identity)
+      const double d = r < nb && c <= r ? L[r][c] + acc[j][e] : r == c ? 1.0 : 0.0;
+      L[r][c] = d;
+      X[r][c] = 0.0;
+    }
+  __syncthreads();
+  bool bad = false;
+#pragma unroll 1
+  for (int s = 0; s < 4; ++s) {
+    const int c0 = 16 * s;
+    if (wave == 0) {
+      double a[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) a[j] = L[lane][c0 + j];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        double d = from_lane(a[j], c0 + j);
+        if (!(d > 0.0)) {
+          bad = true;
+          d = 1.0;
+        }
+        d = sqrt(d);
+        a[j] = lane == c0 + j ? d : a[j] / d;
+#pragma unroll
+        for (int q = j + 1; q < 16; ++q) a[q] = __fma_rn(-a[j], from_lane(a[j], c0 + q), a[q]);
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (lane >= c0 + j) L[lane][c0 + j] = a[j];
+    }
+    __syncthreads();
+    // the block's remaining columns, 16 rows a wave
+    if (wave > s)
+      for (int j = s + 1; j <= wave; ++j) {
+        d4 t{};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int kk = c0 + 4 * q + (lane >> 4);
+          t = __builtin_amdgcn_mfma_f64_16x16x4f64(L[16 * wave + (lane & 15)][kk],
+                                                   L[16 * j + (lane & 15)][kk], t, 0, 0, 0);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = 16 * wave + 4 * e + (lane >> 4), c = 16 * j + (lane & 15);
+          if (c <= r) L[r][c] -= t[e];
+        }
+      }
+    __syncthreads();
+  }
+  if (wave == 0 && lane == 0 && bad) atomicOr(status, 1);
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int r = wave + 4 * u, c = lane;
+    if (r < nb && c <= r) A[(long)(k + r) * ld + k + c] = L[r][c];
+  }
+  // inverse: the four diagonal 16 x 16 blocks, a wave each, lane c its column c ...
+  {
+    const int d0 = 16 * wave, c = lane & 15;
+    double x[16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) x[r] = r == c ? 1.0 : 0.0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      x[q] = x[q] / L[d0 + q][d0 + q];
+#pragma unroll
+      for (int r = q + 1; r < 16; ++r) x[r] = __fma_rn(-L[d0 + r][d0 + q], x[q], x[r]);
+    }
+    if (lane < 16)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) X[d0 + r][d0 + c] = x[r];
+  }
+  __syncthreads();
+  // ... then the blocks below them, by distance: X_ij = -X_ii sum_k L_ik X_kj
+#pragma unroll 1
+  for (int dist = 1; dist < 4; ++dist) {
+    const int i = wave, j = wave - dist;
+    if (j >= 0) {
+      d4 t{};
+      for (int q = j; q < i; ++q) t = mul16(L, 16 * i, 16 * q, X, 16 * q, 16 * j, lane, t);
+      put16(P, 16 * i, 0, lane, t, 1.0);
+      // (a wave reads back only what it wrote)
+      __builtin_amdgcn_wave_barrier();
+      d4 r{};
+      r = mul16(X, 16 * i, 16 * i, P, 16 * i, 0, lane, r);
+      put16(X, 16 * i, 16 * j, lane, r, -1.0);
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int r = wave + 4 * u, c = lane;
+    Linv[r * CB + c] = r < nb && c < nb ? X[r][c] : 0.0;
+  }
+}
+
+// Rows [r0, n) of block column k: brought up to date with the panel's columns [K, k),
+// then multiplied by L_kk^-T; 64 rows a workgroup, in place.
+__global__ __launch_bounds__(256) void panel_rows_kernel(double* A, long ld, int K, int k, int r0,
+                                                         int n, const double* __restrict__ Linv) {
+  __shared__ CBlock T, R, D;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int i0 = r0 + blockIdx.x * CB;
+  double v[16], w[16];
+  block_fetch(Linv, CB, 0, CB, 0, CB, tid, v);
+  d4 acc[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = i0 + 16 * wave + 4 * e + (lane >> 4);
+      acc[j][e] = r < n ? A[(long)r * ld + k + 16 * j + (lane & 15)] : 0.0;
+    }
+  block_put(v, tid, T);
+  for (int c = K; c < k; c += CB) {
+    block_fetch(A, ld, i0, n, c, k, tid, v);
+    block_fetch(A, ld, k, k + CB, c, k, tid, w);
+    __syncthreads();
+    block_put(v, tid, R);
+    block_put(w, tid, D);
+    __syncthreads();
+    mul_nt(R, 16 * wave, D, -1.0, lane, acc);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) put16(R, 16 * wave, 16 * j, lane, acc[j], 1.0);
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) acc[j] = d4{0.0, 0.0, 0.0, 0.0};
+  mul_nt(R, 16 * wave, T, 1.0, lane, acc);
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = i0 + 16 * wave + 4 * e + (lane >> 4);
+      if (r < n) A[(long)r * ld + k + 16 * j + (lane & 15)] = acc[j][e];
+    }
+}
+
+int potrf_inv(double* A, int n, long ld, int* status, double* Linv, hipStream_t st) {
+  for (int K = 0; K < n; K += CW) {
+    const int K1 = std::min(n, K + CW);
+    for (int k = K; k < K1; k += CB) {
+      const int nb = std::min(CB, n - k), r0 = k + nb;
+      double* Li = Linv + (long)(k / CB) * CB * CB;
+      hipLaunchKernelGGL(panel_diag_kernel, dim3(1), dim3(256), 0, st, A, ld, K, k, nb, status, Li);
+      SYNIM_HIP_TRY(hipGetLastError());
+      if (r0 >= n) break;
+      hipLaunchKernelGGL(panel_rows_kernel, dim3((unsigned)((n - r0 + CB - 1) / CB)), dim3(256), 0,
+                         st, A, ld, K, k, r0, n, Li);
+      SYNIM_HIP_TRY(hipGetLastError());
+    }
+    if (K1 >= n) break;
+    // trailing lower triangle: A[K1:, K1:] -= P P^T, P = A[K1:, K:K1]
     GemmArgs g{};
-    g.M = g.N = n - r0;
-    g.K = nb;
-    g.X = g.Y = A + (long)r0 * ld + k;
+    g.M = g.N = n - K1;
+    g.K = K1 - K;
+    g.X = g.Y = A + (long)K1 * ld + K;
     g.sxk = g.syk = 1;
     g.sxm = g.syn = ld;
-    g.C = A + (long)r0 * ld + r0;
+    g.C = A + (long)K1 * ld + K1;
     g.ldc = ld;
     g.alpha = -1.0;
     g.beta = 1.0;
     g.lower = 1;
-    if ((rc = gemm(g, st)) != SYNIM_OK) return rc;
+    const int rc = gemm(g, st);
+    if (rc != SYNIM_OK) return rc;
   }
   return SYNIM_OK;
 }
 
-int potrs_inv(const double* L, int n, long ld, double* B, int m, long ldb, const double* Linv,
-              double* tmp, hipStream_t st) {
-  // B_k <- L_kk^-1 B_k (forward) or L_kk^-T B_k (backward), from a copy
-  auto diag = [&](int k, int nb, bool backward) {
-    int rc = copy2d(B + (long)k * ldb, ldb, tmp, m, nb, m, st);
-    if (rc != SYNIM_OK) return rc;
-    const double* Li = Linv + (long)(k / CB) * CB * CB;
-    GemmArgs d{};
-    d.M = nb;
-    d.N = m;
-    d.K = nb;
-    d.X = Li;   // X(q, i) = L^-1[i][q] (forward) or L^-1[q][i] (backward)
-    d.sxk = backward ? CB : 1;
-    d.sxm = backward ? 1 : CB;
-    d.Y = tmp;  // Y(q, c) = tmp[q][c]
-    d.syk = m;
-    d.syn = 1;
-    d.C = B + (long)k * ldb;
-    d.ldc = ldb;
-    d.alpha = 1.0;
-    d.beta = 0.0;
-    return gemm(d, st);
+// Rows [K, K1) of B: solved against the panel's diagonal triangle, forward (L) or
+// backward (L^T), SCOLS right-hand sides a workgroup, which keeps them in LDS over
+// the panel's blocks.  The next 64 x 64 block of L or of an inverse is fetched
+// while the current one feeds the matrix cores.
+constexpr int SCOLS = 32;
+template <bool BACK>
+__global__ __launch_bounds__(256) void panel_solve_kernel(const double* __restrict__ L, long ld,
+                                                          int K, int K1,
+                                                          const double* __restrict__ Linv,
+                                                          double* B, long ldb, int m) {
+  __shared__ double Y[CW][SCOLS + 2];
+  __shared__ CBlock S;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c0 = blockIdx.x * SCOLS;
+  const int nblk = (K1 - K + CB - 1) / CB;
+  for (int e = tid; e < CW * SCOLS; e += 256) {
+    const int r = e / SCOLS, c = e % SCOLS;
+    Y[r][c] = K + r < K1 && c0 + c < m ? B[(long)(K + r) * ldb + c0 + c] : 0.0;
+  }
+  // block t of the products of block s: L of the blocks solved before it, then the
+  // inverse of its own
+  auto fetch = [&](int s, int t, double (&v)[16]) {
+    const int a = BACK ? nblk - 1 - s : s, b = BACK ? nblk - 1 - t : t;   // block rows of B
+    if (t == s)
+      block_fetch(Linv + (long)(K / CB + a) * CB * CB, CB, 0, CB, 0, CB, tid, v);
+    else if (BACK)
+      block_fetch(L, ld, K + b * CB, K1, K + a * CB, K1, tid, v);   // used transposed
+    else
+      block_fetch(L, ld, K + a * CB, K1, K + b * CB, K1, tid, v);
   };
-  for (int k = 0; k < n; k += CB) {
-    const int nb = std::min(CB, n - k);
-    int rc = diag(k, nb, false);
-    if (rc != SYNIM_OK) return rc;
-    if (k + nb >= n) break;
+  double v[16];
+  fetch(0, 0, v);
+  for (int s = 0; s < nblk; ++s) {
+    const int a = BACK ? nblk - 1 - s : s;
+    d4 acc[2];
+    for (int t = 0; t <= s; ++t) {
+      __syncthreads();   // the block before has been read (and Y written)
+      block_put(v, tid, S);
+      __syncthreads();
+      if (t < s) fetch(s, t + 1, v);
+      else if (s + 1 < nblk) fetch(s + 1, 0, v);
+      const int y0 = (BACK ? nblk - 1 - t : t) * CB, o0 = a * CB + 16 * wave;
+      if (t == 0 && s > 0) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[j][e] = Y[o0 + 4 * e + (lane >> 4)][16 * j + (lane & 15)];
+      }
+      if (t == s) {
+        // the block's right-hand sides, brought up to date, back to LDS for the
+        // product with the inverse (block 0's are there)
+        if (s > 0) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              Y[o0 + 4 * e + (lane >> 4)][16 * j + (lane & 15)] = acc[j][e];
+          __syncthreads();
+        }
+        acc[0] = acc[1] = d4{0.0, 0.0, 0.0, 0.0};
+      }
+      const double sign = t == s ? 1.0 : -1.0;
+#pragma unroll 4
+      for (int q = 0; q < CB / 4; ++q) {
+        const int kk = 4 * q + (lane >> 4), r = 16 * wave + (lane & 15);
+        const double x = sign * (BACK ? S[kk][r] : S[r][kk]);
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+          acc[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(x, Y[y0 + kk][16 * j + (lane & 15)], acc[j],
+                                                        0, 0, 0);
+      }
+      if (t == s) {
+        __syncthreads();   // every wave has read the right-hand sides
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            Y[o0 + 4 * e + (lane >> 4)][16 * j + (lane & 15)] = acc[j][e];
+      }
+    }
+  }
+  __syncthreads();
+  for (int e = tid; e < CW * SCOLS; e += 256) {
+    const int r = e / SCOLS, c = e % SCOLS;
+    if (K + r < K1 && c0 + c < m) B[(long)(K + r) * ldb + c0 + c] = Y[r][c];
+  }
+}
+
+int potrs_inv(const double* L, int n, long ld, double* B, int m, long ldb, const double* Linv,
+              hipStream_t st) {
+  const dim3 sg((unsigned)((m + SCOLS - 1) / SCOLS));
+  // forward: L Y = B, right-looking
+  for (int K = 0; K < n; K += CW) {
+    const int K1 = std::min(n, K + CW);
+    hipLaunchKernelGGL(panel_solve_kernel<false>, sg, dim3(256), 0, st, L, ld, K, K1, Linv, B, ldb,
+                       m);
+    SYNIM_HIP_TRY(hipGetLastError());
+    if (K1 >= n) break;
+    // B[K1:] -= L[K1:, K:K1] Y_K
     GemmArgs g{};
-    g.M = n - k - nb;
+    g.M = n - K1;
     g.N = m;
-    g.K = nb;
-    g.X = L + (long)(k + nb) * ld + k;
+    g.K = K1 - K;
+    g.X = L + (long)K1 * ld + K;
     g.sxk = 1;
     g.sxm = ld;
-    g.Y = B + (long)k * ldb;
+    g.Y = B + (long)K * ldb;
     g.syk = ldb;
     g.syn = 1;
-    g.C = B + (long)(k + nb) * ldb;
+    g.C = B + (long)K1 * ldb;
     g.ldc = ldb;
     g.alpha = -1.0;
     g.beta = 1.0;
-    if ((rc = gemm(g, st)) != SYNIM_OK) return rc;
-  }
-  const int last = ((n - 1) / CB) * CB;
-  for (int k = last; k >= 0; k -= CB) {
-    const int nb = std::min(CB, n - k);
-    int rc = diag(k, nb, true);
+    const int rc = gemm(g, st);
     if (rc != SYNIM_OK) return rc;
-    if (k == 0) break;
+  }
+  // backward: L^T X = Y, from the last panel
+  for (int K = (n - 1) / CW * CW; K >= 0; K -= CW) {
+    const int K1 = std::min(n, K + CW);
+    hipLaunchKernelGGL(panel_solve_kernel<true>, sg, dim3(256), 0, st, L, ld, K, K1, Linv, B, ldb,
+                       m);
+    SYNIM_HIP_TRY(hipGetLastError());
+    if (K == 0) break;
+    // B[0:K] -= L[K:K1, 0:K]^T X_K
     GemmArgs g{};
-    g.M = k;
+    g.M = K;
     g.N = m;
-    g.K = nb;
-    g.X = L + (long)k * ld;
+    g.K = K1 - K;
+    g.X = L + (long)K * ld;
     g.sxk = ld;
     g.sxm = 1;
-    g.Y = B + (long)k * ldb;
+    g.Y = B + (long)K * ldb;
     g.syk = ldb;
     g.syn = 1;
     g.C = B;
     g.ldc = ldb;
     g.alpha = -1.0;
     g.beta = 1.0;
-    if ((rc = gemm(g, st)) != SYNIM_OK) return rc;
+    const int rc = gemm(g, st);
+    if (rc != SYNIM_OK) return rc;
   }
   return SYNIM_OK;
 }
@@ -1288,15 +1552,11 @@ extern "C" int synim_proj_opt(const synim_proj_component* dms, int n_dm,
   SYNIM_HIP_TRY(hipGetLastError());
   if ((rc = product(pt_l, occ_l, nl, popt, nl, 0)) != SYNIM_OK) return rc;
   // the sampled matrices are spent: their memory holds the inverted diagonal
-  // blocks and the copies the solves work from
-  // (where they are too small, the substitution forms need no memory)
+  // blocks (where they are too small, the substitution forms need no memory)
   double* linv = pt_dm;
-  double* tmp = pt_dm + ((ndm + CB - 1) / CB) * CB * CB;
-  if ((size_t)(((ndm + CB - 1) / CB) * CB * CB + std::max(ndm, nl) * CB) <=
-      (size_t)rows * (size_t)ndm) {
-    if ((rc = potrf_inv(G, (int)ndm, ndm, status, linv, tmp, st)) != SYNIM_OK) return rc;
-    if ((rc = potrs_inv(G, (int)ndm, ndm, popt, (int)nl, nl, linv, tmp, st)) != SYNIM_OK)
-      return rc;
+  if ((size_t)((ndm + CB - 1) / CB) * CB * CB <= (size_t)rows * (size_t)ndm) {
+    if ((rc = potrf_inv(G, (int)ndm, ndm, status, linv, st)) != SYNIM_OK) return rc;
+    if ((rc = potrs_inv(G, (int)ndm, ndm, popt, (int)nl, nl, linv, st)) != SYNIM_OK) return rc;
   } else {
     if ((rc = potrf(G, (int)ndm, ndm, status, st)) != SYNIM_OK) return rc;
     if ((rc = potrs(G, (int)ndm, ndm, popt, (int)nl, nl, st)) != SYNIM_OK) return rc;
