@@ -1462,6 +1462,10 @@ int launch_stream(const Plan& P, const synim_wfs& w, const synim_affine& A, cons
                     whole_vectors(w, A, pad, d.PW, W_in);
   if ((long)H_in * W_in * 4 > INT_MAX) return SYNIM_E_SHAPE;   // 32-bit DMA offsets
   StreamFn fn = pick_fn(v, vec4, grad != nullptr);
+  // planes of a Jacobian in pairs, where the variant has a kernel for them
+  const int npl = vec4 && !grad && nplanes % 2 == 0 && v.two4 != nullptr ? 2 : 1;
+  if (npl == 2) fn = v.two4;
+  nplanes /= npl;   // plane sets of the launch
   int G = persistent_grid(fn, v.BLOCK);
   if (G < 0) return SYNIM_E_HIP;
   if (grad && G > GMAX_VJP) return SYNIM_E_SHAPE;

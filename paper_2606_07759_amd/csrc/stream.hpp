@@ -239,12 +239,13 @@ constexpr int stage_pack(int nj, int nst, int pack) {
 // budget of the 16-byte DMA variants is set to match, so registers never cut
 // that occupancy further.  (The 4-byte DMA variants hold four times the DMA
 // offsets and keep the compiler's own budget.)
-constexpr int stream_waves_per_simd(int block, int nj, int vw, int nst) {
+constexpr int stream_waves_per_simd(int block, int nj, int vw, int nst, int npl = 1) {
   const int lds = nst * nj * block * vw * 4 + MAX_TILE_ROWS * 8 + 1024;
   int wgs = 160 * 1024 / lds;
   if (wgs * block > 2048) wgs = 2048 / block;
   const int w = wgs * (block / 64) / 4;
-  return w < 1 ? 1 : (w > 8 ? 8 : w);
+  const int most = npl > 1 ? 2 : 8;
+  return w < 1 ? 1 : (w > most ? most : w);
 }
 
 // BATCH = false: the single-pair launches, with every batch path compiled out.
@@ -254,14 +255,23 @@ constexpr int stream_waves_per_simd(int block, int nj, int vw, int nst) {
 // run.  Its DMA read buffer-resource SGPRs that a v_readfirstlane had written
 // one wait state earlier, where 5 are needed; the DMA padding above removes
 // that hazard from every form.)
+// NPL = 2: the workgroup contracts every staged value with the patches of two
+// weight planes (two derivative maps), so that the four planes of a Jacobian stage
+// the IF rows twice and not four times and each LDS read feeds four products.
+// Its lanes hold twice the weights, so two waves per SIMD fit.  Four planes of 40
+// x 40 subapertures on 272 x 272 grids were bound by neither memory nor one unit
+// (LDS 43% and vector units 35% busy in turn): 265 us, now 221
+// (as much with six stages, or with the next row's reads ahead of the products: two
+// waves per SIMD and a barrier per actuator remain).
 template <int BLOCK, int LPS, int RPL, int PW, int NJ, int VW, int NST, int PACK, bool VJP,
-          bool BATCH>
-__global__ __launch_bounds__(BLOCK, VW == 4 ? stream_waves_per_simd(BLOCK, NJ, VW, NST) : 1) void
+          bool BATCH, int NPL = 1>
+__global__ __launch_bounds__(BLOCK, VW == 4 ? stream_waves_per_simd(BLOCK, NJ, VW, NST, NPL) : 1) void
 im_stream_kernel(StreamArgs g) {
+  static_assert(NPL == 1 || (!VJP && !BATCH), "two planes: single-pair planes only");
   constexpr int PH = LPS * RPL;
   constexpr int E = PH * PW;
   constexpr int STAGE_F4 = NJ * BLOCK * VW / 4;   // float4 per stage buffer
-  constexpr int KPMAX = stage_pack(NJ, NST, PACK);
+  constexpr int KPMAX = stage_pack(NJ, NST, PACK) >= NPL ? stage_pack(NJ, NST, PACK) / NPL : 1;
   static_assert(RPL * PW % 2 == 0, "a lane's weights load as float4");
   static_assert(NST >= 2 && NST <= 8, "2..8 stages");
   static_assert(NJ * (NST - 2) <= 63, "vmcnt range");
@@ -274,7 +284,7 @@ im_stream_kernel(StreamArgs g) {
   const int wave = tid >> 6;
   const int slot = tid / LPS, q = tid % LPS;
   const int xcd = blockIdx.x & 7;
-  const int plane = g.plane0 + blockIdx.z;
+  const int plane = g.plane0 + NPL * blockIdx.z;   // the first of NPL
   // Items of XCD queue x.  The queues of a single-pair launch hold the same
   // number of items, and a workgroup stays on its XCD's.  Those of a batch
   // differ: there a workgroup whose queue is empty takes what is left in the
@@ -499,28 +509,33 @@ im_stream_kernel(StreamArgs g) {
       }
       voff[j] = v;
     }
-    float wx[RPL][PW], wy[RPL][PW];
+    float wx[NPL][RPL][PW], wy[NPL][RPL][PW];
     if (kk >= 0) {
       // this lane's floats (component, row, column), four to a load, the
       // subaperture's lanes side by side
-      const float4* W = reinterpret_cast<const float4*>(
-                            weights_l + ((size_t)plane * nv_l + kk) * 2 * E) + q;
 #pragma unroll
-      for (int f4 = 0; f4 < RPL * PW / 2; ++f4) {
-        const float4 w4 = W[f4 * LPS];
-        const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+      for (int l = 0; l < NPL; ++l) {
+        const float4* W = reinterpret_cast<const float4*>(
+                              weights_l + ((size_t)(plane + l) * nv_l + kk) * 2 * E) + q;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int f = 4 * f4 + u;
-          if (f < RPL * PW) wx[f / PW][f % PW] = w[u];
-          else wy[(f - RPL * PW) / PW][(f - RPL * PW) % PW] = w[u];
+        for (int f4 = 0; f4 < RPL * PW / 2; ++f4) {
+          const float4 w4 = W[f4 * LPS];
+          const float w[4] = {w4.x, w4.y, w4.z, w4.w};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const int f = 4 * f4 + u;
+            if (f < RPL * PW) wx[l][f / PW][f % PW] = w[u];
+            else wy[l][(f - RPL * PW) / PW][(f - RPL * PW) % PW] = w[u];
+          }
         }
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < RPL; ++i)
+      for (int l = 0; l < NPL; ++l)
 #pragma unroll
-        for (int c = 0; c < PW; ++c) wx[i][c] = wy[i][c] = 0.f;
+        for (int i = 0; i < RPL; ++i)
+#pragma unroll
+          for (int c = 0; c < PW; ++c) wx[l][i][c] = wy[l][i][c] = 0.f;
     }
     // chunk = P.chunk actuators, or (P.chunk == 0) an even split of the
     // actuators over P.n_chunks chunks
@@ -545,16 +560,18 @@ im_stream_kernel(StreamArgs g) {
         const int a = a0 + gi * KP + kp;
         const bool act = a < a1;
         const float* fk = fb + kp * nfl;
-        float sx = 0.f, sy = 0.f;
+        float sx[NPL], sy[NPL];
+#pragma unroll
+        for (int l = 0; l < NPL; ++l) sx[l] = sy[l] = 0.f;
 #pragma unroll
         for (int i = 0; i < RPL; ++i) {
-          if constexpr (BATCH || PW >= 12) {
+          if constexpr (BATCH || PW >= 12 || NPL > 1) {
             // a row's values are all read before its products, so that its
             // LDS reads are in flight together (left alone, the scheduler
             // may issue each read just ahead of its two products and wait for
-            // it there, one LDS latency per pair of values).  The batch, and
-            // wide patches (rotated or magnified maps), are bound by this
-            // contraction; the narrower single-pair patches hide it behind
+            // it there, one LDS latency per pair of values).  The batch, two
+            // planes and wide patches (rotated or magnified maps) are bound by
+            // this contraction; the narrower single-pair patches hide it behind
             // the DMA and keep the compiler's order, which needs fewer
             // registers.
             float f[PW];
@@ -562,44 +579,51 @@ im_stream_kernel(StreamArgs g) {
             for (int c = 0; c < PW; ++c) f[c] = fk[base[i] + c];
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int c = 0; c < PW; ++c) {
-              sx = __fmaf_rn(wx[i][c], f[c], sx);
-              sy = __fmaf_rn(wy[i][c], f[c], sy);
-            }
+            for (int c = 0; c < PW; ++c)
+#pragma unroll
+              for (int l = 0; l < NPL; ++l) {
+                sx[l] = __fmaf_rn(wx[l][i][c], f[c], sx[l]);
+                sy[l] = __fmaf_rn(wy[l][i][c], f[c], sy[l]);
+              }
           } else {
 #pragma unroll
             for (int c = 0; c < PW; ++c) {
               const float f = fk[base[i] + c];
-              sx = __fmaf_rn(wx[i][c], f, sx);
-              sy = __fmaf_rn(wy[i][c], f, sy);
+              sx[0] = __fmaf_rn(wx[0][i][c], f, sx[0]);
+              sy[0] = __fmaf_rn(wy[0][i][c], f, sy[0]);
             }
           }
         }
-        sx = dpp_sum(sx, LPS);
-        sy = dpp_sum(sy, LPS);
+#pragma unroll
+        for (int l = 0; l < NPL; ++l) {
+          sx[l] = dpp_sum(sx[l], LPS);
+          sy[l] = dpp_sum(sy[l], LPS);
+        }
         const size_t row = (size_t)(act ? a : a0) * 2 * nv_l;
         if (VJP) {
           if (act && kk >= 0 && q == 0)
-            vacc += (double)g.grad[row + kk] * sx + (double)g.grad[row + nv_l + kk] * sy;
+            vacc += (double)g.grad[row + kk] * sx[0] + (double)g.grad[row + nv_l + kk] * sy[0];
         } else {
-          // exactly one store instruction per (contracting) wave and actuator
+          // exactly NPL store instructions per (contracting) wave and actuator
           // slot, whatever the lanes hold (the pipeline's wait counts rely on this number).
           // Every lane of a subaperture holds both sums after the DPP
           // reduction: even lanes store s_x, odd lanes s_y, so the extra
           // lanes repeat a real store (same address, same value) and add no
           // memory traffic.  Only empty slots and the slots past the chunk's
           // end target a scratch slot.
-          float* o = out_l + (size_t)(plane - g.out_plane0) * P.n_act * 2 * nv_l + row;
           const bool real = act && kk >= 0;
           const bool ycomp = (q & 1) != 0;
-          float* dst = real ? (ycomp ? o + nv_l + kk : o + kk) : g.scratch + (tid & 63);
-          const float val = ycomp ? sy : sx;
           // a global (not flat) store: flat operations may complete out of
           // order with the DMA, and the wait counts need them in order.  A
           // plain (write-back) store: the pieces that the tiles of one chunk
           // write into an IM row merge in the XCD's L2, and the scratch slot
           // stays there (streaming stores measured 4% slower on the ELT build)
-          *(gfloat_t*)dst = val;
+#pragma unroll
+          for (int l = 0; l < NPL; ++l) {
+            float* o = out_l + (size_t)(plane + l - g.out_plane0) * P.n_act * 2 * nv_l + row;
+            float* dst = real ? (ycomp ? o + nv_l + kk : o + kk) : g.scratch + (tid & 63);
+            *(gfloat_t*)dst = ycomp ? sy[l] : sx[l];
+          }
         }
       }
     };
@@ -623,7 +647,7 @@ im_stream_kernel(StreamArgs g) {
     // "at most n in flight", n = the operations issued after this stage's
     // DMA, means this stage has landed.  The wait counts every
     // vector-memory operation issued after this stage's DMA: the later
-    // stages' DMA (NJ each) and, in the IM kernel, the KP stores of each step
+    // stages' DMA (NJ each) and, in the IM kernel, the KP NPL stores of each step
     // since then.
     //
     // With the XCD sync on, group j with j a multiple of E opens block j/E,
@@ -637,7 +661,7 @@ im_stream_kernel(StreamArgs g) {
     auto step = [&](auto kc, int gi) __attribute__((always_inline)) {
       constexpr int K = decltype(kc)::value;
       const int later = min(NST - 2, n_grp - 1 - gi);
-      const int stores = VJP || !wave_on ? 0 : KP * min(gi, NST - 1);
+      const int stores = VJP || !wave_on ? 0 : NPL * KP * min(gi, NST - 1);
       const int x = gi + NST - 1;   // the group this step starts loading
       int extra = 0;
       if (sync_on && wave == 0) extra = later + (gi + later) / sync_e - gi / sync_e;
@@ -700,6 +724,7 @@ struct Variant {
   StreamFn im4, vjp4;                  // 16-byte DMA: rows a multiple of 4 floats, aligned stack
   StreamFn im1, vjp1;                  // 4-byte DMA: any row length / alignment
   StreamFn bim4, bim1;                 // batched launches (IM only)
+  StreamFn two4;                       // two planes a workgroup, 16-byte DMA (null: none)
   int PH() const { return LPS * RPL; }
   int cap_floats() const { return NJ4 * BLOCK * 4; }
 };
@@ -708,6 +733,16 @@ struct Variant {
 // vmcnt counter can express
 constexpr int nst_vw1(int n, int s) { return s < 2 + 63 / (4 * n) ? s : 2 + 63 / (4 * n); }
 
+// The two-plane kernel of a variant: patches whose weights twice over leave room
+// for a row's values in 256 registers, workgroups of at most two waves per SIMD.
+template <int B, int L, int R, int W, int N, int S, int K>
+constexpr StreamFn two_planes() {
+  if constexpr (B <= 512 && R * W <= 36 && (S - 2) * (N + 1) + 1 + 2 * (S - 1) <= 63)
+    return im_stream_kernel<B, L, R, W, N, 4, S, K, false, false, 2>;
+  else
+    return nullptr;
+}
+
 #define SYNIM_VARIANT_K(B, L, R, W, N, S, K)                                           \
   {B, L, R, W, N, S, stage_pack(N, S, K),                                              \
    im_stream_kernel<B, L, R, W, N, 4, S, K, false, false>,                             \
@@ -715,7 +750,8 @@ constexpr int nst_vw1(int n, int s) { return s < 2 + 63 / (4 * n) ? s : 2 + 63 /
    im_stream_kernel<B, L, R, W, 4 * N, 1, nst_vw1(N, S), K, false, false>,             \
    im_stream_kernel<B, L, R, W, 4 * N, 1, nst_vw1(N, S), K, true, false>,              \
    im_stream_kernel<B, L, R, W, N, 4, S, K, false, true>,                              \
-   im_stream_kernel<B, L, R, W, 4 * N, 1, nst_vw1(N, S), K, false, true>}
+   im_stream_kernel<B, L, R, W, 4 * N, 1, nst_vw1(N, S), K, false, true>,              \
+   two_planes<B, L, R, W, N, S, K>()}
 #define SYNIM_VARIANT(B, L, R, W, N, S) SYNIM_VARIANT_K(B, L, R, W, N, S, 1)
 #define SYNIM_VARIANT_PACK(B, L, R, W, N, S) SYNIM_VARIANT_K(B, L, R, W, N, S, 4)
 
