@@ -11,24 +11,39 @@ namespace {
 constexpr int SBLOCK = 256;          // most threads of a workgroup, two pixel columns each
 constexpr int SROWS = 8;             // subaperture rows one workgroup walks in turn
 
-// Four neighbouring samples (any float alignment: one 16-byte load).
-struct __attribute__((packed, aligned(4))) Quad {
-  float v[4];
+// Two neighbouring samples (any float alignment: one 8-byte load).
+struct __attribute__((packed, aligned(4))) Pair {
+  float a, b;
 };
+// A thread's samples of a pixel row: columns x and x + 1, and the ones beside them.
+struct Row {
+  float c0, c1, left, right;
+};
+constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;   // lane i from i + 1, from i - 1
+template <int DPP>
+__device__ __forceinline__ float from_beside(float at_edge, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(at_edge), __float_as_int(v), DPP,
+                                                    0xf, 0xf, false));
+}
 
 // One workgroup per (group of SROWS subaperture rows, run of whole subapertures
 // across the block's pixel columns, run of phase maps).  Thread t owns pixel columns
 // x = x0 + 2t and x + 1 and walks down the group's pixel rows with three of them in
-// registers: one 16-byte load per row holds both columns' samples and their left
-// and right neighbours, and the rows above and below are the ones before and
-// after it (four separate loads and a pupil byte per pixel had taken 0.40 ms for
-// 1200 maps of 482 x 482; the loads' issue, not the 2.8 TB/s, bounded them).  The
-// pupil-masked differences and the pupil count are summed down each subaperture
+// registers: one 8-byte load per row holds both columns' samples, the lanes
+// beside it the samples left and right of them (one load more for the wave's two
+// outer lanes), the rows before and after it the ones above and below.  What
+// bounds it is the cache's accesses and the vector instructions, each about two
+// thirds busy (four separate loads and a pupil byte per pixel: 0.40 ms for 1200
+// maps of 482 x 482; a 16-byte load that overlaps its neighbours' took a cache
+// access for nearly every lane, 0.33).  A wave whose columns lie outside the
+// pupil over a subaperture row reads nothing there, one wholly inside it tests
+// no pupil bits.
+// The pupil-masked differences and the pupil count are summed down each subaperture
 // row; the per-subaperture sums then add those column sums in column order (a
 // fixed order, so results are bit-reproducible).  The pupil of a thread's columns
 // is kept as bits over the run of maps where the group has at most 64 pixel rows.
-// Each XCD takes all blocks of a map before its
-// next, so that shared rows and lines meet in its L2.  Now 0.33.
+// Each XCD takes all blocks of a map before its next, so that shared rows and lines
+// meet in its L2.  Now 0.30.
 __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict__ phase, int n,
                                                         const int32_t* __restrict__ valid,
                                                         const uint8_t* __restrict__ pupil,
@@ -69,6 +84,12 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
   const bool on = 2 * t < nu * p, two = 2 * t + 1 < nu * p;
   const int y_beg = v0 * p, y_end = v_end * p;
   const bool keep = y_end - y_beg <= 64;
+  const bool wave_on = __any(on);
+  // offsets in a haloed row: of column x (columns past W are read as W - 1, W), of
+  // the column before the wave's first and after its last
+  const int at = 1 + min(x, W - 1);
+  const bool edge = lane == 0 || (lane == 63 && x + 2 <= W);
+  const int at_outer = lane == 0 ? min(x, W) : min(x + 3, W + 1);
   unsigned long long in0 = 0, in1 = 0;   // pupil bits of rows y_beg.. of the two columns
   if (keep && on) {
     const int second = two ? 1 : 0;
@@ -91,76 +112,110 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
   for (int i = i0; i < min(n, i0 + maps_per_block); ++i) {
     const float* ph = phase + (size_t)i * (size_t)(H + 2) * (size_t)Wh;
     float* out = slopes + (size_t)i * 2 * nv;
-    // samples x - 1 .. x + 2 of pixel row y (haloed row y + 1); the last only for
-    // a second column
-    auto row = [&](int y) {
-      const float* q = ph + (size_t)(y + 1) * Wh + x;
-      Quad r;
-      if (two) {
-        r = *reinterpret_cast<const Quad*>(q);
-      } else {
-        r.v[0] = q[0];
-        r.v[1] = q[1];
-        r.v[2] = q[2];
-        r.v[3] = 0.f;
-      }
+    // pixel row y (haloed row y + 1): its own two columns per lane, and one of the
+    // wave's two outer columns for its first and last lane
+    auto own = [&](int y) {
+      return *reinterpret_cast<const Pair*>(ph + (size_t)(y + 1) * Wh + at);
+    };
+    auto outer = [&](int y) { return ph[(size_t)(y + 1) * Wh + at_outer]; };
+    auto make = [&](const Pair& v, float e) {
+      Row r;
+      r.c0 = x < W ? v.a : v.b;   // (the pair of column W starts one before it)
+      r.c1 = v.b;
+      r.left = from_beside<DPP_WAVE_SHR1>(e, r.c1);
+      r.right = from_beside<DPP_WAVE_SHL1>(e, r.c0);
       return r;
     };
-    Quad prev{}, cur{};
-    if (on) {
-      prev = row(y_beg - 1);
-      cur = row(y_beg);
-    }
+    Row prev{}, cur{};
+    bool have = false;   // prev and cur hold the pixel rows above and at the next row
     // two subaperture rows per step between barriers
     for (int v = v0; v < v_end; v += 2) {
       const int nr = min(2, v_end - v);
       float gx[2][2] = {}, gy[2][2] = {}, cnt[2][2] = {};   // [subaperture row][column]
-      // U rows' loads in flight (a divisor of p where there is one, so that no
-      // row is loaded twice)
-      auto walk = [&](auto uc) {
+      // subaperture row r, U pixel rows' loads in flight (a divisor of p where there
+      // is one, so that no row is loaded twice); FULL: all of the wave's pixels
+      // are in the pupil
+      auto walk = [&](int r, auto uc, auto full) {
         constexpr int U = decltype(uc)::value;
+        constexpr bool FULL = decltype(full)::value;
+        const int ya = (v + r) * p;
+        if (!have) {
+          const Pair pv = own(ya - 1), pc = own(ya);
+          const float e = edge ? outer(ya) : 0.f;
+          prev = make(pv, 0.f);
+          cur = make(pc, e);
+        }
+        float sx0 = 0.f, sx1 = 0.f, sy0 = 0.f, sy1 = 0.f, c0 = 0.f, c1 = 0.f;
+        for (int d0 = 0; d0 < p; d0 += U) {
+          Pair nx[U];
+          float e[U];
 #pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          if (r >= nr) break;
-          const int ya = (v + r) * p;
-          for (int d0 = 0; d0 < p; d0 += U) {
-            Quad nx[U];
+          for (int u = 0; u < U; ++u) nx[u] = own(min(ya + d0 + u + 1, y_end));
 #pragma unroll
-            for (int u = 0; u < U; ++u) nx[u] = row(min(ya + d0 + u + 1, y_end));
+          for (int u = 0; u < U; ++u) e[u] = 0.f;
+          if (edge) {
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-              if (d0 + u >= p) break;
-              const int y = ya + d0 + u;
-              bool a, b;
+            for (int u = 0; u < U; ++u) e[u] = outer(min(ya + d0 + u + 1, y_end));
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (d0 + u >= p) break;
+            const int y = ya + d0 + u;
+            bool a = true, b = true;
+            if (!FULL) {
               if (keep) {
                 a = (in0 >> (y - y_beg)) & 1;
                 b = (in1 >> (y - y_beg)) & 1;
               } else {
-                const uint8_t* q = pupil + (size_t)y * W + x;
-                a = q[0] != 0;
+                const uint8_t* q = pupil + (size_t)y * W + (on ? x : 0);
+                a = on && q[0] != 0;
                 b = two && q[1] != 0;
               }
-              const float ex0 = 0.5f * (cur.v[2] - cur.v[0]), ex1 = 0.5f * (cur.v[3] - cur.v[1]);
-              const float ey0 = 0.5f * (nx[u].v[1] - prev.v[1]);
-              const float ey1 = 0.5f * (nx[u].v[2] - prev.v[2]);
-              gx[r][0] += a ? ex0 : 0.f;
-              gy[r][0] += a ? ey0 : 0.f;
-              cnt[r][0] += a ? 1.f : 0.f;
-              gx[r][1] += b ? ex1 : 0.f;
-              gy[r][1] += b ? ey1 : 0.f;
-              cnt[r][1] += b ? 1.f : 0.f;
-              prev = cur;
-              cur = nx[u];
+              c0 += a ? 1.f : 0.f;
+              c1 += b ? 1.f : 0.f;
             }
+            const Row next = make(nx[u], e[u]);
+            const float ex0 = 0.5f * (cur.c1 - cur.left), ex1 = 0.5f * (cur.right - cur.c0);
+            const float ey0 = 0.5f * (next.c0 - prev.c0), ey1 = 0.5f * (next.c1 - prev.c1);
+            sx0 += a ? ex0 : 0.f;
+            sy0 += a ? ey0 : 0.f;
+            sx1 += b ? ex1 : 0.f;
+            sy1 += b ? ey1 : 0.f;
+            prev = cur;
+            cur = next;
           }
         }
+        gx[r][0] = sx0;
+        gx[r][1] = sx1;
+        gy[r][0] = sy0;
+        gy[r][1] = sy1;
+        cnt[r][0] = FULL ? (float)p : c0;
+        cnt[r][1] = FULL ? (float)p : c1;
       };
-      if (on) {
-        if (p % 6 == 0) walk(std::integral_constant<int, 6>{});
-        else if (p % 7 == 0) walk(std::integral_constant<int, 7>{});
-        else if (p % 5 == 0) walk(std::integral_constant<int, 5>{});
-        else if (p % 3 == 0) walk(std::integral_constant<int, 3>{});
-        else walk(std::integral_constant<int, 4>{});
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        if (r >= nr) break;
+        // how the wave's columns lie over this row's pixels: outside the pupil
+        // nothing is read
+        bool some = wave_on, full = false;
+        if (keep) {
+          const unsigned long long px = (p < 64 ? (1ull << p) - 1 : ~0ull)
+                                        << ((v + r) * p - y_beg);
+          some = __any(((in0 | in1) & px) != 0);
+          full = __all(!on || (two && (in0 & in1 & px) == px));
+        }
+        if (some) {   // (the wave as a whole: its lanes read each other)
+          auto form = [&](auto uc) {
+            if (full) walk(r, uc, std::true_type{});
+            else walk(r, uc, std::false_type{});
+          };
+          if (p % 6 == 0) form(std::integral_constant<int, 6>{});
+          else if (p % 7 == 0) form(std::integral_constant<int, 7>{});
+          else if (p % 5 == 0) form(std::integral_constant<int, 5>{});
+          else if (p % 3 == 0) form(std::integral_constant<int, 3>{});
+          else form(std::integral_constant<int, 4>{});
+        }
+        have = some;
       }
       __syncthreads();   // the previous step's sums have been read (and s_kk written)
 #pragma unroll
@@ -202,8 +257,8 @@ extern "C" int synim_sa_slopes(const float* phase, int n, const synim_wfs* wfs, 
   const int T = std::min(SBLOCK, ((wfs->n_sub_x * wfs->p + 1) / 2 + 63) / 64 * 64);
   const int spb = std::min(wfs->n_sub_x, 2 * T / wfs->p);
   const long bx = (long)((wfs->n_sub_y + SROWS - 1) / SROWS) * ((wfs->n_sub_x + spb - 1) / spb);
-  // 48 waves per CU, each a run of maps (1200 ELT maps: runs of 2 to 8 maps 347 to
-  // 327 us, of 16 363, where the last round of workgroups is short); eight runs or
+  // 48 waves per CU, each a run of maps (1200 ELT maps, with the 16-byte loads:
+  // runs of 2 to 8 maps 347 to 327 us, of 16 363, where the last round of workgroups is short); eight runs or
   // more in whole eights, an equal number for each XCD, fewer spread over all
   long mpb = std::min<long>(n, std::max(1L, n * bx * (T / 64) / 12288));
   long runs = (n + mpb - 1) / mpb;
