@@ -721,8 +721,8 @@ using StreamFn = void (*)(StreamArgs);
 struct Variant {
   int BLOCK, LPS, RPL, PW, NJ4, NST;   // NJ4: 16-byte DMA instructions per wave per stage
   int PACK;                            // most actuators one stage holds
-  StreamFn im4, vjp4;                  // 16-byte DMA: rows a multiple of 4 floats, aligned stack
-  StreamFn im1, vjp1;                  // 4-byte DMA: any row length / alignment
+  StreamFn im4, vjp4;                  // 16-byte DMA: no staged vector runs over a row's end
+  StreamFn im1, vjp1;                  // 4-byte DMA: any row length
   StreamFn bim4, bim1;                 // batched launches (IM only)
   StreamFn two4;                       // two planes a workgroup, 16-byte DMA (null: none)
   int PH() const { return LPS * RPL; }
