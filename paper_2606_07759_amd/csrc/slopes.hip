@@ -9,7 +9,7 @@ namespace synim {
 namespace {
 
 constexpr int SBLOCK = 256;          // most threads of a workgroup, two pixel columns each
-constexpr int SROWS = 8;             // subaperture rows one workgroup walks in turn
+constexpr int SROWS = 4;             // most subaperture rows one workgroup walks in turn
 
 // Two neighbouring samples (any float alignment: one 8-byte load).
 struct __attribute__((packed, aligned(4))) Pair {
@@ -26,7 +26,7 @@ __device__ __forceinline__ float from_beside(float at_edge, float v) {
                                                     0xf, 0xf, false));
 }
 
-// One workgroup per (group of SROWS subaperture rows, run of whole subapertures
+// One workgroup per (group of up to SROWS subaperture rows, run of whole subapertures
 // across the block's pixel columns, run of phase maps).  Thread t owns pixel columns
 // x = x0 + 2t and x + 1 and walks down the group's pixel rows with three of them in
 // registers: one 8-byte load per row holds both columns' samples, the lanes
@@ -43,13 +43,14 @@ __device__ __forceinline__ float from_beside(float at_edge, float v) {
 // fixed order, so results are bit-reproducible).  The pupil of a thread's columns
 // is kept as bits over the run of maps where the group has at most 64 pixel rows.
 // Each XCD takes all blocks of a map before its next, so that shared rows and lines
-// meet in its L2.  Now 0.30.
+// meet in its L2.  Now 0.29.
 __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict__ phase, int n,
                                                         const int32_t* __restrict__ valid,
                                                         const uint8_t* __restrict__ pupil,
                                                         int n_sub_x, int n_sub_y, int p, int nv,
                                                         int subs_per_block, int maps_per_block,
-                                                        int by_xcd, float* __restrict__ slopes) {
+                                                        int by_xcd, int srows,
+                                                        float* __restrict__ slopes) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, T = blockDim.x;
   // column sums [gx, gy, pupil count][subaperture row][2 T], then the valid-list
   // index of the group's subapertures
@@ -57,7 +58,7 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
   int* const s_kk = reinterpret_cast<int*>(s_sum + 12 * T);
   auto sum_at = [&](int what, int r, int c) -> float& { return s_sum[(2 * what + r) * 2 * T + c]; };
   const int n_runs = (n_sub_x + subs_per_block - 1) / subs_per_block;
-  const int n_blk = (n_sub_y + SROWS - 1) / SROWS * n_runs;
+  const int n_blk = (n_sub_y + srows - 1) / srows * n_runs;
   const int sb = by_xcd ? blockIdx.x >> 3 : blockIdx.x;
   const int blk = sb % n_blk;
   const int i0 = (by_xcd ? sb / n_blk * 8 + (blockIdx.x & 7) : sb / n_blk) * maps_per_block;
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
   const int Wh = W + 2;
   const int nu = min(subs_per_block, n_sub_x - u0);
   const int x = u0 * p + 2 * t;
-  const int v0 = grp * SROWS, v_end = min(n_sub_y, v0 + SROWS);
+  const int v0 = grp * srows, v_end = min(n_sub_y, v0 + srows);
   // valid-list index of every subaperture of the group (-1: not valid)
   for (int e = t; e < (v_end - v0) * nu; e += T) s_kk[e] = -1;
   __syncthreads();
@@ -256,10 +257,20 @@ extern "C" int synim_sa_slopes(const float* phase, int n, const synim_wfs* wfs, 
   // 128, 256 threads within 3% of each other on 480 columns)
   const int T = std::min(SBLOCK, ((wfs->n_sub_x * wfs->p + 1) / 2 + 63) / 64 * 64);
   const int spb = std::min(wfs->n_sub_x, 2 * T / wfs->p);
-  const long bx = (long)((wfs->n_sub_y + SROWS - 1) / SROWS) * ((wfs->n_sub_x + spb - 1) / spb);
-  // 48 waves per CU, each a run of maps (1200 ELT maps, with the 16-byte loads:
-  // runs of 2 to 8 maps 347 to 327 us, of 16 363, where the last round of workgroups is short); eight runs or
-  // more in whole eights, an equal number for each XCD, fewer spread over all
+  // Subaperture rows of a workgroup: four read the fewest rows twice, fewer make
+  // more and shorter chains of loads.  Four where that gives 64 waves a CU or more
+  // (1200 maps of 480 columns, 1 / 2 / 4 / 8 rows: 328, 294, 286, 294 us), else two
+  // (300 of 360: 47, 45, 51, 59; 500 of 350 with 10 pixels: 65, 63, 73, 100), else
+  // one (55 of 168: 7.7, 9.3, 15, 24).
+  int srows = SROWS;
+  while (srows > 1 && (long)n * ((wfs->n_sub_y + srows - 1) / srows) *
+                          ((wfs->n_sub_x + spb - 1) / spb) * (T / 64) < 16384)
+    srows /= 2;
+  const long bx = (long)((wfs->n_sub_y + srows - 1) / srows) * ((wfs->n_sub_x + spb - 1) / spb);
+  // 48 waves per CU, each a run of maps (1200 maps of 480 columns, with eight rows
+  // and 16-byte loads: runs of 2 to 8 maps 347 to 327 us, of 16 363, where the last
+  // round of workgroups is short); eight runs or more in whole eights, an equal
+  // number for each XCD, fewer spread over all
   long mpb = std::min<long>(n, std::max(1L, n * bx * (T / 64) / 12288));
   long runs = (n + mpb - 1) / mpb;
   const bool by_xcd = runs >= 8;
@@ -272,7 +283,7 @@ extern "C" int synim_sa_slopes(const float* phase, int n, const synim_wfs* wfs, 
                      dim3(T),
                      (12 * T + SROWS * spb) * sizeof(float),
                      (hipStream_t)stream, phase, n, wfs->valid_idx, wfs->pupil, wfs->n_sub_x,
-                     wfs->n_sub_y, wfs->p, wfs->n_valid, spb, (int)mpb, by_xcd ? 1 : 0, slopes);
+                     wfs->n_sub_y, wfs->p, wfs->n_valid, spb, (int)mpb, by_xcd ? 1 : 0, srows, slopes);
   SYNIM_HIP_TRY(hipGetLastError());
   return SYNIM_OK;
 }

@@ -9,7 +9,7 @@ namespace synim {
 namespace {
 
 constexpr int WX = 128, WY = 2;   // a workgroup's output pixels
-constexpr int UNR = 8;            // IFs of a workgroup at most, in one pass
+constexpr int MOST = 8;           // IFs of a workgroup at most, in one pass
 // What bounds the step is memory: each source pixel under the window once, the
 // window written.  A workgroup covers 128 x 2 output pixels of a run of IFs, its
 // FP64 source coordinates formed once and the taps of up to 8 IFs in flight.  1200
@@ -28,6 +28,10 @@ struct __attribute__((packed, aligned(4))) Pair {
   float x, y;
 };
 
+// UNR: IFs in flight, a power of two that holds the workgroup's run (a run of two
+// with eight in flight reads its last IF six times over: 55 IFs onto 170 x 170
+// pixels then took longer than the 10.9 us of one IF a workgroup, now 9.0).
+template <int UNR>
 __global__ __launch_bounds__(WX* WY) void warp_kernel(const float* __restrict__ ifs, int n,
                                                       int H_in, int W_in, MapD m, int H_out,
                                                       int W_out, int halo, int if_per_block,
@@ -75,7 +79,7 @@ __global__ __launch_bounds__(WX* WY) void warp_kernel(const float* __restrict__ 
   const size_t plane_in = (size_t)H_in * W_in;
   const size_t plane_out = (size_t)Hh * Wh;
   const size_t o0 = (size_t)oy * Wh + ox;
-  // UNR IFs per pass: all taps are loaded before the first one is used, so a
+  // UNR IFs per pass (one pass): all taps are loaded before the first one is used, so a
   // thread keeps that many gathers in flight instead of one IF's.  (Past the
   // run's end the last IF is read again and not stored.)
   if (__all(t00 && t01 && t10 && t11)) {   // the wave's taps all lie on the grid
@@ -134,7 +138,7 @@ extern "C" int synim_affine_warp(const float* ifs, int n, int H_in, int W_in,
   const int Wh = W_out + 2 * halo, Hh = H_out + 2 * halo;
   const int bx = (Wh + WX - 1) / WX, by = (Hh + WY - 1) / WY;
   const long xy = (long)bx * by;
-  long ipb = std::min<long>(n, std::clamp((long)n * xy / kMinBlocks, 1L, (long)UNR));
+  long ipb = std::min<long>(n, std::clamp((long)n * xy / kMinBlocks, 1L, (long)MOST));
   long runs = (n + ipb - 1) / ipb;
   const bool by_xcd = runs >= 8;
   if (by_xcd) {
@@ -143,7 +147,11 @@ extern "C" int synim_affine_warp(const float* ifs, int n, int H_in, int W_in,
   }
   const long blocks = runs * xy;
   if (blocks > 0x7fffffffL) return SYNIM_E_SHAPE;
-  hipLaunchKernelGGL(warp_kernel, dim3((unsigned)blocks), dim3(WX * WY), 0, (hipStream_t)stream, ifs,
+  const auto kernel = ipb > 4   ? warp_kernel<8>
+                      : ipb > 2 ? warp_kernel<4>
+                      : ipb > 1 ? warp_kernel<2>
+                                : warp_kernel<1>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(WX * WY), 0, (hipStream_t)stream, ifs,
                      n, H_in, W_in, to_map(*A), H_out, W_out, halo, (int)ipb,
                      by_xcd ? 1 : 0, out, oob_count);
   SYNIM_HIP_TRY(hipGetLastError());

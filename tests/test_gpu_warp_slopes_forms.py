@@ -58,3 +58,22 @@ def test_slopes_forms(gpu_lib, n_sub, p, n):
     got = gpu_lib.sa_slopes(to_dev(phase), gpu_lib.Wfs.from_numpy(pupil, p, valid)).cpu().numpy()
     ref = osl.slopes(phase, pupil, p, valid)
     assert np.max(np.abs(got - ref)) <= 1e-5 * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("n_sub,p,n", [
+    (9, 3, 3600),     # two subaperture rows a workgroup, the last group one
+    (9, 3, 5600),     # four
+    (6, 12, 8300),    # four of 12 pixels, the last group two
+    (5, 17, 8300),    # 68 pixel rows: pupil read per row
+])
+def test_slopes_rows_per_workgroup(gpu_lib, n_sub, p, n):
+    import torch
+    size = n_sub * p
+    pupil = wl.pupil_mask(size, float(size), 0.2)
+    valid = wl.valid_subapertures(pupil, p)
+    base = np.random.default_rng(size).standard_normal((61, size + 2, size + 2)).astype(np.float32)
+    at = np.arange(n) % 61
+    phase = to_dev(base)[torch.from_numpy(at).cuda()]
+    got = gpu_lib.sa_slopes(phase, gpu_lib.Wfs.from_numpy(pupil, p, valid)).cpu().numpy()
+    ref = osl.slopes(base, pupil, p, valid)
+    assert np.max(np.abs(got - ref[at])) <= 1e-5 * np.max(np.abs(ref))
