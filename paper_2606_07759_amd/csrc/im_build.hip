@@ -946,30 +946,30 @@ void tile_bound(const synim_affine& A, int p, const Variant& v, int tx, int ty, 
   *bh = (int)std::floor(sy + 1e-6) + 1 + ph_need;
 }
 
-// Tile shapes of one variant for this geometry, cheapest first by the cost
-// model: staged IF floats per subaperture (a partial 128-byte line counted at
-// each row end), for tiles whose packed rows provably fit the stage buffers.
+// Tile shapes of one variant for this geometry with their cost: staged IF floats
+// per subaperture (a partial 128-byte line counted at each row end), for tiles
+// whose packed rows provably fit the stage buffers.
 // pe: the subaperture span the patches must cover (w.p; larger when the
 // plan repairs edges, whose sample window is wider).
-int tiles_for_variant(const synim_wfs& w, const synim_affine& A, const Variant& v, Dims* out,
-                      double* cost_out, int max_out, int pe = -1) {
+template <class Emit>
+void each_tile(const synim_wfs& w, const synim_affine& A, const Variant& v, int pe, Emit emit) {
   int pw_need, ph_need;
   patch_need(A, pe < 0 ? w.p : pe, &pw_need, &ph_need);
-  if (v.PW < pw_need || v.PH() < ph_need) return 0;
+  if (v.PW < pw_need || v.PH() < ph_need) return;
   const int p = w.p;
   const long n_sub = (long)w.n_sub_x * w.n_sub_y;
-  int n = 0;
   const int nslot_max = v.BLOCK / v.LPS;
   for (int ns = nslot_max; ns >= nslot_max / 4; ns /= 2)
-    for (int tx = 1; tx <= ns; tx *= 2) {
-      const int ty = ns / tx;
-      if (tx * ty != ns) continue;   // slot s sits at (s % tx, s / tx) of its tile
+    for (int lx = 0; ns >> lx; ++lx) {   // (powers of two, all of them)
+      // slot s sits at (s % tx, s / tx) of its tile
+      const int tx = 1 << lx, ty = ns >> lx, ly = __builtin_ctz(ty);
       int BW, BH;
       tile_bound(A, p, v, tx, ty, ph_need, &BW, &BH);
       if ((long)BH * BW > v.cap_floats() || BH > MAX_TILE_ROWS) continue;
       const int ux = std::min(tx, w.n_sub_x), uy = std::min(ty, w.n_sub_y);
       const double fill = (double)(ux * uy) / ns;   // lanes with a subaperture
-      const long tiles = (long)((w.n_sub_x + tx - 1) / tx) * ((w.n_sub_y + ty - 1) / ty);
+      const int tiles_x = (w.n_sub_x + tx - 1) >> lx;
+      const long tiles = (long)tiles_x * ((w.n_sub_y + ty - 1) >> ly);
       double cost = (double)(BW + 24) * BH / ((double)ux * uy) / fill;
       if (tiles * 8 < 64 && n_sub > 64) cost *= 1.5;   // too few tiles to spread
       // a packing twin ranks ahead of its one-actuator variant where the
@@ -983,21 +983,30 @@ int tiles_for_variant(const synim_wfs& w, const synim_affine& A, const Variant& 
       d.TX = tx;
       d.TY = ty;
       d.NSLOT = ns;
-      d.n_tiles_x = (w.n_sub_x + tx - 1) / tx;
+      d.n_tiles_x = tiles_x;
       d.n_tiles = (int)tiles;
       d.BWmax = BW;
       d.BHmax = BH;
-      int at = n;
-      while (at > 0 && cost_out[at - 1] > cost) --at;
-      if (at >= max_out) continue;
-      for (int k = std::min(n, max_out - 1); k > at; --k) {
-        out[k] = out[k - 1];
-        cost_out[k] = cost_out[k - 1];
-      }
-      out[at] = d;
-      cost_out[at] = cost;
-      if (n < max_out) ++n;
+      emit(d, cost);
     }
+}
+
+// The same, cheapest first.
+int tiles_for_variant(const synim_wfs& w, const synim_affine& A, const Variant& v, Dims* out,
+                      double* cost_out, int max_out, int pe = -1) {
+  int n = 0;
+  each_tile(w, A, v, pe, [&](const Dims& d, double cost) {
+    int at = n;
+    while (at > 0 && cost_out[at - 1] > cost) --at;
+    if (at >= max_out) return;
+    for (int k = std::min(n, max_out - 1); k > at; --k) {
+      out[k] = out[k - 1];
+      cost_out[k] = cost_out[k - 1];
+    }
+    out[at] = d;
+    cost_out[at] = cost;
+    if (n < max_out) ++n;
+  });
   return n;
 }
 
@@ -1019,14 +1028,25 @@ int persistent_grid(StreamFn fn, int block);
 // Ranking by staged bytes alone, with the one-chunk-per-XCD schedule preferred,
 // picked 1420 us for the ELT build, 337 us instead of 98 for 40x40 subapertures
 // of 6 px, and 586 us instead of 108 for 37x37 of 7 px.
-double stream_cost(const Variant& v, int ns, double tile_cost, double waste) {
+double lane_cost(const Variant& v, int ns) {   // what the tile's shape does not change
   const double waves = stream_waves_per_simd(v.BLOCK, v.NJ4, 4, v.NST);
   const double w = waves * ns * v.LPS / v.BLOCK;   // waves per SIMD holding slots
   const double wgs = waves * 256 / v.BLOCK;        // workgroups per CU
   const int regs = 2 * v.RPL * v.PW + (v.PW >= 12 ? v.PW : 0) + v.RPL + v.NJ4 + 40;
-  return std::pow(waste, 0.25) * (1.0 + tile_cost / 250.0) *
-         (1.0 + 0.264 * std::pow(4.0 / w - 1.0, 1.3)) *
+  return (1.0 + 0.264 * std::pow(4.0 / w - 1.0, 1.3)) *
          (wgs < 2 ? 1.1 : wgs < 3 ? 1.0 : 0.95) * (regs > 512 / waves ? 1.2 : 1.0);
+}
+double stream_cost(double lanes, double tile_cost, double waste) {
+  return std::sqrt(std::sqrt(waste)) * (1.0 + tile_cost / 250.0) * lanes;
+}
+
+// Area of the smallest patch a variant has for the one needed (INT_MAX: none).
+int smallest_patch(int pw_need, int ph_need) {
+  int n = 0, best = INT_MAX;
+  const Variant* v = variants_table(&n);
+  for (int i = 0; i < n; ++i)
+    if (v[i].PW >= pw_need && v[i].PH() >= ph_need) best = std::min(best, v[i].PW * v[i].PH());
+  return best;
 }
 
 // Every (variant, tile shape, schedule) that can run this geometry with the
@@ -1038,10 +1058,7 @@ int candidate_dims(const synim_wfs& w, const synim_affine& A, Dims* out, double*
                    int max_out, int pe = -1) {
   int pw_need, ph_need;
   patch_need(A, pe < 0 ? w.p : pe, &pw_need, &ph_need);
-  int best_area = INT_MAX;
-  for (int i = 0; i < num_variants(); ++i)
-    if (variants_table(nullptr)[i].PW >= pw_need && variants_table(nullptr)[i].PH() >= ph_need)
-      best_area = std::min(best_area, variants_table(nullptr)[i].PW * variants_table(nullptr)[i].PH());
+  const int best_area = smallest_patch(pw_need, ph_need);
   if (best_area == INT_MAX) return 0;
   std::vector<std::pair<double, Dims>> all;
   for (int i = 0; i < num_variants(); ++i) {
@@ -1052,7 +1069,7 @@ int candidate_dims(const synim_wfs& w, const synim_affine& A, Dims* out, double*
     const int m = tiles_for_variant(w, A, v, tmp, tc, 64, pe);
     const int G = persistent_grid(v.im4, v.BLOCK);
     for (int k = 0; k < m; ++k) {
-      tc[k] = stream_cost(v, tmp[k].NSLOT, tc[k],
+      tc[k] = stream_cost(lane_cost(v, tmp[k].NSLOT), tc[k],
                           (double)tmp[k].n_tiles * tmp[k].NSLOT / ((double)w.n_sub_x * w.n_sub_y));
       all.push_back({tc[k], tmp[k]});
       // empty tiles (outside the pupil) are skipped at once, so a few more
@@ -1127,23 +1144,60 @@ TuneKey tune_key(const synim_wfs& w, const synim_affine& A) {
 // The tuned configuration for this geometry if there is one, else the
 // cost model's first choice.
 int choose_dims(const synim_wfs& w, const synim_affine& A, Dims* d, int pe = -1) {
-  Dims cand[MAX_CAND];
-  double cost[MAX_CAND];
-  const int n = candidate_dims(w, A, cand, cost, MAX_CAND, pe);
-  if (n == 0) return SYNIM_E_UNSUPPORTED;
-  *d = cand[0];
   const TuneKey key = tune_key(w, A);
-  std::lock_guard<std::mutex> lk(g_tune_mu);
-  for (int i = 0; i < g_tune_n; ++i)
-    if (g_tune[i].key == key)
-      for (int c = 0; c < n; ++c)
-        if (cand[c].var == &variants_table(nullptr)[g_tune[i].variant] && cand[c].TX == g_tune[i].TX &&
-            cand[c].TY == g_tune[i].TY && cand[c].NSLOT == g_tune[i].NSLOT &&
-            cand[c].sched == g_tune[i].sched && cand[c].sync_every == g_tune[i].sync_every) {
-          *d = cand[c];
-          return SYNIM_OK;
-        }
-  return SYNIM_OK;
+  TuneEntry tuned{};
+  bool have = false;
+  {
+    std::lock_guard<std::mutex> lk(g_tune_mu);
+    for (int i = 0; i < g_tune_n && !have; ++i)
+      if (g_tune[i].key == key) {
+        tuned = g_tune[i];
+        have = true;
+      }
+  }
+  if (have) {
+    Dims cand[MAX_CAND];
+    double cost[MAX_CAND];
+    const int n = candidate_dims(w, A, cand, cost, MAX_CAND, pe);
+    if (n == 0) return SYNIM_E_UNSUPPORTED;
+    *d = cand[0];
+    for (int c = 0; c < n; ++c)
+      if (cand[c].var == &variants_table(nullptr)[tuned.variant] && cand[c].TX == tuned.TX &&
+          cand[c].TY == tuned.TY && cand[c].NSLOT == tuned.NSLOT && cand[c].sched == tuned.sched &&
+          cand[c].sync_every == tuned.sync_every) {
+        *d = cand[c];
+        break;
+      }
+    return SYNIM_OK;
+  }
+  // The first of the candidates alone (the other schedules of a shape rank behind
+  // it): every build asks twice, once for its workspace, and listing, ranking and
+  // sorting them all took 13 to 36 us of a call each time (now 6 to 18).
+  int pw_need, ph_need, n_var = 0;
+  patch_need(A, pe < 0 ? w.p : pe, &pw_need, &ph_need);
+  const int best_area = smallest_patch(pw_need, ph_need);
+  if (best_area == INT_MAX) return SYNIM_E_UNSUPPORTED;
+  const Variant* vars = variants_table(&n_var);
+  const double n_sub = (double)w.n_sub_x * w.n_sub_y;
+  double least = 1e300;
+  for (int i = 0; i < n_var; ++i) {
+    const Variant& v = vars[i];
+    if (v.PW * v.PH() != best_area) continue;
+    double lanes[3] = {0, 0, 0};   // of all, half and a quarter of the slots
+    double staged = -1.0;          // tile cost of this variant's best, the tie-break
+    each_tile(w, A, v, pe, [&](const Dims& t, double tile_cost) {
+      const int part = v.BLOCK / v.LPS / t.NSLOT;
+      double& l = lanes[part >= 4 ? 2 : part >> 1];
+      if (l == 0) l = lane_cost(v, t.NSLOT);
+      const double c = stream_cost(l, tile_cost, (double)t.n_tiles * t.NSLOT / n_sub);
+      if (c < least || (c == least && tile_cost < staged)) {
+        least = c;
+        staged = tile_cost;
+        *d = t;
+      }
+    });
+  }
+  return least < 1e300 ? SYNIM_OK : SYNIM_E_UNSUPPORTED;
 }
 
 WsLayout layout(const synim_wfs& w, const Dims& d, int planes, bool repair = false) {
@@ -2309,7 +2363,7 @@ const Variant* batch_variant(const synim_batch* b, int rank) {
         ok = false;
         break;
       }
-      total += stream_cost(v, v.BLOCK / v.LPS, cost[0], 1.0) * b->wfs[pr.wfs].n_valid;
+      total += stream_cost(lane_cost(v, v.BLOCK / v.LPS), cost[0], 1.0) * b->wfs[pr.wfs].n_valid;
     }
     if (ok) ranked.push_back({total, i});
   }
