@@ -526,7 +526,7 @@ struct ClearWords {
 // second for the subapertures alone, and with every entry forming its candidates'
 // coordinates, cells and pupil tests, the 14 plans of a group of six sensors of
 // 3352 subapertures took 236 us, now 178; 52 subapertures 17, now 7 (a whole build
-// of 49 actuators on them 38.8, now 32.3).  Nothing is summed over workgroups here: a
+// of 77 actuators on them 38.8, then 32.3, now 26).  Nothing is summed over workgroups here: a
 // subaperture's status bits and out-of-grid samples are left in `info` for
 // plan_rows.  MULTI: some job has derivative planes (n_planes > 1).
 constexpr int PLAN_BLOCK = 256, PLAN_SUBS = 8;   // threads, subapertures at most
