@@ -1,0 +1,44 @@
+"""Samples of a large batch that a Gauss-Newton fit leaves to later launches.
+
+Six of the ten samples used here hop between bilinear cells past the first
+launch's iterations.  With up to 12 such samples in a batch each is split over
+workgroups, with more they go on in one workgroup each.  Either way an estimate
+is a function of the batch alone: it repeats bit for bit, with and without a graph,
+and does not depend on where in the batch its sample stands.
+"""
+import pytest
+
+pytestmark = pytest.mark.gpu
+DRAWS = [1000269, 1000577, 1000812, 1000895, 1000957, 1000978, 7, 8, 9, 10]
+
+
+def _fit(S, copies):
+    from paper_2606_07759_amd import learned
+    sy = learned.probe_system("cuda")
+    theta, snr, noise = learned.draw(DRAWS, sy.M)
+    m = S.Misreg(sy.wfs, sy.probes, sy.lo, sy.hi, max_batch=10 * copies)
+    one = learned.synthesize(m, theta, snr, noise, 10)
+    return m, one.repeat(copies, 1).contiguous()
+
+
+@pytest.mark.parametrize("copies", [1, 2, 3, 4])   # 6, 12, 18, 24 slow samples
+def test_estimates_repeat(gpu_lib, copies):
+    import torch
+    m, s = _fit(gpu_lib, copies)
+    a, ia = m.infer(s, use_graph=False)
+    bad = m.unconverged()
+    assert bad == int((ia >= 20).sum().item()) and int((ia > 10).sum().item()) == 6 * copies
+    out = (torch.empty_like(a), torch.empty_like(ia))
+    for k in range(12):
+        if k % 3 == 0:
+            b, ib = m.infer(s, use_graph=False)
+        else:
+            b, ib = m.infer(s, out=out)
+        assert torch.equal(b, a) and torch.equal(ib, ia) and m.unconverged() == bad
+    # equal samples, equal bits, wherever they stand
+    for r in range(1, copies):
+        assert torch.equal(a[10 * r:10 * r + 10], a[:10])
+        assert torch.equal(ia[10 * r:10 * r + 10], ia[:10])
+    perm = torch.randperm(10 * copies, generator=torch.Generator().manual_seed(1)).cuda()
+    b, ib = m.infer(s[perm].contiguous(), use_graph=False)
+    assert torch.equal(b, a[perm]) and torch.equal(ib, ia[perm])
