@@ -594,8 +594,8 @@ int synim_misreg_features(synim_misreg_ctx* c, const float* slopes, int B, const
 /* Estimate theta (device float64 [B][4]) from slopes (device [B][n_probe*2N]).
  * mode: SYNIM_MISREG_GN, _MLP, _MLP_GN (GN started from the MLP estimate).
  * iters (device int32 [B], nullable): GN steps taken (0 for MLP; -1 / -2 flag
- * a probe region beyond the context's bound / a lost workgroup sync, neither
- * expected inside the label box).  iter_cap (<= max_iter, 0 = max_iter)
+ * a probe region beyond the context's bound / a lost workgroup sync in a batch
+ * of up to 8, neither expected inside the label box).  iter_cap (<= max_iter, 0 = max_iter)
  * bounds the GN loop.  use_graph: replay a graph captured on `stream` (must
  * not be NULL) per (B, mode, iter_cap) and, on the paths that read the
  * caller's arrays directly (MLP, one-launch Gauss-Newton), per (slopes,
@@ -614,6 +614,12 @@ int synim_misreg_status(synim_misreg_ctx* c, int* host_out, void* stream);
  * when *host_n > 0, SYNIM_OK otherwise; synchronises `stream`.
  * Errors: SYNIM_E_NULL, SYNIM_E_HIP. */
 int synim_misreg_unconverged(synim_misreg_ctx* c, int32_t* host_n, void* stream);
+/* Most times (about a microsecond each) a workgroup of a sample split over several
+ * polls for the others before it gives up, 200000 until set.  A sample of a batch
+ * of up to 8 is then flagged -2 (see synim_misreg_infer); one of a larger batch is
+ * finished by one workgroup.  Drops the captured graphs, so none may be running.
+ * Errors: SYNIM_E_NULL, SYNIM_E_PARAM (polls < 1). */
+int synim_misreg_set_polls(synim_misreg_ctx* c, int polls);
 void synim_misreg_destroy(synim_misreg_ctx* c);
 
 #ifdef __cplusplus

@@ -135,6 +135,7 @@ SIGNATURES = {
     "synim_misreg_infer": (I, [P, P, I, I, P, P, I, I, P]),
     "synim_misreg_status": (I, [P, C.POINTER(I), P]),
     "synim_misreg_unconverged": (I, [P, C.POINTER(C.c_int32), P]),
+    "synim_misreg_set_polls": (I, [P, I]),
     "synim_misreg_destroy": (None, [P]),
     "synim_im_candidates": (I, [C.POINTER(SynimWfs), C.POINTER(SynimAffine), C.POINTER(I), I,
                                 C.POINTER(I)]),

@@ -42,3 +42,26 @@ def test_estimates_repeat(gpu_lib, copies):
     perm = torch.randperm(10 * copies, generator=torch.Generator().manual_seed(1)).cuda()
     b, ib = m.infer(s[perm].contiguous(), use_graph=False)
     assert torch.equal(b, a[perm]) and torch.equal(ib, ia[perm])
+
+
+@pytest.mark.parametrize("copies", [1, 2])
+def test_workgroups_that_stop_waiting(gpu_lib, copies):
+    """Split samples whose workgroups give up waiting for each other (after one poll)
+    are finished in one workgroup: the same iterations, the same count of
+    unconverged samples, estimates within the 1e-6 the two forms' orders of
+    summation leave between samples that hop."""
+    import torch
+    S = gpu_lib
+    m, s = _fit(S, copies)
+    a, ia = m.infer(s, use_graph=False)
+    bad = m.unconverged()
+    lib = S.load()
+    assert lib.synim_misreg_set_polls(None, 1) == -1
+    assert lib.synim_misreg_set_polls(m._h, 0) == -3
+    assert lib.synim_misreg_set_polls(m._h, 1) == 0
+    out = (torch.empty_like(a), torch.empty_like(ia))
+    for graph in (False, True, True):
+        b, ib = m.infer(s, use_graph=graph, out=out)
+        torch.cuda.synchronize()
+        assert torch.equal(ib, ia) and m.unconverged() == bad
+        assert (b - a).abs().max().item() <= 1e-6
