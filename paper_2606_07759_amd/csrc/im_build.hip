@@ -348,8 +348,12 @@ __device__ __forceinline__ bool plan_table_entry(const PlanJob& J, const MapD& m
   const double dx = (double)(sub.origin.x + c) - m.b0, dy = (double)(sub.origin.y + r) - m.b1;
   const double qx = q.a00 * dx + q.a01 * dy;
   const double qy = q.a10 * dx + q.a11 * dy;
-  const int xl = max(-1, (int)ceil(qx - q.rx) - sx0), xh = min(p, (int)floor(qx + q.rx) - sx0);
-  const int yl = max(-1, (int)ceil(qy - q.ry) - sy0), yh = min(p, (int)floor(qy + q.ry) - sy0);
+  // (clamped before the subtraction: a map that shrinks the grid onto one cell
+  // reaches back over more pixels than an int holds)
+  const int xl = max(sx0 - 1, (int)ceil(qx - q.rx)) - sx0;
+  const int yl = max(sy0 - 1, (int)ceil(qy - q.ry)) - sy0;
+  const int xh = max(sx0 - 2, min(sx0 + p, (int)floor(qx + q.rx))) - sx0;
+  const int yh = max(sy0 - 2, min(sy0 + p, (int)floor(qy + q.ry))) - sy0;
   const int n_planes = MULTI ? J.n_planes : 1;
   constexpr int NP = MULTI ? 5 : 1;
   double acc[NP][2];
