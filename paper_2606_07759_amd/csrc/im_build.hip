@@ -1512,12 +1512,14 @@ bool whole_vectors(const synim_wfs& w, const synim_affine& A, int pad, int PW, i
 
 int launch_stream(const Plan& P, const synim_wfs& w, const synim_affine& A, const float* ifs,
                   int n_act, int H_in, int W_in, int plane0, int nplanes, float* out,
-                  const float* grad, hipStream_t st, int* grid_out = nullptr, int pad = 0) {
+                  const float* grad, hipStream_t st, int* grid_out = nullptr, int pad = 0,
+                  bool planned_here = true) {
   const int nv = w.n_valid;
   const Dims& d = P.d;
   const Variant& v = *d.var;
+  // (the rows a plan of an earlier call stages may lie elsewhere than A puts them)
   const bool vec4 = (reinterpret_cast<uintptr_t>(ifs) & 3) == 0 &&
-                    whole_vectors(w, A, pad, d.PW, W_in);
+                    (planned_here ? whole_vectors(w, A, pad, d.PW, W_in) : W_in % 4 == 0);
   if ((long)H_in * W_in * 4 > INT_MAX) return SYNIM_E_SHAPE;   // 32-bit DMA offsets
   StreamFn fn = pick_fn(v, vec4, grad != nullptr);
   // planes of a Jacobian in pairs, where the variant has a kernel for them
@@ -1996,7 +1998,7 @@ extern "C" int synim_im_apply(const float* ifs, int n_act, int H_in, int W_in,
   if (ws_bytes < P.L.total) return SYNIM_E_WORKSPACE;
   P.ws = static_cast<char*>(const_cast<void*>(ws));
   return launch_stream(P, *wfs, *A, ifs, n_act, H_in, W_in, plane, 1, out, nullptr,
-                       (hipStream_t)stream);
+                       (hipStream_t)stream, nullptr, 0, false);
 }
 
 extern "C" int synim_plan_status(const void* ws, int* host_out, void* stream) {
