@@ -1449,15 +1449,32 @@ int batch_chunk(const std::vector<int>& n_act, const std::vector<int>& tiles, in
 }
 
 // Chunks of a single-pair launch: as many as give every workgroup the same
-// number of items (one, for a stack that a workgroup's share of stays within
-// CHUNK_MAX actuators), a multiple of 8 so that every XCD queue holds the same,
-// the actuators split evenly over them (lengths differ by at most one).
+// number of items, the actuators split evenly over them (lengths differ by at
+// most one).  One item where a workgroup's share stays within CHUNK_MAX actuators;
+// from eight such chunks on a multiple of 8, so that every XCD queue holds the
+// same.  A launch of several rounds has its items in the XCDs' queues, and takes at
+// least 8 chunks (60x60 subapertures of 8 px, the four planes of a VJP of 40
+// actuators: 199 us with the two chunks that fill its workgroups evenly, 103 with
+// 8) and of the multiples of 8 below and above the even number the lower, unless
+// the fullest queue is done with the upper a tenth sooner, an item's set-up
+// counted as ITEM_SETUP actuators (the same sensor's IM of 373 actuators: 121 us
+// with 8 chunks, counted 102, 102 with 16, counted 84).  Closer than that the count
+// is no guide, as it knows nothing of tiles outside the pupil (80x80 of 6 px, a
+// Jacobian of 260 actuators: 179 us with 8, counted 148, 201 with 16, counted 147).
+constexpr int ITEM_SETUP = 4;
 int chunks_for(int n_act, int n_tiles, int G) {
   const long per_round = std::max(1, G / n_tiles);
   const long rounds = (n_act + per_round * CHUNK_MAX - 1) / (per_round * CHUNK_MAX);
-  long nc = per_round * rounds;
-  if (nc > 8) nc = nc / 8 * 8;
-  return (int)std::min<long>(nc, n_act);
+  const long even = per_round * rounds;
+  const long below = std::min<long>(even > 8 ? even / 8 * 8 : even, n_act);
+  if (below * n_tiles <= G) return (int)below;   // one round
+  auto cost = [&](long nc) {   // actuators the last workgroup of the fullest queue streams
+    const long wgs = std::max(1, G / 8), items = (nc + 7) / 8 * n_tiles;
+    return (items + wgs - 1) / wgs * ((n_act + nc - 1) / nc + ITEM_SETUP);
+  };
+  const long lower = std::min<long>(std::max(8L, even / 8 * 8), n_act);
+  const long upper = std::min<long>(lower + 8, n_act);
+  return (int)(10 * cost(upper) <= 9 * cost(lower) ? upper : lower);
 }
 
 StreamFn pick_fn(const Variant& v, bool vec4, bool vjp, bool batch = false) {
