@@ -845,6 +845,13 @@ __global__ __launch_bounds__(256) void plan_rows_shared_kernel(
       rows_out, tile_info, status, true);
 }
 
+// The status words of n jobs, and 16 more (nullable).
+__global__ void clear_status_kernel(const PlanJob* __restrict__ jobs, int n, int* more) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 16 * n) jobs[i / 16].status[i % 16] = 0;
+  if (more != nullptr && i < 16) more[i] = 0;
+}
+
 __global__ void zero_ints_kernel(int* __restrict__ p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
@@ -2501,10 +2508,12 @@ int batch_bind(synim_batch* b, const Variant& v, hipStream_t st) {
                                  b->jgroups_host.size() * sizeof(int2), hipMemcpyHostToDevice,
                                  st));
   }
-  // a batch that has not run yet has nothing to report
-  for (const auto& P : b->plans)
-    SYNIM_HIP_TRY(hipMemsetAsync(P.status(), 0, 16 * sizeof(int), st));
-  if (b->shared) SYNIM_HIP_TRY(hipMemsetAsync(b->ws + b->off_jstatus, 0, 16 * sizeof(int), st));
+  // a batch that has not run yet has nothing to report (one launch: a call per pair
+  // took 2.9 of the 7.0 ms of making a fit context for 1000 samples)
+  hipLaunchKernelGGL(clear_status_kernel, dim3((unsigned)((16L * np + 255) / 256)), dim3(256), 0, st,
+                     reinterpret_cast<const PlanJob*>(b->ws + b->off_jobs), np,
+                     b->shared ? reinterpret_cast<int*>(b->ws + b->off_jstatus) : nullptr);
+  SYNIM_HIP_TRY(hipGetLastError());
   SYNIM_HIP_TRY(hipStreamSynchronize(st));   // the host vectors go out of scope
   return SYNIM_OK;
 }
