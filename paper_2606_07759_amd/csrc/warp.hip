@@ -9,19 +9,22 @@ namespace synim {
 namespace {
 
 constexpr int WX = 128, WY = 2;   // a workgroup's output pixels
-constexpr int MOST = 8;           // IFs of a workgroup at most, in one pass
+constexpr int MOST = 8;           // IFs of a run at most, in one pass
 // What bounds the step is memory: each source pixel under the window once, the
 // window written.  A workgroup covers 128 x 2 output pixels of a run of IFs, its
 // FP64 source coordinates formed once and the taps of up to 8 IFs in flight.  1200
 // ELT IFs of 512^2 onto 482^2: runs of 4 IFs 0.95 ms, of 8 0.60, of 16 0.64, of 64
 // 0.70 (256 x 4 pixels: 0.65 with 8; runs of two, four separate taps waited for in
-// turn: 1.15).  Fewer IFs a run where there would be fewer than kMinBlocks
-// workgroups.
-// Consecutive workgroups go to the 8 XCDs in turn; each XCD takes every window
-// block of one run of IFs before the next run, so that the source rows
-// neighbouring blocks share, and the output lines they share, meet in its L2
-// (eight runs or more, in whole eights; fewer are spread over all XCDs).
-constexpr long kMinBlocks = 4096;
+// turn: 1.15).  Runs of up to 8 also where that makes few workgroups, as a
+// workgroup's coordinates cost more than the IFs (8 IFs onto 482^2: 6.0 us in one run,
+// 11.5 one by one; onto 82^2 no difference).
+// Consecutive workgroups go to the 8 XCDs in turn; from six runs on their number is
+// a multiple of 8, of even length, and each XCD takes every window block of one run
+// before its next, so that the source rows neighbouring blocks share, and the
+// output lines they share, meet in its L2 (64 IFs onto 482^2: 21 us, 31 spread over
+// all; fewer than six would leave XCDs idle).  Runs of equal length with a short
+// last one, one by one from 8 IFs on, took 16 us for 9 IFs onto 386^2 (two on the
+// first XCD), now 6.7.
 
 // Two neighbouring taps (any float alignment: one 8-byte load).
 struct __attribute__((packed, aligned(4))) Pair {
@@ -34,17 +37,18 @@ struct __attribute__((packed, aligned(4))) Pair {
 template <int UNR>
 __global__ __launch_bounds__(WX* WY) void warp_kernel(const float* __restrict__ ifs, int n,
                                                       int H_in, int W_in, MapD m, int H_out,
-                                                      int W_out, int halo, int if_per_block,
-                                                      int by_xcd,
+                                                      int W_out, int halo, int if_per_run,
+                                                      int longer, int by_xcd,
                                                       float* __restrict__ out,
                                                       int32_t* __restrict__ oob) {
   const int Wh = W_out + 2 * halo, Hh = H_out + 2 * halo;
   const int bx = (Wh + WX - 1) / WX, by = (Hh + WY - 1) / WY, nxy = bx * by;
   const int s = by_xcd ? blockIdx.x >> 3 : blockIdx.x;
   const int run = by_xcd ? s / nxy * 8 + (blockIdx.x & 7) : s / nxy, xy = s % nxy;
-  const int i_begin = run * if_per_block;
-  if (i_begin >= n) return;
-  const int i_end = min(n, i_begin + if_per_block);
+  // the IFs of this block's run: the first `longer` runs have one more
+  const int i_begin = run * if_per_run + min(run, longer);
+  const int i_end = min(n, i_begin + if_per_run + (run < longer ? 1 : 0));
+  if (i_begin >= i_end) return;
   const int ox = xy % bx * WX + (threadIdx.x % WX);
   const int oy = xy / bx * WY + (threadIdx.x / WX);
   const bool active = ox < Wh && oy < Hh;
@@ -138,13 +142,10 @@ extern "C" int synim_affine_warp(const float* ifs, int n, int H_in, int W_in,
   const int Wh = W_out + 2 * halo, Hh = H_out + 2 * halo;
   const int bx = (Wh + WX - 1) / WX, by = (Hh + WY - 1) / WY;
   const long xy = (long)bx * by;
-  long ipb = std::min<long>(n, std::clamp((long)n * xy / kMinBlocks, 1L, (long)MOST));
-  long runs = (n + ipb - 1) / ipb;
-  const bool by_xcd = runs >= 8;
-  if (by_xcd) {
-    runs = (runs + 7) / 8 * 8;   // an equal number for each XCD
-    ipb = (n + runs - 1) / runs;
-  }
+  long runs = ((long)n + MOST - 1) / MOST;
+  const bool by_xcd = runs >= 6;
+  if (by_xcd) runs = (runs + 7) / 8 * 8;   // an equal number for each XCD
+  const long ipb = (n + runs - 1) / runs;
   const long blocks = runs * xy;
   if (blocks > 0x7fffffffL) return SYNIM_E_SHAPE;
   const auto kernel = ipb > 4   ? warp_kernel<8>
@@ -152,8 +153,8 @@ extern "C" int synim_affine_warp(const float* ifs, int n, int H_in, int W_in,
                       : ipb > 1 ? warp_kernel<2>
                                 : warp_kernel<1>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(WX * WY), 0, (hipStream_t)stream, ifs,
-                     n, H_in, W_in, to_map(*A), H_out, W_out, halo, (int)ipb,
-                     by_xcd ? 1 : 0, out, oob_count);
+                     n, H_in, W_in, to_map(*A), H_out, W_out, halo, (int)(n / runs),
+                     (int)(n % runs), by_xcd ? 1 : 0, out, oob_count);
   SYNIM_HIP_TRY(hipGetLastError());
   return SYNIM_OK;
 }
