@@ -35,20 +35,27 @@ __device__ __forceinline__ float from_beside(float at_edge, float v) {
 // bounds it is the cache's accesses and the vector instructions, each about two
 // thirds busy (four separate loads and a pupil byte per pixel: 0.40 ms for 1200
 // maps of 482 x 482; a 16-byte load that overlaps its neighbours' took a cache
-// access for nearly every lane, 0.33).  A wave whose columns lie outside the
-// pupil over a subaperture row reads nothing there, one wholly inside it tests
-// no pupil bits.
+// access for nearly every lane, 0.33), at small stacks the chain of a wave's rows.
+// U pixel rows' loads are in flight, a divisor of p where there is one (RAGGED: none,
+// the last rows of a subaperture are loaded and left out), and the pupil comes as a
+// word of bits for them: with a test, a branch and a count a row in one kernel for
+// every p, one map of 2 x 2 subapertures of 32 pixels took 11.5 us, now 7.2 (8.2
+// with a column a thread), of 16 x 16 of 24 11.0, now 7.5.
+// A wave whose columns lie outside the pupil over a subaperture row reads nothing
+// there, one wholly inside it tests no pupil bits.
 // The pupil-masked differences and the pupil count are summed down each subaperture
 // row; the per-subaperture sums then add those column sums in column order (a
 // fixed order, so results are bit-reproducible).  The pupil of a thread's columns
-// is kept as bits over the run of maps where the group has at most 64 pixel rows.
+// is kept as bits over the run of maps.
 // Each XCD takes all blocks of a map before its next, so that shared rows and lines
-// meet in its L2.  Now 0.29.
+// meet in its L2.  Now 0.25.
+template <int U, bool RAGGED>
 __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict__ phase, int n,
                                                         const int32_t* __restrict__ valid,
                                                         const uint8_t* __restrict__ pupil,
                                                         int n_sub_x, int n_sub_y, int p, int nv,
-                                                        int subs_per_block, int maps_per_block,
+                                                        int subs_per_block, int maps_per_run,
+                                                        int longer,
                                                         int by_xcd, int srows,
                                                         float* __restrict__ slopes) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, T = blockDim.x;
@@ -61,8 +68,11 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
   const int n_blk = (n_sub_y + srows - 1) / srows * n_runs;
   const int sb = by_xcd ? blockIdx.x >> 3 : blockIdx.x;
   const int blk = sb % n_blk;
-  const int i0 = (by_xcd ? sb / n_blk * 8 + (blockIdx.x & 7) : sb / n_blk) * maps_per_block;
-  if (i0 >= n) return;
+  // the maps of this block's run: the first `longer` runs have one more
+  const int run = by_xcd ? sb / n_blk * 8 + (blockIdx.x & 7) : sb / n_blk;
+  const int i0 = run * maps_per_run + min(run, longer);
+  const int i_end = min(n, i0 + maps_per_run + (run < longer ? 1 : 0));
+  if (i0 >= i_end) return;
   const int grp = blk / n_runs;
   const int u0 = (blk - grp * n_runs) * subs_per_block;
   const int W = n_sub_x * p, H = n_sub_y * p;
@@ -84,15 +94,14 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
   // this thread's columns: on (the first lies in the block), two (the second too)
   const bool on = 2 * t < nu * p, two = 2 * t + 1 < nu * p;
   const int y_beg = v0 * p, y_end = v_end * p;
-  const bool keep = y_end - y_beg <= 64;
-  const bool wave_on = __any(on);
   // offsets in a haloed row: of column x (columns past W are read as W - 1, W), of
   // the column before the wave's first and after its last
   const int at = 1 + min(x, W - 1);
   const bool edge = lane == 0 || (lane == 63 && x + 2 <= W);
   const int at_outer = lane == 0 ? min(x, W) : min(x + 3, W + 1);
-  unsigned long long in0 = 0, in1 = 0;   // pupil bits of rows y_beg.. of the two columns
-  if (keep && on) {
+  // pupil bits of rows y_beg.. of the two columns (at most 64 rows: the host's rule)
+  unsigned long long in0 = 0, in1 = 0;
+  if (on) {
     const int second = two ? 1 : 0;
     for (int y = y_beg; y < y_end; y += 8) {
       uint8_t q[8][2];
@@ -102,15 +111,18 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
         q[k][0] = at[0];
         q[k][1] = at[second];
       }
+      unsigned m0 = 0, m1 = 0;
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (y + k < y_end) {
-          in0 |= (unsigned long long)(q[k][0] != 0) << (y + k - y_beg);
-          in1 |= (unsigned long long)(two && q[k][1] != 0) << (y + k - y_beg);
-        }
+      for (int k = 0; k < 8; ++k) {
+        m0 |= (q[k][0] != 0 ? 1u : 0u) << k;
+        m1 |= (q[k][1] != 0 ? 1u : 0u) << k;
+      }
+      const unsigned there = (1u << min(8, y_end - y)) - 1;
+      in0 |= (unsigned long long)(m0 & there) << (y - y_beg);
+      in1 |= (unsigned long long)(two ? m1 & there : 0u) << (y - y_beg);
     }
   }
-  for (int i = i0; i < min(n, i0 + maps_per_block); ++i) {
+  for (int i = i0; i < i_end; ++i) {
     const float* ph = phase + (size_t)i * (size_t)(H + 2) * (size_t)Wh;
     float* out = slopes + (size_t)i * 2 * nv;
     // pixel row y (haloed row y + 1): its own two columns per lane, and one of the
@@ -133,11 +145,8 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
     for (int v = v0; v < v_end; v += 2) {
       const int nr = min(2, v_end - v);
       float gx[2][2] = {}, gy[2][2] = {}, cnt[2][2] = {};   // [subaperture row][column]
-      // subaperture row r, U pixel rows' loads in flight (a divisor of p where there
-      // is one, so that no row is loaded twice); FULL: all of the wave's pixels
-      // are in the pupil
-      auto walk = [&](int r, auto uc, auto full) {
-        constexpr int U = decltype(uc)::value;
+      // subaperture row r; FULL: all of the wave's pixels are in the pupil
+      auto walk = [&](int r, auto full) {
         constexpr bool FULL = decltype(full)::value;
         const int ya = (v + r) * p;
         if (!have) {
@@ -146,7 +155,8 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
           prev = make(pv, 0.f);
           cur = make(pc, e);
         }
-        float sx0 = 0.f, sx1 = 0.f, sy0 = 0.f, sy1 = 0.f, c0 = 0.f, c1 = 0.f;
+        float sx0 = 0.f, sx1 = 0.f, sy0 = 0.f, sy1 = 0.f;
+        int c0 = 0, c1 = 0;
         for (int d0 = 0; d0 < p; d0 += U) {
           Pair nx[U];
           float e[U];
@@ -158,26 +168,21 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
 #pragma unroll
             for (int u = 0; u < U; ++u) e[u] = outer(min(ya + d0 + u + 1, y_end));
           }
+          unsigned m0 = ~0u, m1 = ~0u;
+          if (!FULL) {
+            m0 = (unsigned)(in0 >> (ya + d0 - y_beg));
+            m1 = (unsigned)(in1 >> (ya + d0 - y_beg));
+            const unsigned here = (1u << min(U, p - d0)) - 1;
+            c0 += __popc(m0 & here);
+            c1 += __popc(m1 & here);
+          }
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            if (d0 + u >= p) break;
-            const int y = ya + d0 + u;
-            bool a = true, b = true;
-            if (!FULL) {
-              if (keep) {
-                a = (in0 >> (y - y_beg)) & 1;
-                b = (in1 >> (y - y_beg)) & 1;
-              } else {
-                const uint8_t* q = pupil + (size_t)y * W + (on ? x : 0);
-                a = on && q[0] != 0;
-                b = two && q[1] != 0;
-              }
-              c0 += a ? 1.f : 0.f;
-              c1 += b ? 1.f : 0.f;
-            }
+            if (RAGGED && d0 + u >= p) break;
             const Row next = make(nx[u], e[u]);
             const float ex0 = 0.5f * (cur.c1 - cur.left), ex1 = 0.5f * (cur.right - cur.c0);
             const float ey0 = 0.5f * (next.c0 - prev.c0), ey1 = 0.5f * (next.c1 - prev.c1);
+            const bool a = FULL || (m0 >> u & 1), b = FULL || (m1 >> u & 1);
             sx0 += a ? ex0 : 0.f;
             sy0 += a ? ey0 : 0.f;
             sx1 += b ? ex1 : 0.f;
@@ -190,31 +195,20 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
         gx[r][1] = sx1;
         gy[r][0] = sy0;
         gy[r][1] = sy1;
-        cnt[r][0] = FULL ? (float)p : c0;
-        cnt[r][1] = FULL ? (float)p : c1;
+        cnt[r][0] = FULL ? (float)p : (float)c0;
+        cnt[r][1] = FULL ? (float)p : (float)c1;
       };
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         if (r >= nr) break;
         // how the wave's columns lie over this row's pixels: outside the pupil
         // nothing is read
-        bool some = wave_on, full = false;
-        if (keep) {
-          const unsigned long long px = (p < 64 ? (1ull << p) - 1 : ~0ull)
-                                        << ((v + r) * p - y_beg);
-          some = __any(((in0 | in1) & px) != 0);
-          full = __all(!on || (two && (in0 & in1 & px) == px));
-        }
+        const unsigned long long px = (p < 64 ? (1ull << p) - 1 : ~0ull) << ((v + r) * p - y_beg);
+        const bool some = __any(((in0 | in1) & px) != 0);
+        const bool full = __all(!on || (two && (in0 & in1 & px) == px));
         if (some) {   // (the wave as a whole: its lanes read each other)
-          auto form = [&](auto uc) {
-            if (full) walk(r, uc, std::true_type{});
-            else walk(r, uc, std::false_type{});
-          };
-          if (p % 6 == 0) form(std::integral_constant<int, 6>{});
-          else if (p % 7 == 0) form(std::integral_constant<int, 7>{});
-          else if (p % 5 == 0) form(std::integral_constant<int, 5>{});
-          else if (p % 3 == 0) form(std::integral_constant<int, 3>{});
-          else form(std::integral_constant<int, 4>{});
+          if (full) walk(r, std::true_type{});
+          else walk(r, std::false_type{});
         }
         have = some;
       }
@@ -231,10 +225,12 @@ __global__ __launch_bounds__(SBLOCK) void slopes_kernel(const float* __restrict_
         const int kk = s_kk[(v - v0 + r) * nu + u];
         if (kk < 0) continue;
         float sx = 0.f, sy = 0.f, cn = 0.f;
-        for (int c = u * p; c < u * p + p; ++c) {
-          sx += sum_at(0, r, c);
-          sy += sum_at(1, r, c);
-          cn += sum_at(2, r, c);
+        const float* const sums = &sum_at(0, r, u * p);
+#pragma unroll 4
+        for (int c = 0; c < p; ++c) {
+          sx += sums[c];
+          sy += sums[4 * T + c];
+          cn += sums[8 * T + c];
         }
         out[kk] = cn > 0.f ? sx / cn : 0.f;
         out[nv + kk] = cn > 0.f ? sy / cn : 0.f;
@@ -257,33 +253,39 @@ extern "C" int synim_sa_slopes(const float* phase, int n, const synim_wfs* wfs, 
   // 128, 256 threads within 3% of each other on 480 columns)
   const int T = std::min(SBLOCK, ((wfs->n_sub_x * wfs->p + 1) / 2 + 63) / 64 * 64);
   const int spb = std::min(wfs->n_sub_x, 2 * T / wfs->p);
-  // Subaperture rows of a workgroup: four read the fewest rows twice, fewer make
-  // more and shorter chains of loads.  Four where that gives 64 waves a CU or more
-  // (1200 maps of 480 columns, 1 / 2 / 4 / 8 rows: 328, 294, 286, 294 us), else two
-  // (300 of 360: 47, 45, 51, 59; 500 of 350 with 10 pixels: 65, 63, 73, 100), else
-  // one (55 of 168: 7.7, 9.3, 15, 24).
-  int srows = SROWS;
-  while (srows > 1 && (long)n * ((wfs->n_sub_y + srows - 1) / srows) *
-                          ((wfs->n_sub_x + spb - 1) / spb) * (T / 64) < 16384)
-    srows /= 2;
-  const long bx = (long)((wfs->n_sub_y + srows - 1) / srows) * ((wfs->n_sub_x + spb - 1) / spb);
-  // 48 waves per CU, each a run of maps (1200 maps of 480 columns, with eight rows
-  // and 16-byte loads: runs of 2 to 8 maps 347 to 327 us, of 16 363, where the last
-  // round of workgroups is short); eight runs or more in whole eights, an equal
-  // number for each XCD, fewer spread over all
-  long mpb = std::min<long>(n, std::max(1L, n * bx * (T / 64) / 12288));
-  long runs = (n + mpb - 1) / mpb;
+  // Workgroups that are resident together (20 waves a CU) in one round, each with
+  // as many maps as that takes, up to 8, and two or four subaperture rows, which read
+  // fewer rows twice, where one would take more than two rounds and the chain of pixel
+  // rows is no longer than 20.  Maps of 80 x 80 subapertures of 6 pixels, 24 / 64 / 200
+  // / 1200 of them: 8.8, 17, 35, 254 us; with rows and maps a workgroup chosen for 48 to
+  // 64 waves a CU 13, 28, 50, 286, with one map and eight rows each 17, 24, 55, 394.
+  // (Rooms of 12 to 28 waves, chains of 12 to 24 rows: 0.3 to 2% slower over maps of 23
+  // sensors.)  Runs of even length; eight or more in whole eights, an equal number
+  // for each XCD, fewer spread over all.
+  const int p = wfs->p;
+  const long cols = (wfs->n_sub_x + spb - 1) / spb, room = 256 * (20 / (T / 64));
+  auto blocks = [&](int rows) { return (wfs->n_sub_y + rows - 1) / rows * cols; };
+  int srows = 1;
+  while (2 * srows <= std::min(SROWS, wfs->n_sub_y) && 2 * srows * p <= 20 &&
+         n * blocks(srows) > 2 * room)
+    srows *= 2;
+  const long bx = blocks(srows), mpr = std::clamp((n * bx + room - 1) / room, 1L, 8L);
+  long runs = (n + mpr - 1) / mpr;
   const bool by_xcd = runs >= 8;
-  if (by_xcd) {
-    runs = (runs + 7) / 8 * 8;
-    mpb = (n + runs - 1) / runs;
-  }
+  if (by_xcd) runs = (runs + 7) / 8 * 8;
   if (runs * bx > 0x7fffffffL) return SYNIM_E_SHAPE;
-  hipLaunchKernelGGL(slopes_kernel, dim3((unsigned)(runs * bx)),
+  const auto kernel = p % 6 == 0   ? slopes_kernel<6, false>
+                      : p % 7 == 0 ? slopes_kernel<7, false>
+                      : p % 5 == 0 ? slopes_kernel<5, false>
+                      : p % 8 == 0 ? slopes_kernel<8, false>
+                      : p % 4 == 0 ? slopes_kernel<4, false>
+                      : p % 3 == 0 ? slopes_kernel<3, false>
+                                   : slopes_kernel<4, true>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(runs * bx)),
                      dim3(T),
                      (12 * T + SROWS * spb) * sizeof(float),
                      (hipStream_t)stream, phase, n, wfs->valid_idx, wfs->pupil, wfs->n_sub_x,
-                     wfs->n_sub_y, wfs->p, wfs->n_valid, spb, (int)mpb, by_xcd ? 1 : 0, srows, slopes);
+                     wfs->n_sub_y, wfs->p, wfs->n_valid, spb, (int)(n / runs), (int)(n % runs), by_xcd ? 1 : 0, srows, slopes);
   SYNIM_HIP_TRY(hipGetLastError());
   return SYNIM_OK;
 }
