@@ -82,9 +82,10 @@ __device__ double proj_sample(const SampleArgs& g, long row, int a) {
 
 // Marks the steps of PK rows in which a lane of the wave, whose first lane holds
 // matrix row `row`, a multiple of 64, has a non-zero sample of column col (nz: the
-// lanes that do).  A word that has the bits already is left alone: waves of other
-// functions and of the same rows share it, and atomics on one address are served
-// one after another.
+// lanes that do).  LOOK: a word that has the bits already is left alone, where the
+// waves of many functions mark the same rows: atomics on one address are served one
+// after another.  (Without need the look costs its latency at each wave's end.)
+template <bool LOOK>
 __device__ __forceinline__ void mark_rows(const SampleArgs& g, long col, long row,
                                           unsigned long long nz) {
   unsigned long long m = 0;
@@ -93,7 +94,7 @@ __device__ __forceinline__ void mark_rows(const SampleArgs& g, long col, long ro
     if ((nz >> (q * PK)) & ((1ull << PK) - 1)) m |= 1ull << q;
   m <<= row / PK % 64;
   unsigned long long* word = g.occ + col / PT * g.words + row / (64 * PK);
-  if ((__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
+  if (!LOOK || (__hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & m) != m)
     atomicOr(word, m);
 }
 
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(256) void proj_sample_kernel(SampleArgs g) {
   if (g.occ == nullptr) return;
   const unsigned long long nz = __ballot(out != 0.0);
   if (!(fabs(out) <= DBL_MAX)) *g.wild = 1;
-  if ((threadIdx.x & 63) == 0) mark_rows(g, g.col0 + a, row, nz);
+  if ((threadIdx.x & 63) == 0) mark_rows<true>(g, g.col0 + a, row, nz);
 }
 
 // A row's sample is linear in the function, with weights that depend on the row
@@ -217,7 +218,7 @@ __global__ __launch_bounds__(256) void proj_window_kernel(SampleArgs g, int n_rb
   if (g.occ == nullptr) return;
   const unsigned long long bits = __ballot(nz);
   if (wild) *g.wild = 1;
-  if ((threadIdx.x & 63) == 0 && bits != 0) mark_rows(g, g.col0 + a_begin, row, bits);
+  if ((threadIdx.x & 63) == 0 && bits != 0) mark_rows<false>(g, g.col0 + a_begin, row, bits);
 }
 
 // ---------------------------------------------------------------- FP64 GEMM
