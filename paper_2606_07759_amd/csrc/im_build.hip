@@ -533,11 +533,15 @@ struct ClearWords {
 // of 77 actuators on them 38.8, then 32.3, now 26).  Nothing is summed over workgroups here: a
 // subaperture's status bits and out-of-grid samples are left in `info` for
 // plan_rows.  MULTI: some job has derivative planes (n_planes > 1).
-constexpr int PLAN_BLOCK = 256, PLAN_SUBS = 8;   // threads, subapertures at most
+// Threads for patches of at most half as many entries, threads at most (the largest
+// patch, 24 x 24; with 256 each took two of 24 x 20 entries in turn, and the
+// telescoping-sum build of 52 subapertures 124 us, now 75), subapertures at most.
+constexpr int PLAN_BLOCK = 256, PLAN_MOST = 576, PLAN_SUBS = 8;
 // SAMPLES: every job's samples fit the table (plan_table), no edge repair or
 // telescoping sums.
-template <bool MULTI, bool TABLE, bool SAMPLES>
-__global__ __launch_bounds__(PLAN_BLOCK) void plan_weights_kernel(
+// MOST: threads at most (registers are shared out for them).
+template <bool MULTI, bool TABLE, bool SAMPLES, int MOST = PLAN_BLOCK>
+__global__ __launch_bounds__(MOST) void plan_weights_kernel(
     PlanJob one, const PlanJob* __restrict__ jobs, int spb, ClearWords z) {
   const PlanJob& J = job_of<TABLE>(one, jobs);
   __shared__ SubPlan s_sub[PLAN_SUBS];
@@ -1358,18 +1362,31 @@ int enqueue_plan_kernels(const PlanJob& one, const PlanJob* jobs_dev, int n, int
   for (int j0 = 0; j0 < n; j0 += 65535) {
     const int nj = std::min(65535, n - j0);
     const PlanJob* jt = TABLE ? jobs_dev + j0 : nullptr;
-    // whole waves that a patch's entries fill in equal passes
-    const int passes = (max_e + PLAN_BLOCK - 1) / PLAN_BLOCK;
-    const int T = max_e <= PLAN_BLOCK / 2 ? PLAN_BLOCK
-                                          : ((max_e + passes - 1) / passes + 63) / 64 * 64;
+    // whole waves that a patch's entries fill in equal passes: one where the launch
+    // holds 16 waves a CU or less (but for derivative planes without the table, whose
+    // registers allow fewer threads), else of up to PLAN_BLOCK threads (860
+    // subapertures of 24 x 24 entries: telescoping sums 323 us, 421 in one pass)
+    auto threads = [&](bool one_pass) {
+      if (max_e <= PLAN_BLOCK / 2) return PLAN_BLOCK;
+      if (one_pass && (long)max_nv * nj * ((max_e + 63) / 64) <= 16L * 256)
+        return (max_e + 63) / 64 * 64;
+      const int passes = (max_e + PLAN_BLOCK - 1) / PLAN_BLOCK;
+      return ((max_e + passes - 1) / passes + 63) / 64 * 64;
+    };
+    int T = threads(true);
     const int spb = std::clamp(T / max_e, 1, PLAN_SUBS);
     const dim3 wgrid((unsigned)((max_nv + spb - 1) / spb), nj);
     const bool samples = (TABLE || (!one.dm_mask && one.engine == ENGINE_CD)) &&
                          spb * (max_p + 2) * (max_p + 2) <= PLAN_SAMPLES;
-    const auto kernel = planes > 1 ? (samples ? plan_weights_kernel<true, TABLE, true>
-                                              : plan_weights_kernel<true, TABLE, false>)
-                                   : (samples ? plan_weights_kernel<false, TABLE, true>
-                                              : plan_weights_kernel<false, TABLE, false>);
+    if (planes > 1 && !samples) T = threads(false);
+    const auto kernel =
+        T > PLAN_BLOCK ? (planes > 1 ? plan_weights_kernel<true, TABLE, true, PLAN_MOST>
+                          : samples  ? plan_weights_kernel<false, TABLE, true, PLAN_MOST>
+                                     : plan_weights_kernel<false, TABLE, false, PLAN_MOST>)
+        : planes > 1   ? (samples ? plan_weights_kernel<true, TABLE, true>
+                                  : plan_weights_kernel<true, TABLE, false>)
+                       : (samples ? plan_weights_kernel<false, TABLE, true>
+                                  : plan_weights_kernel<false, TABLE, false>);
     hipLaunchKernelGGL(kernel, wgrid, dim3(T), 0, st, one, jt, spb, j0 == 0 ? clear : ClearWords{});
     SYNIM_HIP_TRY(hipGetLastError());
     if (!tiles) continue;
