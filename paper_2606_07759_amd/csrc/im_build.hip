@@ -645,7 +645,7 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
   if (NS > MAX_SLOTS) {
     if (tid == 0) {
       atomicOr(status, 2);   // tile skipped: its slopes stay unwritten
-      tile_info[t] = make_int4(0, 0, 0, 0);
+      tile_info[t] = make_int4(0, 0, 0, -1);
     }
     return;
   }
@@ -684,7 +684,7 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
   if (bh > BHmax || bh > MAX_TILE_ROWS) {
     if (tid == 0) {
       atomicOr(status, 2);
-      tile_info[t] = make_int4(0, 0, 0, 0);
+      tile_info[t] = make_int4(0, 0, 0, -1);
     }
     return;
   }
@@ -733,7 +733,7 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
     if (tid == 0) {
       if ((long)bh * pitch > cap_floats) {
         atomicOr(status, 2);   // tile skipped: its slopes stay unwritten
-        tile_info[t] = make_int4(0, 0, 0, 0);
+        tile_info[t] = make_int4(0, 0, 0, -1);
       } else {
         tile_info[t] = make_int4(y0, bh, X0, pitch);
         atomicAdd(status + 1, 1);
@@ -766,7 +766,7 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
     const int off = s_carry;
     if (off > cap_floats) {
       atomicOr(status, 2);   // tile skipped: its slopes stay unwritten
-      tile_info[t] = make_int4(0, 0, 0, 0);
+      tile_info[t] = make_int4(0, 0, 0, -1);
     } else {
       tile_info[t] = make_int4(y0, bh, off, 0);
       atomicAdd(status + 1, 1);   // non-empty tiles
