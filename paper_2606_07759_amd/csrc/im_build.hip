@@ -79,7 +79,7 @@ struct PlanJob {
   int2* info;                 // [nv] (status bits, samples outside the IF grid)
   float* weights;             // [plane][kk][2*PH*PW], in lane order (plan_weight_entry)
   int* slot_kk;               // [tile][NSLOT]
-  int4* tile_info;            // [tile] (y0, rows, packed floats, 0)
+  int4* tile_info;            // [tile] (y0, rows, packed floats, 0), see build_tile_rows
   int2* rows;                 // [tile][BHmax] (first column, packed offset)
   int* status;
   int* counters;              // the stream kernel's work and sync counters
@@ -613,8 +613,9 @@ __global__ __launch_bounds__(MOST) void plan_weights_kernel(
 
 // One workgroup per tile: the IF rows its patches touch, each trimmed to the
 // column interval those patches cover (aligned to 4 floats), packed one after
-// the other.  tile_info[t] = (y0, rows, packed floats, 0), rows = 0 for an empty
-// tile; rows[t*BHmax + r] = (first column of row r, packed offset of row r).
+// the other.  tile_info[t] = (y0, rows, packed floats, 0), rows = 0 for a tile
+// without a non-zero weight, (0, 0, 0, -1) for one that does not fit;
+// rows[t*BHmax + r] = (first column of row r, packed offset of row r).
 // Row table of tile t: slot_of(s) gives slot s's (origin, patch rows
 // holding a weight), or hr.x >= hr.y for an empty slot.  Writes rows[t*BHmax
 // + r], tile_info[t]; flags bit 1 of status[0] for a tile that does not fit,
@@ -2256,7 +2257,12 @@ int build_shared(synim_batch* b, const Variant& v) {
   // a pitch of 4 mod 8 floats, spread its lanes over the banks of one residue
   // mod 4, and that residue is its origin column's (the staged frame starts at
   // a multiple of 4).  The slots are therefore dealt to the half-wave groups
-  // with the four residues as even as the tile's subapertures allow.
+  // with the four residues as even as the tile's subapertures allow.  That
+  // covers the banks with eight lanes per subaperture (0.5 to 0.8 conflict
+  // cycles per LDS instruction), where a half wave holds four of them; with
+  // four lanes it holds eight, and their rows still collide (4.2 on the 12x12
+  // patches of six clocked sensors; a deal of its own for four lanes took a
+  // seventh of the conflicts and left the time as it was).
   const int HW = std::max(1, 32 / v.LPS);
   auto bank_order = [&](const Sl* in, size_t n) {
     std::vector<Sl> cls[4];

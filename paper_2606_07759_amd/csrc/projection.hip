@@ -390,7 +390,9 @@ int gemm(const GemmArgs& a, hipStream_t st) {
 // of steps: those with the most come first.  Where the tiles alone leave the chip
 // idle each is split into `parts` of equally many steps, added in order after.
 // The two products of 8171 x 94104 (lower half) and 8171 x 4107 x 94104: 180 and
-// 149 ms dense in 256 x 128 tiles, now 12 and 15.
+// 149 ms dense in 256 x 128 tiles, now 12 and 15.  Functions that are non-zero
+// everywhere have no step to skip: the whole of P_opt on that system takes 282 ms
+// (489 with the dense products and solves in blocks of 64).
 struct SkipArgs {
   int M, N, K;
   const double *X, *Y;         // X(k, m) = X[m ld + k], Y(k, n) = Y[n ld + k]
