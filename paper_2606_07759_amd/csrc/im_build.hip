@@ -613,11 +613,16 @@ __global__ __launch_bounds__(MOST) void plan_weights_kernel(
 
 // One workgroup per tile: the IF rows its patches touch, each trimmed to the
 // column interval those patches cover (aligned to 4 floats), packed one after
-// the other.  tile_info[t] = (y0, rows, packed floats, 0), rows = 0 for a tile
-// without a non-zero weight, (0, 0, 0, -1) for one that does not fit;
-// rows[t*BHmax + r] = (first column of row r, packed offset of row r).
-// Row table of tile t: slot_of(s) gives slot s's (origin, patch rows
-// holding a weight), or hr.x >= hr.y for an empty slot.  Writes rows[t*BHmax
+// the other.  tile_info[t] = (y0, rows, packed floats, 0), rows = 0 for an empty
+// tile; rows[t*BHmax + r] = (first column of row r, packed offset of row r).
+// Row table of tile t: slot_of(s) tells whether slot s holds a subaperture and
+// gives its (origin, patch rows holding a weight; hr.x >= hr.y: none does, its
+// pixels lie outside the pupil or the edge repair leaves none).  A tile of such
+// subapertures alone has one row above the IF grid, which the DMA fills with
+// zeros: their slopes are written, as 0, by the path of all others (a branch of
+// its own in the stream kernel cost scalar registers in every variant, and one
+// of them, 12x12 patches on rows of odd length, a wave per SIMD: 534 -> 674 us
+// for a batch of two sensors and 1200 IFs).  Writes rows[t*BHmax
 // + r], tile_info[t]; flags bit 1 of status[0] for a tile that does not fit,
 // counts non-empty tiles in status[1].  256 threads.
 // pitched: the rows are staged at one pitch per tile instead of packed, in
@@ -639,20 +644,21 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
   // per row: the slots' column span [s_lo, s_hi), then in place the staged
   // first column (s_lo) and width (s_hi)
   __shared__ int s_lo[MAX_TILE_ROWS], s_hi[MAX_TILE_ROWS];
-  __shared__ int s_ymin, s_ymax;
+  __shared__ int s_ymin, s_ymax, s_held;
   int* const s_x0 = s_lo;
   int* const s_w = s_hi;
   const int tid = threadIdx.x;
   if (NS > MAX_SLOTS) {
     if (tid == 0) {
       atomicOr(status, 2);   // tile skipped: its slopes stay unwritten
-      tile_info[t] = make_int4(0, 0, 0, -1);
+      tile_info[t] = make_int4(0, 0, 0, 0);
     }
     return;
   }
   if (tid == 0) {
     s_ymin = INT_MAX;
     s_ymax = INT_MIN;
+    s_held = 0;
   }
   for (int r = tid; r < MAX_TILE_ROWS; r += blockDim.x) {
     s_lo[r] = INT_MAX;
@@ -661,7 +667,7 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
   __syncthreads();
   for (int s = tid; s < NS; s += blockDim.x) {
     int2 o, hr;
-    slot_of(s, o, hr);
+    if (slot_of(s, o, hr)) s_held = 1;
     // rows [oy, oe) of the IF grid that the subaperture's weights touch
     int ox = INT_MIN, oy = INT_MIN, oe = INT_MIN;
     if (hr.x < hr.y) {
@@ -678,14 +684,20 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
   __syncthreads();
   const int y0 = s_ymin;
   if (y0 == INT_MAX) {
-    if (tid == 0) tile_info[t] = make_int4(0, 0, 0, 0);
+    if (tid == 0 && s_held == 0) tile_info[t] = make_int4(0, 0, 0, 0);
+    if (tid == 0 && s_held != 0) {
+      // a patch row's width and more, of no column (pitched) or of row -1
+      rows_out[(size_t)t * BHmax] = make_int2(0, 0);
+      tile_info[t] = pitched ? make_int4(-1, 1, 0, 36) : make_int4(-1, 1, 32, 0);
+      atomicAdd(status + 1, 1);
+    }
     return;
   }
   const int bh = s_ymax - y0;
   if (bh > BHmax || bh > MAX_TILE_ROWS) {
     if (tid == 0) {
       atomicOr(status, 2);
-      tile_info[t] = make_int4(0, 0, 0, -1);
+      tile_info[t] = make_int4(0, 0, 0, 0);
     }
     return;
   }
@@ -734,7 +746,7 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
     if (tid == 0) {
       if ((long)bh * pitch > cap_floats) {
         atomicOr(status, 2);   // tile skipped: its slopes stay unwritten
-        tile_info[t] = make_int4(0, 0, 0, -1);
+        tile_info[t] = make_int4(0, 0, 0, 0);
       } else {
         tile_info[t] = make_int4(y0, bh, X0, pitch);
         atomicAdd(status + 1, 1);
@@ -767,7 +779,7 @@ __device__ __forceinline__ void build_tile_rows(int t, int NS, int PW, int BHmax
     const int off = s_carry;
     if (off > cap_floats) {
       atomicOr(status, 2);   // tile skipped: its slopes stay unwritten
-      tile_info[t] = make_int4(0, 0, 0, -1);
+      tile_info[t] = make_int4(0, 0, 0, 0);
     } else {
       tile_info[t] = make_int4(y0, bh, off, 0);
       atomicAdd(status + 1, 1);   // non-empty tiles
@@ -816,6 +828,7 @@ __global__ __launch_bounds__(256) void plan_rows_kernel(PlanJob one,
           if (f.x != 0) atomicOr(&s_bits, f.x);
           if (f.y != 0) atomicAdd(&s_oob, f.y);
         }
+        return kk >= 0;
       },
       J.rows, J.tile_info, J.status);
   __syncthreads();
@@ -846,6 +859,7 @@ __global__ __launch_bounds__(256) void plan_rows_shared_kernel(
             if (f.y != 0) atomicAdd(J.status + 2, f.y);
           }
         }
+        return e >= 0;
       },
       rows_out, tile_info, status, true);
 }

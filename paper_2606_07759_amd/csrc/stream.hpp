@@ -91,14 +91,6 @@ struct StreamArgs {
   int one_round;
 };
 
-// Actuators [a0, a1) of a chunk: P.chunk of them, or (P.chunk == 0) an even split
-// of the actuators over P.n_chunks chunks.
-__device__ __forceinline__ void chunk_range(const PairDesc& P, int chunk_id, int& a0, int& a1) {
-  a0 = P.chunk > 0 ? chunk_id * P.chunk : (int)((long long)chunk_id * P.n_act / P.n_chunks);
-  a1 = P.chunk > 0 ? min(P.n_act, a0 + P.chunk)
-                   : (int)((long long)(chunk_id + 1) * P.n_act / P.n_chunks);
-}
-
 typedef __attribute__((address_space(3))) void lds_void_t;
 
 // s_waitcnt immediates (gfx9 encoding) that wait on vmcnt only.
@@ -409,31 +401,7 @@ im_stream_kernel(StreamArgs g) {
     const int plane_bytes = P.H_in * P.W_in * 4;
     const size_t plane_in = (size_t)P.H_in * P.W_in;
     const int4 ti = shared ? g.jinfo[tile] : P.tile_info[tile];
-    if (ti.y == 0) {
-      // No rows to stage.  Where the tile's subapertures have no weight but
-      // zeros (the pupil, or the repair's source mask, leaves none of their
-      // pixels) their slopes are 0 and nothing else writes them; a tile that
-      // did not fit (ti.w < 0) is reported through the plan's status.
-      if (!VJP && ti.w == 0) {
-        int a0, a1;
-        chunk_range(P, chunk_id, a0, a1);
-        const int ns = shared ? g.jNS : P.ns;
-        for (int s = tid; s < ns; s += BLOCK) {
-          const int e = shared ? g.jslots[(size_t)tile * ns + s] : P.slot_kk[(size_t)tile * ns + s];
-          if (e < 0) continue;
-          const PairDesc* L = shared ? g.pairs + (e >> 20) : nullptr;
-          const int nv = shared ? L->nv : P.nv, k = shared ? e & 0xFFFFF : e;
-          float* o = (shared ? L->out : P.out) + k;
-          for (int l = 0; l < NPL; ++l)
-            for (int a = a0; a < a1; ++a) {
-              float* r = o + ((size_t)(plane + l - g.out_plane0) * P.n_act + a) * 2 * nv;
-              *(gfloat_t*)r = 0.f;
-              *(gfloat_t*)(r + nv) = 0.f;
-            }
-        }
-      }
-      continue;
-    }
+    if (ti.y == 0) continue;   // empty tile
     // ti.w > 0: rows staged at that pitch from the tile's leftmost staged
     // column ti.z (IF pixel (y, x) at (y - y0) * pitch + x - ti.z), row table
     // (first, end) of each row's staged columns relative to ti.z;
@@ -569,8 +537,12 @@ im_stream_kernel(StreamArgs g) {
 #pragma unroll
           for (int c = 0; c < PW; ++c) wx[l][i][c] = wy[l][i][c] = 0.f;
     }
-    int a0, a1;
-    chunk_range(P, chunk_id, a0, a1);
+    // chunk = P.chunk actuators, or (P.chunk == 0) an even split of the
+    // actuators over P.n_chunks chunks
+    const int a0 = P.chunk > 0 ? chunk_id * P.chunk
+                               : (int)((long long)chunk_id * P.n_act / P.n_chunks);
+    const int a1 = P.chunk > 0 ? min(P.n_act, a0 + P.chunk)
+                               : (int)((long long)(chunk_id + 1) * P.n_act / P.n_chunks);
     const int n_grp = a1 > a0 ? (a1 - a0 + KP - 1) / KP : 0;
     // XCD sync (single pair only; E >= NST - 1 groups is guaranteed by the host)
     const bool sync_on = (!BATCH || g.pairs == nullptr) && g.sync_every > 0;

@@ -91,3 +91,22 @@ def test_nothing_left_by_the_repair(gpu_lib, n_sub, p, n_act, core):
     got = S.im_build_repaired(torch.from_numpy(F).cuda(), torch.from_numpy(M).cuda(), A, wfs,
                               out=out).cpu().numpy()
     assert np.max(np.abs(got - ref)) <= 1e-5 * np.abs(ref).max()
+
+
+def test_every_configuration(gpu_lib):
+    import torch
+    S = gpu_lib
+    n_sub, p, grid = 8, 10, 96
+    pupil, valid, _, A, _, F, lit = problem(S, n_sub, p, grid, 40, 20)
+    A, _ = S.affine_from_misreg((0.2, -0.3, 0.01, 1.0), grid, grid, 80, 80)
+    wfs = S.Wfs.from_numpy(pupil, p, valid, device="cuda:0")
+    ref = oim.im_build(F, A[:, :2], A[:, 2], pupil, p, valid[lit])
+    Fd = torch.from_numpy(F).cuda()
+    cands = S.im_candidates(wfs, A)
+    assert any(c["schedule"] != 0 for c in cands)
+    for c in cands:
+        S.im_set_config(wfs, A, c)
+        ws = S.im_plan(wfs, A, device=Fd.device)
+        out = torch.full((40, 2 * len(valid)), 777.0, device="cuda")
+        check(S.im_apply(Fd, A, wfs, ws, out=out), ref, lit, 1e-5)
+    S.autotune_clear()
