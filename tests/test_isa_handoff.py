@@ -47,7 +47,7 @@ def kernels(asm_text, name):
     return out
 
 
-def test_checker_flags_a_store_in_flight():
+def test_scan_finds_a_store_in_flight():
     store = "  global_store_dwordx2 v[2:3], v[0:1], off sc1"
     assert unfinished([store, "  s_waitcnt lgkmcnt(0)", "  s_barrier"]) == (1, [1])
     assert unfinished([store, "  s_waitcnt vmcnt(0)", "  s_barrier"]) == (1, [])
